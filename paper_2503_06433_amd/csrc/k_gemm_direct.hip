@@ -1,0 +1,378 @@
+// GEMM for few token rows: C[M,N] = A[M,K] * Wt[N,K]^T without a block-wide LDS tile.  Serves the 16-bit types up to
+// DIRECT_MAX_M16 token rows (chat-sized decode batches) and fp32.
+//
+// What bounds it: the weight stream (every weight is used by at most four matrix instructions), and at these
+// sizes the number of launches.  So there is no LDS staging and no barrier in the K loop: a block owns NT tiles of
+// 16 weight rows and all the token rows (MT tiles of 16), its W waves take the 128-byte K chunks of those rows
+// in turn, each wave with DEPTH chunks on their way, and the W partial tiles meet in LDS once, at the end.
+// K is therefore never cut over blocks: no partial sums in memory and no second kernel, and the epilogue
+// (RMSNorm factor, SwiGLU, residual) runs on the finished sums.
+//
+// Operand order needs neighbouring lanes on different rows, and a load in that order takes the vector L1 64 clocks per
+// kilobyte instead of 16 (four lanes of a quad on four lines): at 64 token rows that alone held the kernel to 1.4
+// times its present time.  So the loads cover whole lines with neighbouring lanes, into registers (that is what
+// is in flight), and every chunk passes through 2 KB of LDS that belong to the wave alone, once written and once read.
+//
+// The RMSNorm factor of a token row needs sum(x^2) over the whole row, and the block has the whole row passing
+// through its registers anyway: one more matrix instruction per token tile multiplies the token fragment with
+// itself, the diagonal of that 16 x 16 product is the 16 sums of squares (products exact, sums in fp32 like the
+// statistics kernel's).  That takes the statistics kernel out of the chain.
+//
+// The product is formed transposed (weights as the row operand): accumulator register v of lane l is
+// column 4 * (l / 16) + v of token l % 16, four consecutive output columns per lane.
+#include "ss_device.h"
+#include "ss_kernels.h"
+
+namespace SS_NS {
+using namespace ssk;
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+namespace {
+
+// the two k-steps of a 32-byte piece of both operands
+template <typename T> struct DirectOp;
+template <> struct DirectOp<bf16_t> {
+    static constexpr int CH = 64;                            // elements of a 128-byte chunk
+    static __device__ __forceinline__ f32x4_t mul(const u32x4_t* a, const u32x4_t* b, f32x4_t c) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) c = SS_MFMA_16x16x32(__builtin_bit_cast(half8_t, a[h]), __builtin_bit_cast(half8_t, b[h]), c, 0, 0, 0);
+        return c;
+    }
+};
+template <> struct DirectOp<float> {
+    static constexpr int CH = 32;
+    static __device__ __forceinline__ f32x4_t mul(const u32x4_t* a, const u32x4_t* b, f32x4_t c) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[h][e]), __uint_as_float(b[h][e]), c, 0, 0, 0);
+        return c;
+    }
+};
+
+// silu(g) * u: on the hardware's exponential and reciprocal where the result is rounded to 16 bits, by the
+// library's exponential and an IEEE division in fp32
+template <typename T> __device__ __forceinline__ float direct_swiglu(float g, float u);
+template <> __device__ __forceinline__ float direct_swiglu<bf16_t>(float g, float u) {
+    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f)) * u;
+}
+template <> __device__ __forceinline__ float direct_swiglu<float>(float g, float u) { return g / (1.0f + expf(-g)) * u; }
+
+template <typename T> __device__ __forceinline__ void store4(T* p, const float* o);
+template <> __device__ __forceinline__ void store4<float>(float* p, const float* o) {
+    *reinterpret_cast<f32x4_t*>(p) = f32x4_t{o[0], o[1], o[2], o[3]};
+}
+template <> __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, const float* o) {
+    uint2 w;
+    w.x = pack_bf16x2(o[0], o[1]);
+    w.y = pack_bf16x2(o[2], o[3]);
+    *reinterpret_cast<uint2*>(p) = w;
+}
+
+}  // namespace
+
+// SwiGLU: a tile is 8 gate rows and the 8 up rows that belong to them, so a block of NT tiles has 8 NT output columns.
+// Gate rows come in blocks of gate_blk, each followed by its up rows (gate_blk = N / 2: all gate rows first).
+template <typename T, int MT, int NT, int W, int DEPTH, int EPI>
+__global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict__ A, int lda, const T* __restrict__ Wt,
+                                                             void* __restrict__ Cv, int ldc, const T* __restrict__ R,
+                                                             int M, int N, int K, int gate_blk, float norm_eps,
+                                                             int vec_ok) {
+    constexpr int CH = DirectOp<T>::CH;
+    constexpr int EV = VecOf<T>::N;
+    constexpr bool SWI = EPI == EPI_SWIGLU;
+    constexpr int TO = SWI ? 8 : 16;                                         // output columns of a tile
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);                         // [W][NT * MT][64]
+    float* sq = reinterpret_cast<float*>(smem + (size_t)W * NT * MT * 1024);     // [W][MT * 16]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 15, lg = lane >> 4;
+    const int m0 = blockIdx.y * (16 * MT);
+    const int n_out = SWI ? N / 2 : N;
+    const int o0 = blockIdx.x * (TO * NT);                                   // first output column of the block
+    const bool norm = norm_eps >= 0.f;
+
+    // Loads cover whole 128-byte lines with neighbouring lanes: load h of a tile brings rows 8h .. 8h + 7, lane l row
+    // 8h + l / 8, piece l % 8 (rows beyond the matrix: the last one, never stored).
+    const int sr = lane >> 3, sp = lane & 7;
+    const T* wp[NT][2];
+    const T* xp[MT][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r16 = 8 * h + sr;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            int row;
+            if (SWI) {
+                int col = o0 + 8 * j + (r16 & 7);
+                col = col < n_out ? col : n_out - 1;
+                row = (col / gate_blk) * (2 * gate_blk) + col % gate_blk + (r16 >> 3) * gate_blk;
+            } else {
+                row = o0 + 16 * j + r16;
+                row = row < N ? row : N - 1;
+            }
+            wp[j][h] = Wt + (size_t)row * K;
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            int row = m0 + 16 * i + r16;
+            row = row < M ? row : M - 1;
+            xp[i][h] = A + (size_t)row * lda;
+        }
+    }
+    // this wave's transposer: one 2 KB image of a 16-row chunk per tile, 16-byte pieces XOR-swizzled with the row
+    uint8_t* tr = smem + (size_t)wave * ((NT + MT) * 2048);
+    int st_off[2], ld_off[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = 8 * h + sr;
+        st_off[h] = r * 128 + ((sp ^ ((r >> 1) & 7)) << 4);
+        ld_off[h] = lr * 128 + (((4 * h + lg) ^ ((lr >> 1) & 7)) << 4);
+    }
+    f32x4_t acc[NT][MT], gram[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        gram[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[j][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+
+    // chunks of this wave: wave, wave + W, ...; the pieces of the last one that lie beyond K count as zeros
+    const int nch = (K + CH - 1) / CH;
+    struct Buf { u32x4_t w[NT][2], x[MT][2]; } buf[DEPTH];
+    auto load_full = [&](int d, int c) {
+        const size_t k0 = (size_t)c * CH + sp * EV;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) buf[d].w[j][h] = *reinterpret_cast<const u32x4_t*>(wp[j][h] + k0);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) buf[d].x[i][h] = *reinterpret_cast<const u32x4_t*>(xp[i][h] + k0);
+        }
+    };
+    auto load = [&](int d, int c) {
+        const u32x4_t z = {0u, 0u, 0u, 0u};
+        const bool in = (long long)c * CH + sp * EV < K;
+        const size_t k0 = in ? (size_t)c * CH + sp * EV : 0;                 // some piece of the row, dropped below
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(wp[j][h] + k0);
+                buf[d].w[j][h] = in ? v : z;
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(xp[i][h] + k0);
+                buf[d].x[i][h] = in ? v : z;
+            }
+        }
+    };
+    // through the transposer into operand order (a wave's LDS operations execute in order: no barrier)
+    auto multiply = [&](int d) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) *reinterpret_cast<u32x4_t*>(tr + j * 2048 + st_off[h]) = buf[d].w[j][h];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) *reinterpret_cast<u32x4_t*>(tr + (NT + i) * 2048 + st_off[h]) = buf[d].x[i][h];
+        }
+        u32x4_t wf[NT][2], xf[MT][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) wf[j][h] = *reinterpret_cast<const u32x4_t*>(tr + j * 2048 + ld_off[h]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) xf[i][h] = *reinterpret_cast<const u32x4_t*>(tr + (NT + i) * 2048 + ld_off[h]);
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[j][i] = DirectOp<T>::mul(wf[j], xf[i], acc[j][i]);
+            if (norm) gram[i] = DirectOp<T>::mul(xf[i], xf[i], gram[i]);
+        }
+    };
+    // whole rounds of DEPTH chunks that lie inside K run a round ahead without a test; what is left (fewer than DEPTH
+    // whole chunks, and the one that K cuts) is loaded behind the last of them
+    const int whole = K / CH;
+    const int full = (whole > wave ? (whole - wave + W - 1) / W : 0) / DEPTH;
+    int c = wave;
+    auto load_rest = [&](int d, int at) { if (at < nch) load(d, at); };
+    if (full > 0) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) load_full(d, c + d * W);
+        for (int r = 1; r < full; ++r) {
+            c += DEPTH * W;
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                multiply(d);
+                load_full(d, c + d * W);
+            }
+        }
+        c += DEPTH * W;
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            multiply(d);
+            load_rest(d, c + d * W);
+        }
+    } else {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) load_rest(d, c + d * W);
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+        if (c + d * W < nch) multiply(d);
+    // ---- the W partial tiles meet (in the LDS of the transposers)
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) red[(wave * (NT * MT) + j * MT + i) * 64 + lane] = acc[j][i];
+    if (norm) {
+        const int v = lr - 4 * lg;                                           // register that holds the diagonal
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+            if (v >= 0 && v < 4) sq[wave * (MT * 16) + i * 16 + lr] = v == 0 ? gram[i][0] : v == 1 ? gram[i][1] : v == 2 ? gram[i][2] : gram[i][3];
+    }
+    __syncthreads();
+    constexpr int LO = SWI ? 32 : 64;                                        // four-column pieces of an output tile
+    for (int p = threadIdx.x; p < NT * MT * LO; p += 64 * W) {
+        const int l = p % LO, t = p / LO, i = t % MT, j = t / MT;
+        const int tok = m0 + 16 * i + (l & 15), col = o0 + TO * j + 4 * (l >> 4);
+        if (tok >= M || col >= n_out) continue;
+        auto sum = [&](int ll) {
+            f32x4_t s = red[(j * MT + i) * 64 + ll];
+#pragma unroll
+            for (int w = 1; w < W; ++w) s += red[(w * (NT * MT) + j * MT + i) * 64 + ll];
+            return s;
+        };
+        float rs = 1.0f;
+        if (norm) {
+            float ss = 0.f;
+#pragma unroll
+            for (int w = 0; w < W; ++w) ss += sq[w * (MT * 16) + i * 16 + (l & 15)];
+            rs = 1.0f / sqrtf(ss / (float)K + norm_eps);
+        }
+        float o[4];
+        const f32x4_t s = sum(l);
+        if (SWI) {
+            const f32x4_t u = sum(l + 32);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = direct_swiglu<T>(s[e] * rs, u[e] * rs);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = s[e] * rs;
+        }
+        const size_t off = (size_t)tok * ldc + col;
+        const int cols = n_out - col < 4 ? n_out - col : 4;
+        if (EPI == EPI_RESIDUAL)
+            for (int e = 0; e < cols; ++e) o[e] += ldf(R + off + e);
+        if (EPI == EPI_STORE_F32) {
+            float* C = reinterpret_cast<float*>(Cv);
+            if (vec_ok && cols == 4) store4<float>(C + off, o);
+            else for (int e = 0; e < cols; ++e) C[off + e] = o[e];
+        } else {
+            T* C = reinterpret_cast<T*>(Cv);
+            if (vec_ok && cols == 4) store4<T>(C + off, o);
+            else for (int e = 0; e < cols; ++e) stf(C + off + e, o[e]);
+        }
+    }
+}
+
+template <typename T, int MT, int NT, int W, int DEPTH>
+static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
+                                int epi, int gate_blk, float norm_eps, hipStream_t s) {
+    const int n_out = epi == EPI_SWIGLU ? N / 2 : N, per = (epi == EPI_SWIGLU ? 8 : 16) * NT;
+    const dim3 grid((unsigned)((n_out + per - 1) / per), (unsigned)((M + 16 * MT - 1) / (16 * MT)));
+    if (grid.y > 65535) return hipErrorInvalidValue;
+    constexpr size_t LDS_TR = (size_t)W * (NT + MT) * 2048, LDS_RED = (size_t)W * NT * MT * 1024 + (size_t)W * MT * 64;
+    constexpr size_t LDS = LDS_TR > LDS_RED ? LDS_TR : LDS_RED;
+    const size_t out_es = epi == EPI_STORE_F32 ? 4 : sizeof(T);
+    const int vec_ok = ldc % 4 == 0 && ((uintptr_t)C & (4 * out_es - 1)) == 0;
+    const T* a = (const T*)A;
+    const T* w = (const T*)Wt;
+    const T* r = (const T*)R;
+#define SS_GO(E)                                                                                                 \
+    {                                                                                                           \
+        auto kfn = gemm_direct_kernel<T, MT, NT, W, DEPTH, E>;                                                  \
+        if constexpr (LDS > 65536) {                                                                            \
+            static bool attr_set = false;                                                                       \
+            if (!attr_set) {                                                                                    \
+                hipError_t e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS); \
+                if (e != hipSuccess) return e;                                                                  \
+                attr_set = true;                                                                                \
+            }                                                                                                   \
+        }                                                                                                       \
+        kfn<<<grid, 64 * W, LDS, s>>>(a, lda, w, C, ldc, r, M, N, K, gate_blk, norm_eps, vec_ok);               \
+    }
+    switch (epi) {
+        case EPI_STORE: SS_GO(EPI_STORE) break;
+        case EPI_RESIDUAL:
+            if (!R) return hipErrorInvalidValue;
+            SS_GO(EPI_RESIDUAL) break;
+        case EPI_STORE_F32: SS_GO(EPI_STORE_F32) break;
+        case EPI_SWIGLU: SS_GO(EPI_SWIGLU) break;
+        default: return hipErrorInvalidValue;
+    }
+#undef SS_GO
+    return hipGetLastError();
+}
+
+// Which products come here.  16-bit types: up to 64 token rows.  Measured against the 128 x 128 tile kernel with its
+// statistics, split-K and reduce launches, on the projections of the 7B layer and of the 13B / 70B shards: 1 row
+// 1.5-2.9 times, 32 rows 1.3-2.5 times, 64 rows 1.1-2.3 times as fast (QKV 12288 x 4096: 31.7 -> 18.9 us at 1 row =
+// 5.3 TB/s of weights, 33.1 -> 21.5 at 32, 37.1 -> 24.9 at 64; down 4096 x 11008: 41.5 -> 21.8, 43.7 -> 28.8,
+// 45.1 -> 37.2).  fp32: every aligned shape.  Against the 64 x 64 FMA kernel, 256-wide layer of 4 rows: QKV 28.1 ->
+// 3.8 us, down (K = 688) 60.4 -> 4.0; 4096 x 4096 at 64 rows 469 -> 42 us, at 2048 rows 1803 -> 911 us.
+constexpr int DIRECT_MAX_M16 = 64;
+
+bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int K, int lda, int epi) {
+    const int ev = dt == F32 ? 4 : 8;
+    if (M <= 0 || N <= 0 || K <= 0 || K % ev != 0 || lda % ev != 0) return false;
+    if (((uintptr_t)A & 15) != 0 || ((uintptr_t)Wt & 15) != 0) return false;
+    if ((epi == EPI_SWIGLU && N % 64 != 0) || (epi == EPI_SWIGLU_HALVES && N % 2 != 0)) return false;
+    return dt == F32 ? M <= 65535 * 16 : M <= DIRECT_MAX_M16;
+}
+
+// NT (tiles of weight rows per block): more tiles mean fewer times that the token rows are read (every block reads
+// them all), fewer tiles more blocks.  The line is where the blocks still fill the 256 compute units: up to 256 tiles
+// one per block, up to 512 two, beyond that three (gate/up 22016 x 4096 at 16 rows, blocks of 1 / 2 / 3 / 6 tiles:
+// 36.0 / 44 / 34.6 / 36.0 us; QKV 12288 x 4096 at 64 rows: 53 / 37 / 24.9 us).  DEPTH 2 (16 KB and more on their way per
+// wave) except for the widest blocks, whose single chunk is as large and which would spill.
+template <typename T, int MT>
+static hipError_t pick_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
+                              int epi, int gate_blk, float norm_eps, hipStream_t s) {
+    if constexpr (MT == 1)
+        if (M <= 8 && sizeof(T) == 2) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s);
+    const long long tiles = (long long)((N + 15) / 16) * ((M + 16 * MT - 1) / (16 * MT));
+    if (tiles <= 256) return launch_direct<T, MT, 1, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s);
+    if (tiles <= 512) return launch_direct<T, MT, 2, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s);
+    return launch_direct<T, MT, 3, 8, 1>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s);
+}
+
+hipError_t gemm_direct(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
+                       int epi, float norm_eps, hipStream_t s) {
+    if (!gemm_direct_takes(dt, A, Wt, M, N, K, lda, epi)) return hipErrorInvalidValue;
+    const int gate_blk = epi == EPI_SWIGLU ? 32 : N / 2;
+    if (epi == EPI_SWIGLU_HALVES) epi = EPI_SWIGLU;
+#define SS_GO(TT, MT) return pick_direct<TT, MT>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s)
+#ifndef SS_HALF_F16          // fp32 is the same code in both builds of this file: only the first has it
+    if (dt == F32) {
+        if (M <= 16) SS_GO(float, 1);
+        SS_GO(float, 2);
+    }
+#else
+    if (dt == F32) return hipErrorInvalidValue;
+#endif
+    if (M <= 16) SS_GO(bf16_t, 1);
+    if (M <= 32) SS_GO(bf16_t, 2);
+    if (M <= 48) SS_GO(bf16_t, 3);
+    SS_GO(bf16_t, 4);
+#undef SS_GO
+}
+
+}  // namespace SS_NS

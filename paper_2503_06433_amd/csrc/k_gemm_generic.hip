@@ -1,6 +1,7 @@
 // Plain LDS-tiled FMA GEMM: C[M,N] = A[M,K] * Wt[N,K]^T with fp32 accumulation.
-// Serves the fp32 configuration and any shape the MFMA kernel does not take
-// (K not a multiple of 64).  64x64 output tile per 256-thread block, 16-deep
+// Serves the shapes that the MFMA kernels do not take (16-bit types with K not a
+// multiple of 64, fp32 with rows that are not 16-byte aligned) and is the reference
+// path of SS_FORCE_GENERIC.  64x64 output tile per 256-thread block, 16-deep
 // K slices staged through LDS as floats, 4x4 outputs per thread.  Any M, N, K.
 #include "ss_device.h"
 #include "ss_kernels.h"
@@ -84,12 +85,22 @@ static hipError_t launch_generic(const void* A, int lda, const void* Wt, void* C
 hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N,
                           int K, int epi, hipStream_t s, float* ws, size_t ws_bytes, int max_rounds, const float* rs);
 bool gemm_mfma_supported(int M, int N, int K, int lda, int ldc, int epi);
+bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int K, int lda, int epi);
+hipError_t gemm_direct(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
+                       int epi, float norm_eps, hipStream_t s);
+
+bool gemm_norms_itself(int dt, const void* A, int lda, const void* Wt, int M, int N, int K, int epi, bool force_generic) {
+    return !force_generic && gemm_direct_takes(dt, A, Wt, M, N, K, lda, epi);
+}
 
 hipError_t gemm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N,
                    int K, int epi, bool force_generic, hipStream_t s, float* ws, size_t ws_bytes, int max_rounds,
-                   const float* row_scale) {
+                   const float* row_scale, float norm_eps) {
     if (M <= 0 || N <= 0) return hipSuccess;
     if (K <= 0 || lda < K || !A || !Wt || !C) return hipErrorInvalidValue;
+    if (!row_scale && gemm_norms_itself(dt, A, lda, Wt, M, N, K, epi, force_generic))
+        return gemm_direct(dt, A, lda, Wt, C, ldc, R, M, N, K, epi, norm_eps, s);
+    if (norm_eps >= 0.f || epi == EPI_SWIGLU_HALVES) return hipErrorInvalidValue;     // only the kernel above does these
     if (dt == BF16 && !force_generic && gemm_mfma_supported(M, N, K, lda, ldc, epi))
         return gemm_mfma_bf16(A, lda, Wt, C, ldc, R, M, N, K, epi, s, ws, ws_bytes, max_rounds, row_scale);
     if (epi == EPI_SWIGLU) return hipErrorInvalidValue;

@@ -22,6 +22,7 @@ enum Epilogue {
     EPI_SWIGLU = 2,     // weight rows come in blocks of 32 gate rows followed by the
                         // matching 32 up rows; C[m, j] = silu(gate_j) * up_j, C has N/2 columns
     EPI_STORE_F32 = 3,  // C is float regardless of the input dtype
+    EPI_SWIGLU_HALVES = 4,   // as EPI_SWIGLU with the N / 2 gate rows first and the up rows behind them
 };
 
 // Paged cache geometry of one shard and one layer.
@@ -110,7 +111,7 @@ using namespace ssk;
 // C[M,N] = A[M,K] * Wt[N,K]^T.  A row-major with leading dimension lda, Wt
 // row-major [N,K] (K contiguous), C row-major with leading dimension ldc.
 // force_generic selects the plain LDS-tiled FMA kernel (any shape, any dtype);
-// otherwise bf16 with K % 64 == 0 runs on the MFMA kernel.
+// otherwise few rows (and fp32) run on the direct kernel and bf16 with K % 64 == 0 on the MFMA tile kernels.
 // `ws` is an optional float workspace of ws_bytes for split-K partial sums (used
 // when the output has too few tiles to occupy the chip, as at decode batch sizes).
 // The large-output bf16 kernel runs as persistent blocks that own their CUs until the launch is done;
@@ -120,10 +121,13 @@ using namespace ssk;
 // activation or store: the RMSNorm factor of token m when A holds the raw activations and the gains are
 // folded into the weight rows.  Not combined with EPI_RESIDUAL or EPI_STORE_F32 by the large-output and
 // fp32-output kernels (refused there).
+// norm_eps >= 0 instead of a row_scale: the product works out the factor rsqrt(mean(A[m, 0..K)^2) + norm_eps) of its
+// rows by itself.  Only where gemm_norms_itself says so (few rows, or fp32), refused elsewhere; EPI_SWIGLU_HALVES as well.
+bool gemm_norms_itself(int dt, const void* A, int lda, const void* Wt, int M, int N, int K, int epi, bool force_generic);
 hipError_t gemm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int ldc,
                    const void* R, int M, int N, int K, int epi, bool force_generic,
                    hipStream_t s, float* ws = nullptr, size_t ws_bytes = 0, int max_rounds = 0,
-                   const float* row_scale = nullptr);
+                   const float* row_scale = nullptr, float norm_eps = -1.0f);
 
 // out[t,:] = x[t,:] * rsqrt(mean(x[t,:]^2) + eps) * g
 hipError_t rmsnorm(int dt, const void* x, const void* g, void* out, int T, int H, float eps,

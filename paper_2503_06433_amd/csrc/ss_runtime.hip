@@ -804,6 +804,25 @@ int mark_meta_used(ss_ctx* c, MetaSlot* ms, hipStream_t stream) {
             return fail((c), e_ == hipErrorInvalidValue ? SS_EINVAL : SS_EHIP, "%s: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
+// C = norm(x) W, T rows of `hidden`.  RMSNorm is not a pass of its own: the gains are folded into the rows of W at load
+// time, the product runs on the raw activations and its epilogue multiplies every token row by
+// rsqrt(mean(x^2) + eps).  Products of few rows work that factor out from the rows that pass through them; for the
+// others a read-only pass over x provides it (T floats).
+int norm_gemm(ss_ctx* c, const void* x, const void* wt, void* out, int ldc, int T, int N, int epi, hipStream_t st) {
+    const int H = c->m.hidden;
+    const bool itself = c->m.rms_eps >= 0.f && SSK_CALL(c, gemm_norms_itself, x, H, wt, T, N, H, epi, c->force_generic);
+    if (!itself) {
+        int rc;
+        if ((rc = ensure_buf(c, c->ws_rs, (size_t)T * sizeof(float)))) return rc;
+        ProfScope ps(c, 4, st);
+        K_TRY(c, SSK_CALL(c, row_scale, x, (float*)c->ws_rs.p, T, H, c->m.rms_eps, st));
+    }
+    ProfScope ps(c, 0, st);
+    K_TRY(c, SSK_CALL(c, gemm_nt, x, H, wt, out, ldc, nullptr, T, N, H, epi, c->force_generic, st, (float*)c->ws_splitk.p,
+                      c->ws_splitk.cap, c->gemm_rounds, itself ? nullptr : (const float*)c->ws_rs.p, itself ? c->m.rms_eps : -1.0f));
+    return SS_OK;
+}
+
 int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, const void* x_in, void* out,
                    bool residual, hipStream_t st) {
     const ss_model_cfg& m = c->m;
@@ -813,7 +832,6 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     if (rc) return rc;
     const int T = ms->bm.T, H = m.hidden, d = m.head_dim;
     const int nqkv = (s->nq_l + 2 * s->nkv_l) * d;
-    if ((rc = ensure_buf(c, c->ws_rs, (size_t)T * sizeof(float)))) return rc;
     if ((rc = ensure_buf(c, c->ws_qkv, (size_t)T * nqkv * c->es))) return rc;
     if ((rc = ensure_buf(c, c->ws_attn, (size_t)T * s->nq_l * d * c->es))) return rc;
     if (decode) {
@@ -822,19 +840,7 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     }
     if (c->dt != SS_F32 && T <= 2048 && (rc = ensure_buf(c, c->ws_splitk, (size_t)128 << 20))) return rc;
     const ssk::KvLayer kv = kv_layer(c, s, ll);
-    // RMSNorm is not a pass of its own: the gains are folded into the rows of Wqkv at load time, the product
-    // runs on the raw activations and its epilogue multiplies every token row by rsqrt(mean(x^2) + eps), which
-    // a read-only pass over x provides (T floats)
-    {
-        ProfScope ps(c, 4, st);
-        K_TRY(c, SSK_CALL(c, row_scale, x_in, (float*)c->ws_rs.p, T, H, m.rms_eps, st));
-    }
-    {
-        ProfScope ps(c, 0, st);
-        K_TRY(c, SSK_CALL(c, gemm_nt, x_in, H, w.wqkv_t, c->ws_qkv.p, nqkv, nullptr, T, nqkv, H, ssk::EPI_STORE,
-                              c->force_generic, st, (float*)c->ws_splitk.p, c->ws_splitk.cap, c->gemm_rounds,
-                              (const float*)c->ws_rs.p));
-    }
+    if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, st))) return rc;
     {
         ProfScope ps(c, 4, st);
         K_TRY(c, SSK_CALL(c, rope_kvwrite, c->ws_qkv.p, s->nq_l, s->nkv_l, c->d_rope, ms->bm, kv, st));
@@ -861,25 +867,14 @@ int run_mlp_phase(ss_ctx* c, Shard* s, int ll, int T, const void* x1, void* out,
     const LayerW& w = s->w[ll];
     const int H = m.hidden, F = s->f_l;
     int rc;
-    if ((rc = ensure_buf(c, c->ws_rs, (size_t)T * sizeof(float)))) return rc;
     if ((rc = ensure_buf(c, c->ws_act, (size_t)T * F * c->es))) return rc;
     if (c->dt != SS_F32 && T <= 2048 && (rc = ensure_buf(c, c->ws_splitk, (size_t)128 << 20))) return rc;
-    {
-        ProfScope ps(c, 4, st);
-        K_TRY(c, SSK_CALL(c, row_scale, x1, (float*)c->ws_rs.p, T, H, m.rms_eps, st));      // as in the attention phase
-    }
-    if (w.gu_interleaved) {
-        ProfScope ps(c, 0, st);
-        K_TRY(c, SSK_CALL(c, gemm_nt, x1, H, w.wgu_t, c->ws_act.p, F, nullptr, T, 2 * F, H, ssk::EPI_SWIGLU,
-                              false, st, (float*)c->ws_splitk.p, c->ws_splitk.cap, c->gemm_rounds, (const float*)c->ws_rs.p));
+    const int halves = w.gu_interleaved ? ssk::EPI_SWIGLU : ssk::EPI_SWIGLU_HALVES;
+    if (w.gu_interleaved || (m.rms_eps >= 0.f && SSK_CALL(c, gemm_norms_itself, x1, H, w.wgu_t, T, 2 * F, H, halves, c->force_generic))) {
+        if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_act.p, F, T, 2 * F, halves, st))) return rc;
     } else {
         if ((rc = ensure_buf(c, c->ws_gu, (size_t)T * 2 * F * c->es))) return rc;
-        {
-            ProfScope ps(c, 0, st);
-            K_TRY(c, SSK_CALL(c, gemm_nt, x1, H, w.wgu_t, c->ws_gu.p, 2 * F, nullptr, T, 2 * F, H,
-                                  ssk::EPI_STORE, c->force_generic, st, (float*)c->ws_splitk.p, c->ws_splitk.cap, c->gemm_rounds,
-                                  (const float*)c->ws_rs.p));
-        }
+        if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_gu.p, 2 * F, T, 2 * F, ssk::EPI_STORE, st))) return rc;
         ProfScope ps(c, 4, st);
         K_TRY(c, SSK_CALL(c, swiglu, c->ws_gu.p, c->ws_act.p, T, F, st));
     }
