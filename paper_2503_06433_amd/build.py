@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libseesaw_rt.so")
 HOST_SOURCES = ["ss_runtime.hip", "ss_offline.hip"]
 # the kernel files are built twice: brain-float (namespace ssk) and, with SS_HALF_F16, IEEE half (ssk16)
-KERNEL_SOURCES = ["k_elementwise.hip", "k_gemm_generic.hip", "k_gemm_mfma.hip", "k_gemm_direct.hip",
+KERNEL_SOURCES = ["k_elementwise.hip", "k_gemm_generic.hip", "k_gemm_mfma.hip", "k_gemm_direct.hip", "k_gemm_tile.hip",
                   "k_attn_generic.hip", "k_attn_mfma.hip", "k_kv_repack.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]

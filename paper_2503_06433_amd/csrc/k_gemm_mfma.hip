@@ -894,6 +894,11 @@ static hipError_t launch_cfg(const bf16_t* A, int lda, const bf16_t* Wt, bf16_t*
     return hipGetLastError();
 }
 
+bool gemm_tile_supported(const void* A, const void* Wt, const void* C, const void* R, int ldc, int M, int N, int K, int lda, int epi);
+float gemm_tile_estimate(int M, int N, int K, int n_cus, int* pick);
+hipError_t gemm_tile(int pick, const bf16_t* A, int lda, const bf16_t* Wt, void* C, int ldc, const bf16_t* R, int M, int N, int K,
+                     int epi, const float* rs, hipStream_t s);
+
 hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N,
                           int K, int epi, hipStream_t s, float* ws, size_t ws_bytes, int max_rounds, const float* rs) {
     const bf16_t* a = (const bf16_t*)A;
@@ -901,35 +906,38 @@ hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int l
     bf16_t* c = (bf16_t*)C;
     const bf16_t* r = (const bf16_t*)R;
     // Prefill-sized outputs (at least one 256 x 256 tile per CU): the persistent direct-to-LDS kernel.
-    // Smaller outputs (decode batches) are bound by streaming the weights: 128 x 128 tiles with split-K
-    // (partials in fp32, summed by a small second kernel).
     const long long big = (long long)((M + 255) / 256) * ((N + 255) / 256);
     static const long long stream_min = getenv("SS_GEMM_STREAM_MIN_TILES") ? atoll(getenv("SS_GEMM_STREAM_MIN_TILES")) : 256;
     if (big >= stream_min && epi != EPI_STORE_F32 && gemm_mfma_stream_supported(C, R, ldc, M, N, K, lda, epi))
         return launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs);
-    // In between (a thousand tokens or so, as in the decode step of a tensor-parallel shard): too few 256 x 256
-    // tiles for the chip, but long contractions.  The persistent kernel with K cut into ranges, so that tiles x
-    // ranges fill the CUs, with fp32 partial sums and the reduce kernel of the small-tile path; only while the
-    // partial sums stay below the weight bytes (as below) and at least half the CUs get a block.  Measured with
-    // 1024 tokens on the shapes of the k = 8 shard of the 70B layer: gate/up (7168 x 8192) 150 -> 113 us; the
-    // down projection (K = 3584) would lose (73 -> 83 us: its partial sums outweigh its weights) and is excluded
-    // by the rule, as are outputs too narrow to fill the chip even when split (QKV of the shard: 20 tiles).  At 256
-    // tokens (one tile row) the four GEMMs of the 7B layer together go from 232 to 217 us.
+    // Fewer tiles than compute units: the tile kernel, or the persistent kernel, with K cut into ranges so that tiles x
+    // ranges fill the chip where that is needed (fp32 partial sums, summed by the reduce kernel of the small-tile path).
+    // By estimated time: the persistent kernel takes 1.5 us for a slice, the partial sums are read at 4.2 TB/s; split, it
+    // has to be a quarter faster by estimate (at less it lost: 512 x 6912 x 5120 in four ranges 60 us, tiles 54).  The
+    // persistent kernel is left with outputs of 200 tiles and more and, split, with long contractions of few tiles
+    // (512 x 8192 x 28672 in four ranges: 202 + 28 us for the sums, tiles 289; 1500 x 10240 x 8192 whole: 230, tiles 297).
     static const int stream_split = getenv("SS_GEMM_STREAM_SPLIT") ? atoi(getenv("SS_GEMM_STREAM_SPLIT")) : 1;
     static const int stream_split_min_m = getenv("SS_GEMM_STREAM_SPLIT_MIN_M") ? atoi(getenv("SS_GEMM_STREAM_SPLIT_MIN_M")) : 256;
-    if (stream_split && M >= stream_split_min_m && big >= 8 && big < 256 && epi != EPI_STORE_F32 && ws &&
-        gemm_mfma_stream_supported(C, R, ldc, M, N, K, lda, epi) && ((uintptr_t)ws & 15) == 0) {
-        int ks = 1;
-        constexpr int min_slices = 16, min_blocks = 128;      // (64 blocks: the 7B-shape decode GEMMs 217 -> 260 us)
-        while (ks < 8 && big * (ks * 2) <= 288 && (K / 64) % (ks * 2) == 0 && K / 64 / (ks * 2) >= min_slices &&
-               (long long)(ks * 2) * 4 * M <= K && (size_t)(ks * 2) * M * N * sizeof(float) <= ws_bytes)
-            ks *= 2;
-        if (ks > 1 && big * ks >= min_blocks) {
-            hipError_t e = launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs, ks, ws);
-            if (e != hipSuccess) return e;
-            return reduce_partials(ws, ks, c, ldc, r, M, N, epi, rs, s);
+    if (gemm_tile_supported(A, Wt, C, R, ldc, M, N, K, lda, epi)) {
+        constexpr int n_cus = 256;
+        int pick = -1, ks = 0;
+        float us = gemm_tile_estimate(M, N, K, n_cus, &pick);
+        if (stream_split && M >= stream_split_min_m && epi != EPI_STORE_F32 && gemm_mfma_stream_supported(C, R, ldc, M, N, K, lda, epi)) {
+            for (int t = 1; t <= 8 && big * t <= n_cus && (K / 64) % t == 0 && K / 64 / t >= 16; t *= 2) {
+                const size_t bytes = (size_t)t * M * N * sizeof(float);
+                if (t > 1 && (!ws || ((uintptr_t)ws & 15) != 0 || bytes > ws_bytes)) break;
+                float e = 7.f + 1.5f * (K / 64 / t);
+                if (t > 1) e = 1.25f * (e + 5.f + bytes / 4.2e6f);
+                if (e < us) { us = e; ks = t; }
+            }
         }
+        if (ks == 0) return gemm_tile(pick, a, lda, w, C, ldc, r, M, N, K, epi, rs, s);
+        if (ks == 1) return launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs);
+        hipError_t e = launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs, ks, ws);
+        if (e != hipSuccess) return e;
+        return reduce_partials(ws, ks, c, ldc, r, M, N, epi, rs, s);
     }
+    // What is left: rows that are not whole 16-byte pieces (an odd vocabulary), buffers that are not aligned.
     const long long mid = (long long)((M + 127) / 128) * ((N + 127) / 128);
     // split K until every CU has a block, but only while the fp32 partials (8*S*M*N bytes written and
     // read back) stay below twice the weight bytes (2*N*K) they help to stream: S <= K / (2 M).  (With the bound at
