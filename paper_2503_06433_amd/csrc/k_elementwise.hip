@@ -66,37 +66,66 @@ hipError_t rmsnorm(int dt, const void* x, const void* g, void* out, int T, int H
 // r[t] = 1 / sqrt(mean(x[t,:]^2) + eps): the per-row factor of RMSNorm.  The gains are folded into the rows
 // of the weight matrix that follows and the factor is applied in that product's epilogue
 // (norm(x) W = r * (x (g W))), so the normalised activations are never written.  One read of x, T floats out.
-// One wave per row, four rows per block.
-template <typename T>
+// WPR waves per row, up to four 16-byte loads of a lane on their way at once: at decode sizes the launch is a chain of memory
+// latencies (256 rows of 4096: one wave per row and one load at a time 6.5 us, a block per row 4.1; 1024 rows of 8192: 10.7
+// and 5.7 us).
+template <typename T, int WPR>
 __global__ __launch_bounds__(256) void row_scale_kernel(const T* __restrict__ x, float* __restrict__ r, int n_rows, int H,
                                                         float eps) {
-    constexpr int V = VecOf<T>::N;
-    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+    constexpr int V = VecOf<T>::N, STEP = 64 * WPR * V;
+    const int wave = threadIdx.x >> 6;
+    const int t = blockIdx.x * (4 / WPR) + wave / WPR;
     if (t >= n_rows) return;
-    const int lane = threadIdx.x & 63;
+    const int tid = (wave % WPR) * 64 + (threadIdx.x & 63);      // thread of the row
     const T* row = x + (size_t)t * H;
     float ss = 0.f;
-    if ((H % V) == 0) {
-        for (int i = lane * V; i < H; i += 64 * V) {
-            vec16 v = *reinterpret_cast<const vec16*>(row + i);
-            float f[V];
-            unpack16<T>(v, f);
+    auto add = [&](const vec16& v) {
+        float f[V];
+        unpack16<T>(v, f);
 #pragma unroll
-            for (int j = 0; j < V; ++j) ss += f[j] * f[j];
+        for (int j = 0; j < V; ++j) ss += f[j] * f[j];
+    };
+    if ((H % V) == 0) {
+        int i = tid * V;
+        for (; i + 3 * STEP < H; i += 4 * STEP) {
+            vec16 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const vec16*>(row + i + u * STEP);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add(v[u]);
         }
+        if (i + STEP < H) {
+            const vec16 v0 = *reinterpret_cast<const vec16*>(row + i), v1 = *reinterpret_cast<const vec16*>(row + i + STEP);
+            add(v0);
+            add(v1);
+            i += 2 * STEP;
+        }
+        if (i < H) add(*reinterpret_cast<const vec16*>(row + i));
     } else {
-        for (int i = lane; i < H; i += 64) { float f = ldf(row + i); ss += f * f; }
+        for (int i = tid; i < H; i += 64 * WPR) { float f = ldf(row + i); ss += f * f; }
     }
     ss = wave_sum(ss);
-    if (lane == 0) r[t] = 1.0f / sqrtf(ss / (float)H + eps);
+    if constexpr (WPR > 1) {
+        __shared__ float part[WPR];
+        if ((threadIdx.x & 63) == 0) part[wave] = ss;
+        __syncthreads();
+        ss = part[0];
+#pragma unroll
+        for (int w = 1; w < WPR; ++w) ss += part[w];
+    }
+    if (tid == 0) r[t] = 1.0f / sqrtf(ss / (float)H + eps);
 }
 
 hipError_t row_scale(int dt, const void* x, float* r, int T, int H, float eps, hipStream_t s) {
     if (T <= 0) return hipSuccess;
     if (H <= 0) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)((T + 3) / 4);
-    if (dt == F32) row_scale_kernel<float><<<grid, 256, 0, s>>>((const float*)x, r, T, H, eps);
-    else row_scale_kernel<bf16_t><<<grid, 256, 0, s>>>((const bf16_t*)x, r, T, H, eps);
+    // a block per row up to 2048 rows (eight blocks per compute unit); beyond that one wave per row fills the chip
+    const bool few = T <= 2048;
+    const unsigned grid = few ? (unsigned)T : (unsigned)((T + 3) / 4);
+#define SS_GO(TT, WPR) row_scale_kernel<TT, WPR><<<grid, 256, 0, s>>>((const TT*)x, r, T, H, eps)
+    if (dt == F32) { if (few) SS_GO(float, 4); else SS_GO(float, 1); }
+    else { if (few) SS_GO(bf16_t, 4); else SS_GO(bf16_t, 1); }
+#undef SS_GO
     return hipGetLastError();
 }
 
