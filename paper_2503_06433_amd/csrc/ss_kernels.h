@@ -142,6 +142,12 @@ hipError_t swiglu(int dt, const void* gu, void* out, int T, int F, hipStream_t s
 // Gathers rows of an embedding table.
 hipError_t embed_rows(int dt, const void* table, const int32_t* ids, void* out, int n, int H,
                       hipStream_t s);
+// The same with the ids (host memory) passed as kernel arguments, EmbedIds::N a launch.
+struct EmbedIds {
+    static constexpr int N = 512;
+    int32_t v[N];
+};
+hipError_t embed_ids(int dt, const void* table, const int32_t* ids_host, void* out, int n, int H, hipStream_t s);
 
 // Rotates q and k in place inside qkv [T, (n_q + 2 n_kv) d] by the token's
 // position (half-split pairing, angles from the fp32 table rope[pos][d/2][cos,sin]),

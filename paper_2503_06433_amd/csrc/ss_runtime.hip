@@ -2213,6 +2213,15 @@ int ss_embed(ss_ctx* c, const int32_t* ids, int n, void* x_out, void* stream) {
     for (int i = 0; i < n; ++i)
         if (ids[i] < 0 || ids[i] >= c->m.vocab) return fail(c, SS_EINVAL, "token id %d out of range", ids[i]);
     hipStream_t st = (hipStream_t)stream;
+    // Up to four launches' worth of ids travel as kernel arguments: no wait, no copy, and the host is free to prepare the
+    // layers behind it.  More of them (prompts of thousands of tokens) are one copy, which a wait of 20 us does not hurt.
+    if (n <= 4 * ssk::EmbedIds::N) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;      // as with the copy, not part of a captured graph: the
+        HIP_TRY(c, hipStreamIsCapturing(st, &cap));                   // ids are host memory that a replay would not read again
+        if (cap != hipStreamCaptureStatusNone) return fail(c, SS_EHIP, "ss_embed: the stream is capturing");
+        K_TRY(c, SSK_CALL(c, embed_ids, c->d_embed, ids, x_out, n, c->m.hidden, st));
+        return SS_OK;
+    }
     HIP_TRY(c, hipStreamSynchronize(st));
     if ((size_t)n > c->d_ids_cap) {
         if (c->d_ids) HIP_TRY(c, hipFree(c->d_ids));
