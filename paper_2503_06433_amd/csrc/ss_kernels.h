@@ -148,6 +148,8 @@ struct EmbedIds {
     int32_t v[N];
 };
 hipError_t embed_ids(int dt, const void* table, const int32_t* ids_host, void* out, int n, int H, hipStream_t s);
+// Copy of a multiple of 16 bytes from page-locked host memory (its device address), by a kernel.
+hipError_t upload(const void* src_mapped, void* dst, size_t bytes, hipStream_t s);
 
 // Rotates q and k in place inside qkv [T, (n_q + 2 n_kv) d] by the token's
 // position (half-split pairing, angles from the fp32 table rope[pos][d/2][cos,sin]),

@@ -755,7 +755,11 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, hipStream
     memcpy(ms.host + off_upos, unit_pos0.data(), 4 * n_units);
     memcpy(ms.host + off_ucnt, unit_cnt.data(), 4 * n_units);
     if (!pf_items.empty()) memcpy(ms.host + off_pf, pf_items.data(), 4 * pf_items.size());
-    HIP_TRY(c, hipMemcpyAsync(ms.dev, ms.host, total, hipMemcpyHostToDevice, stream));
+    {   // by a kernel: it queues behind the launch before it, where the copy engine costs two hand-overs between queues
+        void* mapped = nullptr;
+        HIP_TRY(c, hipHostGetDevicePointer(&mapped, ms.host, 0));
+        HIP_TRY(c, ssk::upload(mapped, ms.dev, total, stream));
+    }
     ms.bm.tok_seq = (const int32_t*)(ms.dev + off_tok_seq);
     ms.bm.tok_pos = (const int32_t*)(ms.dev + off_tok_pos);
     ms.bm.cu_q = (const int32_t*)(ms.dev + off_cu);
