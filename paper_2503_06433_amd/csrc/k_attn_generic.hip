@@ -83,21 +83,118 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const T* __restrict__
     }
 }
 
+// One query per sequence.  A block per (q head, sequence) whose four waves take every fourth page each and merge their
+// partial results in LDS: the tiled kernel above puts its one query on four of 256 lanes and walks the pages one after
+// the other, two barriers each.  Bound by the latency of the page loads, so a wave requests K and V of a page together.
+// K: four lanes per token, a quarter of the head dimension each.  V^T: a lane owns whole rows of 16 tokens and fetches
+// their weights from the lanes that hold them.  Four sequences of 32 to 40 tokens, fp32, 4 heads of 64: a run of
+// eight tokens through two layers in 612 us with this kernel and 750 us with the tiled one.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __restrict__ qkv, T* __restrict__ out, int n_q,
+                                                                  int n_kv, BatchMeta bm, const T* __restrict__ k_pool,
+                                                                  const T* __restrict__ v_pool, float scale) {
+    constexpr int PS = 16, DS = D / 4, DR = D / 64;
+    constexpr int EV = 16 / (int)sizeof(T);             // elements of a 16-byte load
+    __shared__ float sm[4], sl[4], so[4][D];
+    const int a = blockIdx.x, sq = blockIdx.y;
+    const int q_begin = bm.cu_q[sq];
+    if (bm.cu_q[sq + 1] - q_begin != 1) return;
+    const int p = bm.kv_before[sq], n_pages = p / PS + 1;
+    const int g = a / (n_q / n_kv);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int tok = lane >> 2, sub = lane & 3;
+    float q[DS], acc[DR];
+    {
+        const T* qp = qkv + (size_t)q_begin * ((size_t)(n_q + 2 * n_kv) * D) + (size_t)a * D + sub * DS;
+#pragma unroll
+        for (int i = 0; i < DS / EV; ++i) unpack16<T>(*reinterpret_cast<const vec16*>(qp + i * EV), q + i * EV);
+#pragma unroll
+        for (int e = 0; e < DS; ++e) q[e] *= scale;
+    }
+#pragma unroll
+    for (int r = 0; r < DR; ++r) acc[r] = 0.f;
+    float m = -INFINITY, l = 0.f;
+    const int32_t* pt = bm.page_tables + (size_t)sq * bm.pt_stride;
+    const size_t page_elems = (size_t)n_kv * PS * D;
+    for (int j = wave; j < n_pages; j += 4) {
+        const T* kp = k_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D + tok * D + sub * DS;
+        const T* vp = v_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D + lane * PS;
+        vec16 kr[DS / EV], vr[DR][PS / EV];
+#pragma unroll
+        for (int i = 0; i < DS / EV; ++i) kr[i] = *reinterpret_cast<const vec16*>(kp + i * EV);
+#pragma unroll
+        for (int r = 0; r < DR; ++r)
+#pragma unroll
+            for (int i = 0; i < PS / EV; ++i) vr[r][i] = *reinterpret_cast<const vec16*>(vp + r * 64 * PS + i * EV);
+        float d = 0.f;
+#pragma unroll
+        for (int i = 0; i < DS / EV; ++i) {
+            float k[EV];
+            unpack16<T>(kr[i], k);
+#pragma unroll
+            for (int e = 0; e < EV; ++e) d = fmaf(q[i * EV + e], k[e], d);
+        }
+        d += __shfl_xor(d, 1, 64);
+        d += __shfl_xor(d, 2, 64);
+        d = (j * PS + tok <= p) ? d : -INFINITY;
+        float mx = d;
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        mx = fmaxf(mx, m);
+        const float ref = mx == -INFINITY ? 0.f : mx;     // scores of -infinity only: weights 0, not NaN, in this share
+        const float alpha = __expf(m - ref), w = __expf(d - ref);
+        m = mx;
+        l = l * alpha + w;
+#pragma unroll
+        for (int r = 0; r < DR; ++r) {
+            float v[PS], sum = acc[r] * alpha;
+#pragma unroll
+            for (int i = 0; i < PS / EV; ++i) unpack16<T>(vr[r][i], v + i * EV);
+#pragma unroll
+            for (int t = 0; t < PS; ++t) sum = fmaf(__shfl(w, 4 * vtok(t, lane), 64), v[t], sum);   // rows lane, lane + 64: one order
+            acc[r] = sum;
+        }
+    }
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) l += __shfl_xor(l, o, 64);
+    if (lane == 0) { sm[wave] = m; sl[wave] = l; }
+#pragma unroll
+    for (int r = 0; r < DR; ++r) so[wave][r * 64 + lane] = acc[r];
+    __syncthreads();
+    if ((int)threadIdx.x < D) {
+        const float M = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+        float num = 0.f, den = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float w = __expf(sm[i] - M);
+            num = fmaf(w, so[i][threadIdx.x], num);
+            den = fmaf(w, sl[i], den);
+        }
+        stf(out + (size_t)q_begin * ((size_t)n_q * D) + (size_t)a * D + threadIdx.x, num / den);
+    }
+}
+
 hipError_t attn_generic(int dt, const void* qkv, void* out, int n_q, int n_kv, const BatchMeta& bm,
                         const KvLayer& kv, hipStream_t s) {
     if (bm.T <= 0 || bm.n_seqs <= 0) return hipSuccess;
     if (kv.page_size != 16 || (kv.d != 64 && kv.d != 128) || n_kv <= 0 || n_q % n_kv != 0 || kv.n_heads != n_kv)
         return hipErrorInvalidValue;
     if (bm.n_seqs > 65535 || n_q > 65535) return hipErrorInvalidValue;
+    // every sequence brings one query: the kernel made for that, whatever the number of cached tokens
+    const bool one = bm.max_q_len == 1;
     dim3 grid((bm.max_q_len + 63) / 64, n_q, bm.n_seqs);
     const float scale = 1.0f / sqrtf((float)kv.d);
 #define SS_GO(TT, DD)                                                                                       \
-    attn_generic_kernel<TT, DD><<<grid, 256, 0, s>>>((const TT*)qkv, (TT*)out, n_q, n_kv, bm,               \
-                                                     (const TT*)kv.k_pool, (const TT*)kv.v_pool, scale)
+    if (one)                                                                                                \
+        attn_generic_decode_kernel<TT, DD><<<dim3(n_q, bm.n_seqs), 256, 0, s>>>(                            \
+            (const TT*)qkv, (TT*)out, n_q, n_kv, bm, (const TT*)kv.k_pool, (const TT*)kv.v_pool, scale);    \
+    else                                                                                                    \
+        attn_generic_kernel<TT, DD><<<grid, 256, 0, s>>>((const TT*)qkv, (TT*)out, n_q, n_kv, bm,           \
+                                                         (const TT*)kv.k_pool, (const TT*)kv.v_pool, scale)
     if (dt == F32) {
-        if (kv.d == 64) SS_GO(float, 64); else SS_GO(float, 128);
+        if (kv.d == 64) { SS_GO(float, 64); } else { SS_GO(float, 128); }
     } else {
-        if (kv.d == 64) SS_GO(bf16_t, 64); else SS_GO(bf16_t, 128);
+        if (kv.d == 64) { SS_GO(bf16_t, 64); } else { SS_GO(bf16_t, 128); }
     }
 #undef SS_GO
     return hipGetLastError();
