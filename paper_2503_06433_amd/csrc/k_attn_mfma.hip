@@ -490,10 +490,10 @@ hipError_t attn_prefill(int dt, const void* qkv, void* out, int n_q, int n_kv, c
 // Decode.  One wave per (work item, kv head).  A work item is a run of pages of
 // one sequence.  All G = n_q / n_kv (<= 16) query heads that share the kv head
 // form the 16 query columns of v_mfma_f32_16x16x32_bf16 (unused columns are
-// zero), so K and V are read from HBM once per group:
-//   accumulator register v of lane l <-> token 4*(l/16) + v, query l%16.
-// Each step covers two pages; k-slot e of lane group g4 is token 4*g4 + e of
-// page A for e < 4 and token 4*g4 + e - 4 of page B for e >= 4.
+// zero), so K and V are read from HBM once per group.  Each step covers two pages, A and B.  The rows of the two score
+// products are tokens 0-7 of A and of B, and tokens 8-15 of A and of B, so that lane group g4 = l/16 holds tokens
+// 4*(g4%2) + v and 8 + 4*(g4%2) + v (v = 0..3) of page A (g4 < 2) or B: the eight tokens that are one 16-byte piece of
+// a row of V^T, and the eight k-slots of the group in the second product.
 // Partial (max, sum, O) of every item go to scratch and are merged per sequence.
 // scratch layout: float [n_items][n_q][D + 4]  (O[D], running max, running sum)
 // ======================================================================
@@ -533,10 +533,9 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
     const int32_t* pt = bm.page_tables + (size_t)sq * bm.pt_stride + page0;
     const size_t page_elems = (size_t)n_kv * 16 * D;
     const size_t head_off = (size_t)g * 16 * D;
-    // tokens 4*g4 .. 4*g4+3 sit at piece ((g4 & 1) << 1 | g4 >> 1) of a V^T row, in rows with bit 3 of the row
-    // index set in the other half of the row (see vpos)
-    const int vpiece = (((g4 & 1) << 1) | (g4 >> 1)) ^ (((lq >> 3) & 1) << 1);
-    const size_t k_lane = head_off + (size_t)lq * D + g4 * 8, v_lane = head_off + (size_t)lq * 16 + 4 * vpiece;
+    // the group's tokens are half g4 & 1 of a V^T row, in rows with bit 3 of the row index set the other half (see vpos)
+    const int vhalf = (g4 & 1) ^ ((lq >> 3) & 1);
+    const size_t k_lane = head_off + (size_t)(lq & 7) * D + g4 * 8, v_lane = head_off + (size_t)lq * 16 + 8 * vhalf;
     // The loop is software-pipelined over page pairs: the K fragments of the next pair (8 KB per wave) are
     // requested right after the score product of this pair has consumed its own, and the V^T fragments of
     // this pair before that product, so that a wave always has 8 to 16 KB on their way instead of the 2 KB
@@ -549,23 +548,20 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
         pgB = pt[ib * stride];
     };
     auto load_k = [&](int pgA, int pgB, Frag* fa, Frag* fb) {
+        const bf16_t* kp = k_pool + (size_t)(lq < 8 ? pgA : pgB) * page_elems + k_lane;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            fa[ks].q = *reinterpret_cast<const vec16*>(k_pool + (size_t)pgA * page_elems + k_lane + ks * 32);
-            fb[ks].q = *reinterpret_cast<const vec16*>(k_pool + (size_t)pgB * page_elems + k_lane + ks * 32);
+            fa[ks].q = *reinterpret_cast<const vec16*>(kp + ks * 32);
+            fb[ks].q = *reinterpret_cast<const vec16*>(kp + 8 * D + ks * 32);
         }
     };
     // one pair of pages: fragments ka / kb hold its K, na / nb receive the K of the next pair
     auto step = [&](auto prefetch, int pi, int pA, int pB, const Frag* ka, const Frag* kb, int nA, int nB, Frag* na, Frag* nb) {
         const bool hasB = pi + 1 < npg;
-        const bf16_t* vA = v_pool + (size_t)pA * page_elems + v_lane;
-        const bf16_t* vB = v_pool + (size_t)pB * page_elems + v_lane;
+        const bf16_t* vp = v_pool + (size_t)(g4 < 2 ? pA : pB) * page_elems + v_lane;
         Frag vf[DT];
 #pragma unroll
-        for (int t = 0; t < DT; ++t) {
-            vf[t].h[0] = *reinterpret_cast<const vec8*>(vA + t * 16 * 16);
-            vf[t].h[1] = *reinterpret_cast<const vec8*>(vB + t * 16 * 16);
-        }
+        for (int t = 0; t < DT; ++t) vf[t].q = *reinterpret_cast<const vec16*>(vp + t * 16 * 16);
         __builtin_amdgcn_sched_barrier(0);
         f32x4_t sA = {0.f, 0.f, 0.f, 0.f}, sB = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -576,12 +572,13 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (decltype(prefetch)::value) load_k(nA, nB, na, nb);
         __builtin_amdgcn_sched_barrier(0);
-        const int posA = (page0 + pi * stride) * 16 + 4 * g4, posB = posA + 16 * stride;
+        const int pos0 = (page0 + (pi + (g4 >> 1)) * stride) * 16 + 4 * (g4 & 1);
+        const bool there = g4 < 2 || hasB;
         float mx = m;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            sA[v] = (posA + v < kv_len) ? sA[v] * scale_log2e : -INFINITY;
-            sB[v] = (hasB && posB + v < kv_len) ? sB[v] * scale_log2e : -INFINITY;
+            sA[v] = (there && pos0 + v < kv_len) ? sA[v] * scale_log2e : -INFINITY;
+            sB[v] = (there && pos0 + 8 + v < kv_len) ? sB[v] * scale_log2e : -INFINITY;
             mx = fmaxf(mx, fmaxf(sA[v], sB[v]));
         }
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
@@ -635,24 +632,49 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
     }
 }
 
-// Merge of the per-item partials: D threads per (q head, sequence), HB heads per block.
+// Merge of the per-item partials: D / 4 threads per (q head, sequence), HB heads per block.  Bound by latency: a
+// sequence has one to a few items, so the maxima, sums and outputs of four of them are requested together.
 template <int D, int HB>
-__global__ __launch_bounds__(D * HB) void attn_decode_merge_kernel(const float* __restrict__ scratch,
-                                                                   bf16_t* __restrict__ out, int n_q, BatchMeta bm,
-                                                                   DecodeWork wk) {
-    const int a = blockIdx.x * HB + threadIdx.x / D, sq = blockIdx.y, e = threadIdx.x % D;
+__global__ __launch_bounds__(D / 4 * HB) void attn_decode_merge_kernel(const float* __restrict__ scratch,
+                                                                       bf16_t* __restrict__ out, int n_q, BatchMeta bm,
+                                                                       DecodeWork wk) {
+    const int a = blockIdx.x * HB + threadIdx.x / (D / 4), sq = blockIdx.y, e = threadIdx.x % (D / 4) * 4;
     if (a >= n_q) return;
     const int i0 = wk.seq_item0[sq], i1 = wk.seq_item0[sq + 1];
-    float M = -INFINITY;
-    for (int i = i0; i < i1; ++i) M = fmaxf(M, scratch[((size_t)i * n_q + a) * (D + 4) + D]);
-    float num = 0.f, den = 0.f;
-    for (int i = i0; i < i1; ++i) {
-        const float* sp = scratch + ((size_t)i * n_q + a) * (D + 4);
-        const float w = fast_exp2(sp[D] - M);
-        num += w * sp[e];
-        den += w * sp[D + 1];
+    float M = -INFINITY, den = 0.f;
+    f32x4_t num = {0.f, 0.f, 0.f, 0.f};
+    for (int i = i0; i < i1; i += 4) {
+        float m[4], l[4];
+        f32x4_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float* sp = scratch + ((size_t)(i + u < i1 ? i + u : i1 - 1) * n_q + a) * (D + 4);
+            m[u] = sp[D];
+            l[u] = sp[D + 1];
+            v[u] = *reinterpret_cast<const f32x4_t*>(sp + e);
+        }
+        float mx = M;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            m[u] = i + u < i1 ? m[u] : -INFINITY;
+            mx = fmaxf(mx, m[u]);
+        }
+        const float ref = mx == -INFINITY ? 0.f : mx;
+        const float alpha = fast_exp2(M - ref);
+        M = mx;
+        num *= alpha;
+        den *= alpha;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float w = fast_exp2(m[u] - ref);
+            num += w * v[u];
+            den += w * l[u];
+        }
     }
-    out[(size_t)bm.cu_q[sq] * ((size_t)n_q * D) + (size_t)a * D + e] = f2bf(num / den);
+    vec8 w;
+    w.w[0] = pack_bf16x2(num[0] / den, num[1] / den);
+    w.w[1] = pack_bf16x2(num[2] / den, num[3] / den);
+    *reinterpret_cast<vec8*>(out + (size_t)bm.cu_q[sq] * ((size_t)n_q * D) + (size_t)a * D + e) = w;
 }
 
 size_t attn_decode_scratch_floats(int n_items, int n_q, int d) { return (size_t)n_items * n_q * (d + 4); }
@@ -672,7 +694,7 @@ hipError_t attn_decode(int dt, const void* qkv, void* out, int n_q, int n_kv, co
     attn_decode_mfma_kernel<128><<<grid, 64, 0, s>>>((const bf16_t*)qkv, n_q, n_kv, bm, wk,
                                                      (const bf16_t*)kv.k_pool, (const bf16_t*)kv.v_pool, scratch, sl2);
     dim3 mgrid((n_q + 7) / 8, bm.n_seqs);
-    attn_decode_merge_kernel<128, 8><<<mgrid, 1024, 0, s>>>(scratch, (bf16_t*)out, n_q, bm, wk);
+    attn_decode_merge_kernel<128, 8><<<mgrid, 256, 0, s>>>(scratch, (bf16_t*)out, n_q, bm, wk);
     return hipGetLastError();
 }
 
