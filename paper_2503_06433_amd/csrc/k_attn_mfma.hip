@@ -659,7 +659,10 @@ __global__ __launch_bounds__(D / 4 * HB) void attn_decode_merge_kernel(const flo
         float mx = M;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            m[u] = i + u < i1 ? m[u] : -INFINITY;
+            if (i + u >= i1) {                  // repeated: weight 0, and 0 times an infinite result must not count either
+                m[u] = -INFINITY;
+                v[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
             mx = fmaxf(mx, m[u]);
         }
         const float ref = mx == -INFINITY ? 0.f : mx;
