@@ -53,13 +53,14 @@ template <> struct DirectOp<float> {
     }
 };
 
-// silu(g) * u: on the hardware's exponential and reciprocal where the result is rounded to 16 bits, by the
-// library's exponential and an IEEE division in fp32
-template <typename T> __device__ __forceinline__ float direct_swiglu(float g, float u);
-template <> __device__ __forceinline__ float direct_swiglu<bf16_t>(float g, float u) {
+// silu(g) * u.  Gate and up rows in turns (the layers that the tile kernels take as well): on the hardware's exponential
+// and reciprocal, as there.  fp32, and 16-bit layers with the gate rows first: by the library's exponential and an IEEE
+// division like the kernel that serves those layers beyond 64 rows, so that the gate's left tail (reciprocals below
+// 2^-126, which the hardware flushes) is not lost at some row counts.
+__device__ __forceinline__ float direct_swiglu(float g, float u, bool divide) {
+    if (divide) return g / (1.0f + expf(-g)) * u;
     return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f)) * u;
 }
-template <> __device__ __forceinline__ float direct_swiglu<float>(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 
 template <typename T> __device__ __forceinline__ void store4(T* p, const float* o);
 template <> __device__ __forceinline__ void store4<float>(float* p, const float* o) {
@@ -79,8 +80,8 @@ template <> __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, const floa
 template <typename T, int MT, int NT, int W, int DEPTH, int EPI>
 __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict__ A, int lda, const T* __restrict__ Wt,
                                                              void* __restrict__ Cv, int ldc, const T* __restrict__ R,
-                                                             int M, int N, int K, int gate_blk, float norm_eps,
-                                                             int vec_ok) {
+                                                             int M, int N, int K, int gate_blk, int divide,
+                                                             float norm_eps, int vec_ok) {
     constexpr int CH = DirectOp<T>::CH;
     constexpr int EV = VecOf<T>::N;
     constexpr bool SWI = EPI == EPI_SWIGLU;
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
         if (SWI) {
             const f32x4_t u = sum(l + 32);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = direct_swiglu<T>(s[e] * rs, u[e] * rs);
+            for (int e = 0; e < 4; ++e) o[e] = direct_swiglu(s[e] * rs, u[e] * rs, sizeof(T) == 4 || divide);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = s[e] * rs;
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
 
 template <typename T, int MT, int NT, int W, int DEPTH>
 static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
-                                int epi, int gate_blk, float norm_eps, hipStream_t s) {
+                                int epi, int gate_blk, int divide, float norm_eps, hipStream_t s) {
     const int n_out = epi == EPI_SWIGLU ? N / 2 : N, per = (epi == EPI_SWIGLU ? 8 : 16) * NT;
     const dim3 grid((unsigned)((n_out + per - 1) / per), (unsigned)((M + 16 * MT - 1) / (16 * MT)));
     if (grid.y > 65535) return hipErrorInvalidValue;
@@ -307,7 +308,7 @@ static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C,
                 attr_set = true;                                                                                \
             }                                                                                                   \
         }                                                                                                       \
-        kfn<<<grid, 64 * W, LDS, s>>>(a, lda, w, C, ldc, r, M, N, K, gate_blk, norm_eps, vec_ok);               \
+        kfn<<<grid, 64 * W, LDS, s>>>(a, lda, w, C, ldc, r, M, N, K, gate_blk, divide, norm_eps, vec_ok);       \
     }
     switch (epi) {
         case EPI_STORE: SS_GO(EPI_STORE) break;
@@ -345,21 +346,22 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
 // wave) except for the widest blocks, whose single chunk is as large and which would spill.
 template <typename T, int MT>
 static hipError_t pick_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
-                              int epi, int gate_blk, float norm_eps, hipStream_t s) {
+                              int epi, int gate_blk, int divide, float norm_eps, hipStream_t s) {
     if constexpr (MT == 1)
-        if (M <= 8 && sizeof(T) == 2) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s);
+        if (M <= 8 && sizeof(T) == 2) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
     const long long tiles = (long long)((N + 15) / 16) * ((M + 16 * MT - 1) / (16 * MT));
-    if (tiles <= 256) return launch_direct<T, MT, 1, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s);
-    if (tiles <= 512) return launch_direct<T, MT, 2, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s);
-    return launch_direct<T, MT, 3, 8, 1>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s);
+    if (tiles <= 256) return launch_direct<T, MT, 1, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
+    if (tiles <= 512) return launch_direct<T, MT, 2, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
+    return launch_direct<T, MT, 3, 8, 1>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
 }
 
 hipError_t gemm_direct(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
                        int epi, float norm_eps, hipStream_t s) {
     if (!gemm_direct_takes(dt, A, Wt, M, N, K, lda, epi)) return hipErrorInvalidValue;
     const int gate_blk = epi == EPI_SWIGLU ? 32 : N / 2;
-    if (epi == EPI_SWIGLU_HALVES) epi = EPI_SWIGLU;
-#define SS_GO(TT, MT) return pick_direct<TT, MT>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, norm_eps, s)
+    const int divide = epi == EPI_SWIGLU_HALVES;
+    if (divide) epi = EPI_SWIGLU;
+#define SS_GO(TT, MT) return pick_direct<TT, MT>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s)
 #ifndef SS_HALF_F16          // fp32 is the same code in both builds of this file: only the first has it
     if (dt == F32) {
         if (M <= 16) SS_GO(float, 1);
