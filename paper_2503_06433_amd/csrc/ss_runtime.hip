@@ -821,13 +821,14 @@ int mark_meta_used(ss_ctx* c, MetaSlot* ms, hipStream_t stream) {
 // C = norm(x) W, T rows of `hidden`.  RMSNorm is not a pass of its own: the gains are folded into the rows of W at load
 // time, the product runs on the raw activations and its epilogue multiplies every token row by
 // rsqrt(mean(x^2) + eps).  Products of few rows work that factor out from the rows that pass through them; for the
-// others a read-only pass over x provides it (T floats).
+// others a read-only pass over x provides it (T floats).  The floats are there on either route: which of them a batch
+// takes depends on the alignment of x too, and a call that is captured after an eager one must not allocate.
 int norm_gemm(ss_ctx* c, const void* x, const void* wt, void* out, int ldc, int T, int N, int epi, hipStream_t st) {
     const int H = c->m.hidden;
+    int rc;
+    if ((rc = ensure_buf(c, c->ws_rs, (size_t)T * sizeof(float)))) return rc;
     const bool itself = c->m.rms_eps >= 0.f && SSK_CALL(c, gemm_norms_itself, x, H, wt, T, N, H, epi, c->force_generic);
     if (!itself) {
-        int rc;
-        if ((rc = ensure_buf(c, c->ws_rs, (size_t)T * sizeof(float)))) return rc;
         ProfScope ps(c, 4, st);
         K_TRY(c, SSK_CALL(c, row_scale, x, (float*)c->ws_rs.p, T, H, c->m.rms_eps, st));
     }
@@ -883,11 +884,11 @@ int run_mlp_phase(ss_ctx* c, Shard* s, int ll, int T, const void* x1, void* out,
     int rc;
     if ((rc = ensure_buf(c, c->ws_act, (size_t)T * F * c->es))) return rc;
     if (c->dt != SS_F32 && T <= 2048 && (rc = ensure_buf(c, c->ws_splitk, (size_t)128 << 20))) return rc;
+    if (!w.gu_interleaved && (rc = ensure_buf(c, c->ws_gu, (size_t)T * 2 * F * c->es))) return rc;   // on either route, as above
     const int halves = w.gu_interleaved ? ssk::EPI_SWIGLU : ssk::EPI_SWIGLU_HALVES;
     if (w.gu_interleaved || (m.rms_eps >= 0.f && SSK_CALL(c, gemm_norms_itself, x1, H, w.wgu_t, T, 2 * F, H, halves, c->force_generic))) {
         if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_act.p, F, T, 2 * F, halves, st))) return rc;
     } else {
-        if ((rc = ensure_buf(c, c->ws_gu, (size_t)T * 2 * F * c->es))) return rc;
         if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_gu.p, 2 * F, T, 2 * F, ssk::EPI_STORE, st))) return rc;
         ProfScope ps(c, 4, st);
         K_TRY(c, SSK_CALL(c, swiglu, c->ws_gu.p, c->ws_act.p, T, F, st));
