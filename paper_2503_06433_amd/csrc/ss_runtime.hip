@@ -103,11 +103,11 @@ struct MetaSlot {
     ssk::DecodeWork wk{};
 };
 
-// Metadata images of the device-side export / import, page-locked and on the device: two in turn.
+// Metadata images of the device-side export / import, page-locked and on the device: two in turn, made with the
+// context (a call that grew them would wait for the whole device to free the old ones).
 struct XferSlot {
     uint8_t* host = nullptr;
     uint8_t* dev = nullptr;
-    size_t cap = 0;
     hipEvent_t done = nullptr;                   // the kernels that read the slot
 };
 
@@ -306,6 +306,7 @@ struct ss_ctx {
     int meta_next = 0;
     XferSlot xfer[2];
     int xfer_next = 0;
+    size_t xfer_cap = 0;               // of each image
     void *d_embed = nullptr, *d_gf = nullptr, *d_wlm_t = nullptr;
     int32_t* d_ids = nullptr;
     size_t d_ids_cap = 0;
@@ -1624,6 +1625,12 @@ int ss_create(const ss_model_cfg* model, const ss_runtime_cfg* rt, ss_ctx** out)
             for (hipEvent_t& e : L.copy_ev) HIP_TRY(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
             for (int i = 0; i < 2; ++i) HIP_TRY(c, hipEventCreateWithFlags(&L.mv_ev[i], hipEventDisableTiming));
         }
+        c->xfer_cap = c->mv_meta_cap / 2;
+        for (XferSlot& x : c->xfer) {
+            HIP_TRY(c, hipHostMalloc((void**)&x.host, c->xfer_cap, hipHostMallocDefault));
+            HIP_TRY(c, hipMalloc((void**)&x.dev, c->xfer_cap));
+            HIP_TRY(c, hipEventCreateWithFlags(&x.done, hipEventDisableTiming));
+        }
         return SS_OK;
     };
     rc = boot();
@@ -2118,22 +2125,9 @@ static int xfer_dev(ss_ctx* c, const ss_shard_desc* d, const int64_t* seq_ids, c
         const size_t u1 = std::min(units.size(), u0 + 32768);
         XferSlot& x = c->xfer[c->xfer_next];
         c->xfer_next ^= 1;
-        if (x.done) HIP_TRY(c, hipEventSynchronize(x.done));
-        else HIP_TRY(c, hipEventCreateWithFlags(&x.done, hipEventDisableTiming));
-        size_t want = 5 * 64 + 20 * (u1 - u0);                       // 20 bytes a unit and the pages of its sequences
-        for (size_t i = units[u0].seq_idx; i <= (size_t)units[u1 - 1].seq_idx; ++i) want += 4 * seqs[i].pages.size();
-        want = std::min(want, c->mv_meta_cap / 2);
-        if (want > x.cap) {
-            if (x.host) { HIP_TRY(c, hipHostFree(x.host)); x.host = nullptr; }
-            if (x.dev) { HIP_TRY(c, hipFree(x.dev)); x.dev = nullptr; }
-            x.cap = 0;
-            const size_t bytes = std::min(want + want / 4 + 4096, c->mv_meta_cap / 2);
-            HIP_TRY(c, hipHostMalloc((void**)&x.host, bytes, hipHostMallocDefault));
-            HIP_TRY(c, hipMalloc((void**)&x.dev, bytes));
-            x.cap = bytes;
-        }
+        HIP_TRY(c, hipEventSynchronize(x.done));
         ssk::RepackUnits ru{};
-        const size_t mbytes = build_units(c, s, seqs, units, u0, u1, x.host, x.dev, x.cap, &ru);
+        const size_t mbytes = build_units(c, s, seqs, units, u0, u1, x.host, x.dev, c->xfer_cap, &ru);
         if (!mbytes) return fail(c, SS_ENOMEM, "repack metadata region too small");
         void* mapped = nullptr;
         HIP_TRY(c, hipHostGetDevicePointer(&mapped, x.host, 0));
