@@ -819,12 +819,26 @@ int mark_meta_used(ss_ctx* c, MetaSlot* ms, hipStream_t stream) {
             return fail((c), e_ == hipErrorInvalidValue ? SS_EINVAL : SS_EHIP, "%s: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
+// Workspace for partial sums of a layer call's products: 128 MB for 16-bit batches of up to 2048 rows, none beyond, even
+// where an earlier batch left it.  Which kernel a product takes, and with it the order of its sums, is then a function of
+// the batch alone.
+struct SplitWs {
+    float* p = nullptr;
+    size_t bytes = 0;
+};
+int splitk_ws(ss_ctx* c, int T, SplitWs* w) {
+    if (c->dt == SS_F32 || T > 2048) return SS_OK;
+    const int rc = ensure_buf(c, c->ws_splitk, (size_t)128 << 20);
+    if (rc == SS_OK) *w = {(float*)c->ws_splitk.p, c->ws_splitk.cap};
+    return rc;
+}
+
 // C = norm(x) W, T rows of `hidden`.  RMSNorm is not a pass of its own: the gains are folded into the rows of W at load
 // time, the product runs on the raw activations and its epilogue multiplies every token row by
 // rsqrt(mean(x^2) + eps).  Products of few rows work that factor out from the rows that pass through them; for the
 // others a read-only pass over x provides it (T floats).  The floats are there on either route: which of them a batch
 // takes depends on the alignment of x too, and a call that is captured after an eager one must not allocate.
-int norm_gemm(ss_ctx* c, const void* x, const void* wt, void* out, int ldc, int T, int N, int epi, hipStream_t st) {
+int norm_gemm(ss_ctx* c, const void* x, const void* wt, void* out, int ldc, int T, int N, int epi, const SplitWs& ws, hipStream_t st) {
     const int H = c->m.hidden;
     int rc;
     if ((rc = ensure_buf(c, c->ws_rs, (size_t)T * sizeof(float)))) return rc;
@@ -834,8 +848,8 @@ int norm_gemm(ss_ctx* c, const void* x, const void* wt, void* out, int ldc, int 
         K_TRY(c, SSK_CALL(c, row_scale, x, (float*)c->ws_rs.p, T, H, c->m.rms_eps, st));
     }
     ProfScope ps(c, 0, st);
-    K_TRY(c, SSK_CALL(c, gemm_nt, x, H, wt, out, ldc, nullptr, T, N, H, epi, c->force_generic, st, (float*)c->ws_splitk.p,
-                      c->ws_splitk.cap, c->gemm_rounds, itself ? nullptr : (const float*)c->ws_rs.p, itself ? c->m.rms_eps : -1.0f));
+    K_TRY(c, SSK_CALL(c, gemm_nt, x, H, wt, out, ldc, nullptr, T, N, H, epi, c->force_generic, st, ws.p,
+                      ws.bytes, c->gemm_rounds, itself ? nullptr : (const float*)c->ws_rs.p, itself ? c->m.rms_eps : -1.0f));
     return SS_OK;
 }
 
@@ -854,9 +868,10 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
         size_t fl = ssk::attn_decode_scratch_floats(ms->wk.n_items, s->nq_l, d);
         if ((rc = ensure_buf(c, c->ws_scratch, fl * sizeof(float)))) return rc;
     }
-    if (c->dt != SS_F32 && T <= 2048 && (rc = ensure_buf(c, c->ws_splitk, (size_t)128 << 20))) return rc;
+    SplitWs ws;
+    if ((rc = splitk_ws(c, T, &ws))) return rc;
     const ssk::KvLayer kv = kv_layer(c, s, ll);
-    if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, st))) return rc;
+    if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, ws, st))) return rc;
     {
         ProfScope ps(c, 4, st);
         K_TRY(c, SSK_CALL(c, rope_kvwrite, c->ws_qkv.p, s->nq_l, s->nkv_l, c->d_rope, ms->bm, kv, st));
@@ -873,7 +888,7 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     {
         ProfScope ps(c, 0, st);
         K_TRY(c, SSK_CALL(c, gemm_nt, c->ws_attn.p, s->nq_l * d, w.wo_t, out, H, residual ? x_in : nullptr, T, H,
-                              s->nq_l * d, residual ? ssk::EPI_RESIDUAL : ssk::EPI_STORE, c->force_generic, st, (float*)c->ws_splitk.p, c->ws_splitk.cap, c->gemm_rounds));
+                              s->nq_l * d, residual ? ssk::EPI_RESIDUAL : ssk::EPI_STORE, c->force_generic, st, ws.p, ws.bytes, c->gemm_rounds));
     }
     return mark_meta_used(c, ms, st);
 }
@@ -884,20 +899,21 @@ int run_mlp_phase(ss_ctx* c, Shard* s, int ll, int T, const void* x1, void* out,
     const int H = m.hidden, F = s->f_l;
     int rc;
     if ((rc = ensure_buf(c, c->ws_act, (size_t)T * F * c->es))) return rc;
-    if (c->dt != SS_F32 && T <= 2048 && (rc = ensure_buf(c, c->ws_splitk, (size_t)128 << 20))) return rc;
+    SplitWs ws;
+    if ((rc = splitk_ws(c, T, &ws))) return rc;
     if (!w.gu_interleaved && (rc = ensure_buf(c, c->ws_gu, (size_t)T * 2 * F * c->es))) return rc;   // on either route, as above
     const int halves = w.gu_interleaved ? ssk::EPI_SWIGLU : ssk::EPI_SWIGLU_HALVES;
     if (w.gu_interleaved || (m.rms_eps >= 0.f && SSK_CALL(c, gemm_norms_itself, x1, H, w.wgu_t, T, 2 * F, H, halves, c->force_generic))) {
-        if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_act.p, F, T, 2 * F, halves, st))) return rc;
+        if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_act.p, F, T, 2 * F, halves, ws, st))) return rc;
     } else {
-        if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_gu.p, 2 * F, T, 2 * F, ssk::EPI_STORE, st))) return rc;
+        if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_gu.p, 2 * F, T, 2 * F, ssk::EPI_STORE, ws, st))) return rc;
         ProfScope ps(c, 4, st);
         K_TRY(c, SSK_CALL(c, swiglu, c->ws_gu.p, c->ws_act.p, T, F, st));
     }
     {
         ProfScope ps(c, 0, st);
         K_TRY(c, SSK_CALL(c, gemm_nt, c->ws_act.p, F, w.wd_t, out, H, residual ? x1 : nullptr, T, H, F,
-                              residual ? ssk::EPI_RESIDUAL : ssk::EPI_STORE, c->force_generic, st, (float*)c->ws_splitk.p, c->ws_splitk.cap, c->gemm_rounds));
+                              residual ? ssk::EPI_RESIDUAL : ssk::EPI_STORE, c->force_generic, st, ws.p, ws.bytes, c->gemm_rounds));
     }
     return SS_OK;
 }

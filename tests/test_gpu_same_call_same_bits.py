@@ -1,5 +1,5 @@
-"""The result of a call is a function of its arguments, not of what the context has run before: replayed from a captured
-graph."""
+"""The result of a call is a function of its arguments: not of the batches the context has seen before, and not of
+whether the call is replayed from a captured graph."""
 import pytest
 import torch
 
@@ -9,11 +9,35 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import paper_2503_06433_amd as ss
-    from paper_2503_06433_amd.harness import make_context, pp_desc, torch_dtype, empty_like_acts
+    from paper_2503_06433_amd.harness import make_context, pp_desc, tp_desc, torch_dtype, empty_like_acts
 
 
 def _filled(gen, shape, dtype, std=1.0):
     return torch.empty(shape, device="cuda", dtype=torch_dtype(dtype)).normal_(0, std, generator=gen)
+
+
+def test_rows_beyond_the_workspace_do_not_depend_on_an_earlier_smaller_batch():
+    """2450 rows on a narrow shard (1280 x 8192): with a workspace for partial sums the contraction could be cut, and
+    the workspace is there only once a batch of up to 2048 rows has run."""
+    cfg = wl.ModelCfg(hidden=8192, n_q_heads=64, n_kv_heads=8, head_dim=128, ffn=512, n_layers=1, dtype=wl.BF16)
+    T = 2450
+    gen = torch.Generator(device="cuda").manual_seed(941)
+    H, q, kv = cfg.hidden, 64 * 128, 8 * 128
+    w = {n: _filled(gen, s, cfg.dtype, 0.02) for n, s in (("wq", (H, q)), ("wk", (H, kv)), ("wv", (H, kv)), ("wo", (q, H)),
+                                                          ("wg", (H, 512)), ("wu", (H, 512)), ("wd", (512, H)))}
+    w["g1"] = w["g2"] = torch.ones(H, device="cuda", dtype=torch.bfloat16)
+    x = _filled(gen, (T, H), cfg.dtype)
+    d, res = tp_desc(cfg, 8, 0), []
+    for before in (0, 100):
+        ctx = make_context(cfg, pages=T + 8, max_seq_len=32)
+        ctx.load_layer(d, 0, w, ss.SS_DEVICE)
+        out = empty_like_acts(T, H, cfg.dtype)
+        for n in ([before] if before else []) + [T]:
+            ctx.layer_prefill(d, 0, ss.SS_ATTN, list(range(n)), [1] * n, [0] * n, x[:n], out[:n])
+        torch.cuda.synchronize()
+        res.append(out)
+        ctx.destroy()
+    assert torch.equal(res[0], res[1])
 
 
 @pytest.mark.parametrize("dtype,hidden,phase", [(wl.BF16, 256, 1), (wl.BF16, 200, 2), (wl.F32, 256, 1), (wl.F32, 256, 2)])
