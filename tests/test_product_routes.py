@@ -1,0 +1,48 @@
+"""The launcher of the products on the host (no GPU: every call here is refused or fails before a launch)."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+import pytest
+
+import paper_2503_06433_amd as ss
+
+BF16, EPI_STORE, EPI_STORE_F32, INVALID_VALUE = 1, 0, 3, 1
+
+
+def _library():
+    if not os.path.exists(ss.library_path()):
+        from paper_2503_06433_amd.build import build
+        build()
+    return ss.library_path()
+
+
+def _symbol(prefix):
+    out = subprocess.run(["nm", "-D", "--defined-only", _library()], capture_output=True, text=True, check=True).stdout
+    return next(l.split()[2] for l in out.splitlines() if l.split()[2].startswith(prefix))
+
+
+CALL = """
+import ctypes as C, sys
+f = getattr(C.CDLL(sys.argv[1]), sys.argv[2])
+I, V = C.c_int, C.c_void_p
+f.argtypes = [I, V, I, V, V, I, V, I, I, I, I, C.c_bool, V, V, C.c_size_t, I, V, C.c_float]
+p = 4096                                                    # never followed: there is no device in this process
+print(f(1, p, 1024, p, p, 1024, None, int(sys.argv[3]), 1024, 1024, int(sys.argv[4]), False, None, None, 0, 0, p if sys.argv[5] == "1" else None, -1.0))
+"""
+
+
+@pytest.mark.parametrize("rows", [65, 128, 333, 2000])
+def test_fp32_output_refuses_a_row_factor(rows):
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")
+
+    def call(epi, factor):
+        r = subprocess.run([sys.executable, "-c", CALL, _library(), _symbol("_ZN3ssk7gemm_nt"), str(rows), str(epi), factor],
+                           capture_output=True, text=True, env=env, timeout=60)
+        assert r.returncode == 0, r.stderr[-500:]
+        return int(r.stdout.split()[-1])
+
+    assert call(EPI_STORE_F32, "1") == INVALID_VALUE
+    for epi, factor in ((EPI_STORE_F32, "0"), (EPI_STORE, "1")):      # taken: these get as far as the missing device
+        assert call(epi, factor) not in (0, INVALID_VALUE)
