@@ -85,6 +85,9 @@ static hipError_t launch_generic(const void* A, int lda, const void* Wt, void* C
 hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N,
                           int K, int epi, hipStream_t s, float* ws, size_t ws_bytes, int max_rounds, const float* rs);
 bool gemm_mfma_supported(int M, int N, int K, int lda, int ldc, int epi);
+bool gemm_mfma_stream_supported(const void* C, const void* R, int ldc, int M, int N, int K, int lda, int epi);
+bool gemm_tile_supported(const void* A, const void* Wt, const void* C, const void* R, int ldc, int M, int N, int K, int lda, int epi);
+GemmPlan gemm_mfma_plan(bool stream_ok, bool tile_ok, int M, int N, int K, int epi, size_t ws_bytes, int n_cus);
 bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int K, int lda, int epi);
 hipError_t gemm_direct(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
                        int epi, float norm_eps, hipStream_t s);
@@ -109,3 +112,19 @@ hipError_t gemm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int 
 }
 
 }  // namespace SS_NS
+
+#ifndef SS_HALF_F16
+// The choice of gemm_nt for dense operands on 16-byte boundaries, without a GPU (for tests of the rules).
+extern "C" int ssk_gemm_plan(int dt, int M, int N, int K, int epi, long long ws_bytes, int n_cus, int* pick, int* split) {
+    const void* p = (const void*)(uintptr_t)4096;
+    const int ldc = epi == ssk::EPI_SWIGLU || epi == ssk::EPI_SWIGLU_HALVES ? N / 2 : N;
+    ssk::GemmPlan plan{ssk::GEMM_GENERIC, 0, 1};
+    if (ssk::gemm_direct_takes(dt, p, p, M, N, K, K, epi)) plan.kernel = ssk::GEMM_DIRECT;
+    else if (dt == ssk::BF16 && ssk::gemm_mfma_supported(M, N, K, K, ldc, epi))
+        plan = ssk::gemm_mfma_plan(ssk::gemm_mfma_stream_supported(p, p, ldc, M, N, K, K, epi),
+                                   ssk::gemm_tile_supported(p, p, p, p, ldc, M, N, K, K, epi), M, N, K, epi, (size_t)ws_bytes, n_cus);
+    *pick = plan.pick;
+    *split = plan.split;
+    return plan.kernel;
+}
+#endif

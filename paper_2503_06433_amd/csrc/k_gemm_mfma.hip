@@ -720,6 +720,21 @@ bool gemm_mfma_stream_supported(const void* C, const void* R, int ldc, int M, in
     return true;
 }
 
+// Compute units of the device, asked for once.
+static hipError_t device_cus(int* out) {
+    static int n_cus = 0;
+    if (!n_cus) {
+        int dev = 0, n = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        n_cus = n < 8 ? 8 : n;
+    }
+    *out = n_cus;
+    return hipSuccess;
+}
+
 // Blocks of the persistent kernel own their CU (all registers, all LDS) until they are done, so a kernel
 // of another stream can only start at a launch boundary.  `max_rounds` > 0 cuts the walk into launches
 // of at most that many tiles per block, for callers that have latency-bound work on other streams.
@@ -738,15 +753,9 @@ static hipError_t launch_stream(const bf16_t* A, int lda, const bf16_t* Wt, bf16
     const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
     const long long n_tiles = (long long)tiles_m * tiles_n;
     if (n_tiles > (1ll << 30)) return hipErrorInvalidValue;
-    static int n_cus = 0;
-    if (!n_cus) {
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        e = hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        if (n_cus < 8) n_cus = 8;
-    }
+    int n_cus = 0;
+    hipError_t e_cus = device_cus(&n_cus);
+    if (e_cus != hipSuccess) return e_cus;
     const int cus_per_xcd = n_cus / 8;
     // Tile rows per group of the walk: the 32 CUs of an XCD cover GM x 32/GM tiles at a time, so an XCD re-fetches
     // its token slices (tiles_n * GM / 32) times and the weight slices once per group from beyond its L2; with the
@@ -899,56 +908,73 @@ float gemm_tile_estimate(int M, int N, int K, int n_cus, int* pick);
 hipError_t gemm_tile(int pick, const bf16_t* A, int lda, const bf16_t* Wt, void* C, int ldc, const bf16_t* R, int M, int N, int K,
                      int epi, const float* rs, hipStream_t s);
 
+// Ranges of K for the register-staged kernel: until every CU has a block, but only while the fp32 partials (8*S*M*N bytes
+// written and read back) stay below twice the weight bytes (2*N*K) they help to stream: S <= K / (2 M).  (With the bound at
+// the weight bytes themselves, S <= K / (4 M), the QKV projection of the k = 8 shard of the 70B layer with 1024
+// tokens stopped at two ranges: 57 us, with four 47 us; the same for the QKV and down projections of the 13B
+// k = 4 shard with 512 tokens, 44 -> 41 and 46 -> 43 us; the 7B shapes with 256 tokens choose as before.)
+static int staged_split(int M, int N, int K, size_t ws_bytes) {
+    const long long tiles = (long long)((M + 127) / 128) * ((N + 127) / 128);
+    int split = 1;
+    while (split < 8 && tiles * split < 256 && (K / 64) % (split * 2) == 0 && (long long)(split * 2) * 2 * M <= K &&
+           (size_t)(split * 2) * M * N * sizeof(float) <= ws_bytes)
+        split *= 2;
+    return split;
+}
+
+// Which kernel, which tile, how many ranges of K.  A function of sizes only (the workspace is one of them).
+GemmPlan gemm_mfma_plan(bool stream_ok, bool tile_ok, int M, int N, int K, int epi, size_t ws_bytes, int n_cus) {
+    stream_ok = stream_ok && epi != EPI_STORE_F32;
+    // Prefill-sized outputs (at least one 256 x 256 tile per CU): the persistent direct-to-LDS kernel.
+    const long long big = (long long)((M + 255) / 256) * ((N + 255) / 256);
+    static const long long stream_min = getenv("SS_GEMM_STREAM_MIN_TILES") ? atoll(getenv("SS_GEMM_STREAM_MIN_TILES")) : 0;
+    if (stream_ok && big >= (stream_min > 0 ? stream_min : n_cus)) return {GEMM_STREAM, 0, 1};
+    // Rows that are not whole 16-byte pieces (an odd vocabulary), buffers that are not aligned: register-staged.
+    const int s_staged = staged_split(M, N, K, ws_bytes);
+    if (!tile_ok) return {GEMM_STAGED, 0, s_staged};
+    // Fewer tiles than compute units: the tile kernel, or a kernel with K cut into ranges so that tiles x ranges fill the
+    // chip (fp32 partial sums, summed by a second launch).  By estimated time.
+    static const int stream_split = getenv("SS_GEMM_STREAM_SPLIT") ? atoi(getenv("SS_GEMM_STREAM_SPLIT")) : 1;
+    static const int stream_split_min_m = getenv("SS_GEMM_STREAM_SPLIT_MIN_M") ? atoi(getenv("SS_GEMM_STREAM_SPLIT_MIN_M")) : 256;
+    GemmPlan plan{GEMM_TILE, -1, 1};
+    float us = gemm_tile_estimate(M, N, K, n_cus, &plan.pick);
+    const int slices = K / 64;
+    // The persistent kernel takes 1.5 us for a slice, the partial sums are read at 4.2 TB/s; split, it has to be a quarter
+    // faster by estimate (at less it lost: 512 x 6912 x 5120 in four ranges 60 us, tiles 54).  The
+    // persistent kernel is left with outputs of nearly a tile per compute unit and, split, with long contractions of few tiles
+    // (512 x 8192 x 28672 in four ranges: 202 + 28 us for the sums, tiles 289; 1500 x 10240 x 8192 whole: 230, tiles 297).
+    if (stream_split && stream_ok && M >= stream_split_min_m) {
+        for (int t = 1; t <= 8 && big * t <= n_cus && slices % t == 0 && slices / t >= 16; t *= 2) {
+            const size_t bytes = (size_t)t * M * N * sizeof(float);
+            if (t > 1 && bytes > ws_bytes) break;
+            float e = 7.f + 1.5f * (slices / t);
+            if (t > 1) e = 1.25f * (e + 5.f + bytes / 4.2e6f);
+            if (e < us) { us = e; plan = {GEMM_STREAM, 0, t}; }
+        }
+    }
+    return plan;
+}
+
 hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N,
                           int K, int epi, hipStream_t s, float* ws, size_t ws_bytes, int max_rounds, const float* rs) {
     const bf16_t* a = (const bf16_t*)A;
     const bf16_t* w = (const bf16_t*)Wt;
     bf16_t* c = (bf16_t*)C;
     const bf16_t* r = (const bf16_t*)R;
-    // Prefill-sized outputs (at least one 256 x 256 tile per CU): the persistent direct-to-LDS kernel.
-    const long long big = (long long)((M + 255) / 256) * ((N + 255) / 256);
-    static const long long stream_min = getenv("SS_GEMM_STREAM_MIN_TILES") ? atoll(getenv("SS_GEMM_STREAM_MIN_TILES")) : 256;
-    if (big >= stream_min && epi != EPI_STORE_F32 && gemm_mfma_stream_supported(C, R, ldc, M, N, K, lda, epi))
-        return launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs);
-    // Fewer tiles than compute units: the tile kernel, or the persistent kernel, with K cut into ranges so that tiles x
-    // ranges fill the chip where that is needed (fp32 partial sums, summed by the reduce kernel of the small-tile path).
-    // By estimated time: the persistent kernel takes 1.5 us for a slice, the partial sums are read at 4.2 TB/s; split, it
-    // has to be a quarter faster by estimate (at less it lost: 512 x 6912 x 5120 in four ranges 60 us, tiles 54).  The
-    // persistent kernel is left with outputs of 200 tiles and more and, split, with long contractions of few tiles
-    // (512 x 8192 x 28672 in four ranges: 202 + 28 us for the sums, tiles 289; 1500 x 10240 x 8192 whole: 230, tiles 297).
-    static const int stream_split = getenv("SS_GEMM_STREAM_SPLIT") ? atoi(getenv("SS_GEMM_STREAM_SPLIT")) : 1;
-    static const int stream_split_min_m = getenv("SS_GEMM_STREAM_SPLIT_MIN_M") ? atoi(getenv("SS_GEMM_STREAM_SPLIT_MIN_M")) : 256;
-    if (gemm_tile_supported(A, Wt, C, R, ldc, M, N, K, lda, epi)) {
-        constexpr int n_cus = 256;
-        int pick = -1, ks = 0;
-        float us = gemm_tile_estimate(M, N, K, n_cus, &pick);
-        if (stream_split && M >= stream_split_min_m && epi != EPI_STORE_F32 && gemm_mfma_stream_supported(C, R, ldc, M, N, K, lda, epi)) {
-            for (int t = 1; t <= 8 && big * t <= n_cus && (K / 64) % t == 0 && K / 64 / t >= 16; t *= 2) {
-                const size_t bytes = (size_t)t * M * N * sizeof(float);
-                if (t > 1 && (!ws || ((uintptr_t)ws & 15) != 0 || bytes > ws_bytes)) break;
-                float e = 7.f + 1.5f * (K / 64 / t);
-                if (t > 1) e = 1.25f * (e + 5.f + bytes / 4.2e6f);
-                if (e < us) { us = e; ks = t; }
-            }
-        }
-        if (ks == 0) return gemm_tile(pick, a, lda, w, C, ldc, r, M, N, K, epi, rs, s);
-        if (ks == 1) return launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs);
-        hipError_t e = launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs, ks, ws);
-        if (e != hipSuccess) return e;
-        return reduce_partials(ws, ks, c, ldc, r, M, N, epi, rs, s);
-    }
-    // What is left: rows that are not whole 16-byte pieces (an odd vocabulary), buffers that are not aligned.
-    const long long mid = (long long)((M + 127) / 128) * ((N + 127) / 128);
-    // split K until every CU has a block, but only while the fp32 partials (8*S*M*N bytes written and
-    // read back) stay below twice the weight bytes (2*N*K) they help to stream: S <= K / (2 M).  (With the bound at
-    // the weight bytes themselves, S <= K / (4 M), the QKV projection of the k = 8 shard of the 70B layer with 1024
-    // tokens stopped at two ranges: 57 us, with four 47 us; the same for the QKV and down projections of the 13B
-    // k = 4 shard with 512 tokens, 44 -> 41 and 46 -> 43 us; the 7B shapes with 256 tokens choose as before.)
-    int split = 1;
-    while (split < 8 && mid * split < 256 && (K / 64) % (split * 2) == 0 && (long long)(split * 2) * 2 * M <= K &&
-           (size_t)(split * 2) * M * N * sizeof(float) <= ws_bytes && ws)
-        split *= 2;
-    return launch_cfg<128, 128, 2, 2>(a, lda, w, c, ldc, r, M, N, K, epi, s, split, ws, rs);
+    if (rs && epi == EPI_STORE_F32) return hipErrorInvalidValue;      // the fp32 epilogues apply no row factor
+    int n_cus = 0;
+    hipError_t e = device_cus(&n_cus);
+    if (e != hipSuccess) return e;
+    const bool tile_ok = gemm_tile_supported(A, Wt, C, R, ldc, M, N, K, lda, epi);
+    const bool ws_ok = ws && ((uintptr_t)ws & 15) == 0;
+    const GemmPlan p = gemm_mfma_plan(gemm_mfma_stream_supported(C, R, ldc, M, N, K, lda, epi), tile_ok, M, N, K, epi,
+                                      ws_ok ? ws_bytes : 0, n_cus);
+    if (p.kernel == GEMM_TILE) return gemm_tile(p.pick, a, lda, w, C, ldc, r, M, N, K, epi, rs, s);
+    if (p.kernel == GEMM_STAGED) return launch_cfg<128, 128, 2, 2>(a, lda, w, c, ldc, r, M, N, K, epi, s, p.split, ws, rs);
+    if (p.split == 1) return launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs);
+    e = launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs, p.split, ws);
+    if (e != hipSuccess) return e;
+    return reduce_partials(ws, p.split, c, ldc, r, M, N, epi, rs, s);
 }
 
 }  // namespace SS_NS

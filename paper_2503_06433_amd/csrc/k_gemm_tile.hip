@@ -272,7 +272,6 @@ template <class G>
 static hipError_t launch_tile(const bf16_t* A, int lda, const bf16_t* Wt, void* C, int ldc, const bf16_t* R, int M, int N, int K,
                               int epi, const float* rs, hipStream_t s) {
     if (epi == EPI_RESIDUAL && !R) return hipErrorInvalidValue;
-    if (epi == EPI_STORE_F32 && rs) return hipErrorInvalidValue;      // the fp32 epilogue applies no row factor
     const int tiles_m = (M + G::BM - 1) / G::BM, tiles_n = (N + G::BN - 1) / G::BN;
     const long long n_tiles = (long long)tiles_m * tiles_n;
     if (n_tiles > (1ll << 27) || K % (64 * G::SL) != 0) return hipErrorInvalidValue;

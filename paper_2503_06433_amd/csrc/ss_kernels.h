@@ -25,6 +25,12 @@ enum Epilogue {
     EPI_SWIGLU_HALVES = 4,   // as EPI_SWIGLU with the N / 2 gate rows first and the up rows behind them
 };
 
+// How a product is done: kernel, tile of the tile kernel, ranges of K whose sums meet in memory.
+enum GemmKernel { GEMM_GENERIC = 0, GEMM_DIRECT = 1, GEMM_STREAM = 2, GEMM_TILE = 3, GEMM_STAGED = 4 };
+struct GemmPlan {
+    int kernel, pick, split;
+};
+
 // Paged cache geometry of one shard and one layer.
 //   K page: [n_heads][page_size][d]   (token-major, d contiguous)
 //   V page: [n_heads][d][page_size]   (transposed inside the page: token contiguous, in the

@@ -1,4 +1,5 @@
-"""The launcher of the products on the host (no GPU: every call here is refused or fails before a launch)."""
+"""The launcher of the products on the host: which kernel a product takes, and what is refused (no GPU: every call here is
+answered, refused or fails before a launch)."""
 import ctypes as C
 import os
 import subprocess
@@ -8,7 +9,11 @@ import pytest
 
 import paper_2503_06433_amd as ss
 
-BF16, EPI_STORE, EPI_STORE_F32, INVALID_VALUE = 1, 0, 3, 1
+F32, BF16 = 0, 1
+EPI_STORE, EPI_RESIDUAL, EPI_SWIGLU, EPI_STORE_F32, EPI_SWIGLU_HALVES = 0, 1, 2, 3, 4
+INVALID_VALUE = 1
+GENERIC, DIRECT, STREAM, TILE, STAGED = range(5)
+WS = 128 << 20                                                # the layer calls' workspace
 
 
 def _library():
@@ -16,6 +21,14 @@ def _library():
         from paper_2503_06433_amd.build import build
         build()
     return ss.library_path()
+
+
+def plan(rows, n, k, epi=EPI_STORE, dt=BF16, ws=WS, cus=256):
+    """(kernel, place of the tile in the list, ranges of K)"""
+    f = C.CDLL(_library()).ssk_gemm_plan
+    f.argtypes = [C.c_int] * 5 + [C.c_longlong, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+    pick, split = C.c_int(), C.c_int()
+    return f(dt, rows, n, k, epi, ws, cus, pick, split), pick.value, split.value
 
 
 def _symbol(prefix):
@@ -46,3 +59,7 @@ def test_fp32_output_refuses_a_row_factor(rows):
     assert call(EPI_STORE_F32, "1") == INVALID_VALUE
     for epi, factor in ((EPI_STORE_F32, "0"), (EPI_STORE, "1")):      # taken: these get as far as the missing device
         assert call(epi, factor) not in (0, INVALID_VALUE)
+
+
+def test_fewer_compute_units_mean_fewer_tiles_for_the_persistent_kernel():
+    assert plan(1024, 4096, 4096, cus=256)[0] == TILE and plan(1024, 4096, 4096, cus=64)[0] == STREAM
