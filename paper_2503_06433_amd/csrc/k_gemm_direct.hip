@@ -325,9 +325,15 @@ static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C,
 
 // Which products come here.  16-bit types: up to 64 token rows.  Measured against the 128 x 128 tile kernel with its
 // statistics, split-K and reduce launches, on the projections of the 7B layer and of the 13B / 70B shards: 1 row
-// 1.5-2.9 times, 32 rows 1.3-2.5 times, 64 rows 1.1-2.3 times as fast (QKV 12288 x 4096: 31.7 -> 18.9 us at 1 row =
+// 1.5-2.9 times, 32 rows 1.3-2.5 times, 64 rows up to 2.3 times as fast (QKV 12288 x 4096: 31.7 -> 18.9 us at 1 row =
 // 5.3 TB/s of weights, 33.1 -> 21.5 at 32, 37.1 -> 24.9 at 64; down 4096 x 11008: 41.5 -> 21.8, 43.7 -> 28.8,
-// 45.1 -> 37.2).  fp32: every aligned shape.  Against the 64 x 64 FMA kernel, 256-wide layer of 4 rows: QKV 28.1 ->
+// 45.1 -> 37.2).  Not where the tile kernel or that one is faster:
+//  - more than 16 rows of an output wider than 12288, that is of more blocks of three tiles than compute units: the second
+//    round of blocks reads all token rows again (here / tile kernel with its statistics, 64 rows: 13824 x 5120 54 / 39 us,
+//    27648 x 5120 84 / 59, 57344 x 8192 203 / 168; 17 rows: 37.8 / 31.2, 59.9 / 53.5, 174 / 169; up to 16 rows 22016 x 4096
+//    35.1 / 36.1).
+// Only where that kernel takes the product (rows of whole 16-byte pieces, K in whole slices).
+// fp32: every aligned shape.  Against the 64 x 64 FMA kernel, 256-wide layer of 4 rows: QKV 28.1 ->
 // 3.8 us, down (K = 688) 60.4 -> 4.0; 4096 x 4096 at 64 rows 469 -> 42 us, at 2048 rows 1803 -> 911 us.
 constexpr int DIRECT_MAX_M16 = 64;
 
@@ -336,7 +342,12 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
     if (M <= 0 || N <= 0 || K <= 0 || K % ev != 0 || lda % ev != 0) return false;
     if (((uintptr_t)A & 15) != 0 || ((uintptr_t)Wt & 15) != 0) return false;
     if ((epi == EPI_SWIGLU && N % 64 != 0) || (epi == EPI_SWIGLU_HALVES && N % 2 != 0)) return false;
-    return dt == F32 ? M <= 65535 * 16 : M <= DIRECT_MAX_M16;
+    if (dt == F32) return M <= 65535 * 16;
+    if (M > DIRECT_MAX_M16) return false;
+    if (K % 64 == 0 && N % 8 == 0 && epi != EPI_SWIGLU_HALVES) {
+        if (M > 16 && N > 48 * 256) return false;
+    }
+    return true;
 }
 
 // NT (tiles of weight rows per block): more tiles mean fewer times that the token rows are read (every block reads

@@ -61,5 +61,17 @@ def test_fp32_output_refuses_a_row_factor(rows):
         assert call(epi, factor) not in (0, INVALID_VALUE)
 
 
+# Both sides of the lines between the kernels, at products whose times on either side are in the comments of the rules.
+@pytest.mark.parametrize("rows,n,k,epi,kernel,split", [
+    # outputs of more three-tile blocks than compute units: few rows only up to 16
+    (16, 13824, 5120, EPI_SWIGLU, DIRECT, 1), (17, 13824, 5120, EPI_SWIGLU, TILE, 1), (64, 27648, 5120, EPI_SWIGLU, TILE, 1),
+    (64, 15360, 5120, EPI_STORE, TILE, 1), (64, 12288, 4096, EPI_STORE, DIRECT, 1), (64, 32000, 4096, EPI_STORE_F32, TILE, 1),
+    (64, 32001, 4096, EPI_STORE_F32, DIRECT, 1), (64, 13824, 200, EPI_SWIGLU_HALVES, DIRECT, 1),
+])
+def test_products_take_the_kernel_that_was_faster(rows, n, k, epi, kernel, split):
+    got = plan(rows, n, k, epi)
+    assert (got[0], got[2]) == (kernel, split)
+
+
 def test_fewer_compute_units_mean_fewer_tiles_for_the_persistent_kernel():
     assert plan(1024, 4096, 4096, cus=256)[0] == TILE and plan(1024, 4096, 4096, cus=64)[0] == STREAM
