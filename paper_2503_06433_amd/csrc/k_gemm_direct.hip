@@ -331,7 +331,11 @@ static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C,
 //  - more than 16 rows of an output wider than 12288, that is of more blocks of three tiles than compute units: the second
 //    round of blocks reads all token rows again (here / tile kernel with its statistics, 64 rows: 13824 x 5120 54 / 39 us,
 //    27648 x 5120 84 / 59, 57344 x 8192 203 / 168; 17 rows: 37.8 / 31.2, 59.9 / 53.5, 174 / 169; up to 16 rows 22016 x 4096
-//    35.1 / 36.1).
+//    35.1 / 36.1);
+//  - more than 48 rows of a contraction of 12800 and more, more than 32 where the blocks do not fill the chip either: the
+//    chunks of a wave, one behind the other, outweigh the second launch of split K (here / split K: 8192 x 28672
+//    at 48 rows 107 / 112, at 64 122 / 113; 5120 x 13824 in 160 blocks at 32 rows 40.6 / 42.3, at 48 47.6 / 43, at 64 55 / 45;
+//    4096 x 11008 at 64 rows 38 / 45).
 // Only where that kernel takes the product (rows of whole 16-byte pieces, K in whole slices).
 // fp32: every aligned shape.  Against the 64 x 64 FMA kernel, 256-wide layer of 4 rows: QKV 28.1 ->
 // 3.8 us, down (K = 688) 60.4 -> 4.0; 4096 x 4096 at 64 rows 469 -> 42 us, at 2048 rows 1803 -> 911 us.
@@ -346,6 +350,8 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
     if (M > DIRECT_MAX_M16) return false;
     if (K % 64 == 0 && N % 8 == 0 && epi != EPI_SWIGLU_HALVES) {
         if (M > 16 && N > 48 * 256) return false;
+        const int blocks = N <= 4096 ? N / 16 : N <= 8192 ? N / 32 : N / 48;
+        if (M > (blocks >= 224 ? 48 : 32) && K >= 12800 && epi != EPI_STORE_F32) return false;
     }
     return true;
 }

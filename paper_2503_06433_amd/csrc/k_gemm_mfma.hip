@@ -939,18 +939,30 @@ GemmPlan gemm_mfma_plan(bool stream_ok, bool tile_ok, int M, int N, int K, int e
     GemmPlan plan{GEMM_TILE, -1, 1};
     float us = gemm_tile_estimate(M, N, K, n_cus, &plan.pick);
     const int slices = K / 64;
-    // The persistent kernel takes 1.5 us for a slice, the partial sums are read at 4.2 TB/s; split, it has to be a quarter
-    // faster by estimate (at less it lost: 512 x 6912 x 5120 in four ranges 60 us, tiles 54).  The
-    // persistent kernel is left with outputs of nearly a tile per compute unit and, split, with long contractions of few tiles
-    // (512 x 8192 x 28672 in four ranges: 202 + 28 us for the sums, tiles 289; 1500 x 10240 x 8192 whole: 230, tiles 297).
+    // The persistent kernel takes 1.5 us for a slice, the partial sums are read at 4.2 TB/s.  Split, it has to be a quarter
+    // faster by estimate (at less it lost: 512 x 6912 x 5120 in four ranges 60 us, tiles 54): the tile estimate is 15 to 25 %
+    // high, the persistent kernel's is not.  For contractions of 160 slices and more, where the tile estimate is
+    // right, a tenth: 512 x 5120 x 13824 in four ranges 97 us, tiles 109; 384 x 8192 x 14336 118, tiles 133; 640 x 4096 x 11008
+    // 81, tiles 87; 1024 x 8192 x 28672 in two 398, tiles 425.  Whole: 1500 x 10240 x 8192 230 us, tiles 297.
     if (stream_split && stream_ok && M >= stream_split_min_m) {
         for (int t = 1; t <= 8 && big * t <= n_cus && slices % t == 0 && slices / t >= 16; t *= 2) {
             const size_t bytes = (size_t)t * M * N * sizeof(float);
             if (t > 1 && bytes > ws_bytes) break;
             float e = 7.f + 1.5f * (slices / t);
-            if (t > 1) e = 1.25f * (e + 5.f + bytes / 4.2e6f);
+            if (t > 1) e = (slices >= 160 ? 1.1f : 1.25f) * (e + 5.f + bytes / 4.2e6f);
             if (e < us) { us = e; plan = {GEMM_STREAM, 0, t}; }
         }
+    }
+    // The register-staged kernel of up to 128 rows and 200 slices and more: tiles leave compute units idle or each of them
+    // with all of K.  Its time: 0.81 us for a slice with one block per CU, 1.26 with two, 0.4 us per megabyte of partial
+    // sums (7 % off over 900 products).  5120 x 13824: 65 rows 45 us, tiles 52; 96 rows 48, tiles 56; 128 rows 55,
+    // tiles 66.  8192 x 28672: 126 and 145 at 128 rows.  At 172 slices and fewer, and beyond 128 rows, tiles are faster or within 4 %
+    // (4096 x 11008 at 80 / 192 / 224 / 256 rows: 45 / 47.4 / 48.5 / 49.4 us in four ranges, tiles 30 / 49.5 / 45 / 51.3).
+    if (s_staged > 1 && M <= 128 && slices >= 200 && epi != EPI_STORE_F32) {
+        const long long blocks = (long long)((N + 127) / 128) * s_staged;
+        const float per = blocks <= n_cus ? 0.81f : 1.26f * (float)((blocks + 2 * n_cus - 1) / (2 * n_cus));
+        const float e = 8.f + per * (slices / s_staged) + 0.4e-6f * (float)s_staged * M * N * sizeof(float);
+        if (e < us) { us = e; plan = {GEMM_STAGED, 0, s_staged}; }
     }
     return plan;
 }

@@ -308,7 +308,11 @@ bool gemm_tile_supported(const void* A, const void* Wt, const void* C, const voi
 // line, which it mostly has not) and what its products take (0.024 ns per output element, 15 % more where one group of
 // waves does all k-steps); 7 us go to launch, first loads and epilogue, 8 more to every further round of tiles.  The four
 // numbers were fitted to 31 shapes of 100 to 2000 rows, every tile timed on each: the choice is within 1 % of the
-// fastest tile on average, 5 % at worst.
+// fastest tile on average, 5 % at worst.  Later, over 44 shapes of 65 to 1280 rows: 15 to 25 % above the measured time
+// nearly everywhere, which leaves the order of the tiles as it is, but right for the 96 x 32 tile with one row of tiles,
+// whose weight lines no second block of the XCD shares: its token lines count 2.4 ns there (64 x 64 tiles instead, 96 rows:
+// 5120 x 13824 65 -> 56 us, 8192 x 14336 72 -> 63, 5120 x 8192 37 -> 33, 6912 x 5120 28.5 -> 26.7; 5120 x 1280 at 80 rows
+// loses 0.3 us of 7).
 float gemm_tile_estimate(int M, int N, int K, int n_cus, int* pick) {
     float best = 0.f;
     *pick = -1;
@@ -317,7 +321,7 @@ float gemm_tile_estimate(int M, int N, int K, int n_cus, int* pick) {
     if (K % (64 * SL) == 0) {                                                                                               \
         const long long tiles = (long long)((M + BM - 1) / BM) * ((N + BN - 1) / BN);                                       \
         const float rounds = (float)((tiles + n_cus - 1) / n_cus);                                                          \
-        const float lines = 1.8f * BM + 3.3f * BN, mul = (KG == 1 ? 0.0276f : 0.024f) * BM * BN;                            \
+        const float lines = (BN == 32 && BM == 96 && M <= BM ? 2.4f : 1.8f) * BM + 3.3f * BN, mul = (KG == 1 ? 0.0276f : 0.024f) * BM * BN;                            \
         const float us = 7.f + 8.f * (rounds - 1.f) + rounds * (K / 64) * (lines > mul ? lines : mul) * 1e-3f;              \
         if (*pick < 0 || us < best) { best = us; *pick = at; }                                                              \
     }                                                                                                                       \

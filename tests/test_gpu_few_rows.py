@@ -21,7 +21,8 @@ if torch.cuda.is_available():
     (wl.BF16, 192, 3104),      # two; the down projection's contraction ends inside a chunk
     (wl.F16, 128, 5152),       # three
     (wl.F16, 128, 8224),       # three up to 16 rows, and a long contraction for one wave's share
-    (wl.BF16, 128, 12800),     # gate / up so wide that more than 16 rows take the tile kernel
+    (wl.BF16, 128, 12800),     # gate / up so wide that more than 16 rows take the tile kernel, a contraction so long that more
+                               # than 32 take split K in front of it
     (wl.BF16, 200, 72),        # hidden no multiple of 64: gate rows first, up rows behind; chunks cut on both sides
     (wl.F32, 256, 688),
     (wl.F32, 36, 4100),        # fp32 with three tiles per block and a contraction of little more than one chunk

@@ -19,6 +19,7 @@ if torch.cuda.is_available():
     (wl.BF16, 64, 64),         # one slice, one tile
     (wl.BF16, 192, 1088),      # three and seventeen slices (no stages of two slices), gate / up tiles that end inside
     (wl.F16, 512, 2304),
+    (wl.F16, 192, 12800),      # up to 128 rows the down projection is cut along its 200 slices
     (wl.BF16, 1344, 8192),     # tiles of 128 weight rows and more for the gate / up product
 ])
 def test_mlp_of_middling_row_counts_matches_oracle(dtype, hidden, ffn):

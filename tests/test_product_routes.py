@@ -67,10 +67,24 @@ def test_fp32_output_refuses_a_row_factor(rows):
     (16, 13824, 5120, EPI_SWIGLU, DIRECT, 1), (17, 13824, 5120, EPI_SWIGLU, TILE, 1), (64, 27648, 5120, EPI_SWIGLU, TILE, 1),
     (64, 15360, 5120, EPI_STORE, TILE, 1), (64, 12288, 4096, EPI_STORE, DIRECT, 1), (64, 32000, 4096, EPI_STORE_F32, TILE, 1),
     (64, 32001, 4096, EPI_STORE_F32, DIRECT, 1), (64, 13824, 200, EPI_SWIGLU_HALVES, DIRECT, 1),
+    # long contractions of few rows
+    (32, 5120, 13824, EPI_RESIDUAL, DIRECT, 1), (33, 5120, 13824, EPI_RESIDUAL, STAGED, 8), (64, 5120, 13824, EPI_RESIDUAL, STAGED, 8),
+    (48, 8192, 28672, EPI_RESIDUAL, DIRECT, 1), (49, 8192, 28672, EPI_RESIDUAL, STAGED, 4), (64, 4096, 11008, EPI_RESIDUAL, DIRECT, 1),
+    # ... and of up to 128
+    (96, 5120, 13824, EPI_RESIDUAL, STAGED, 8), (128, 8192, 28672, EPI_RESIDUAL, STAGED, 4), (129, 8192, 28672, EPI_RESIDUAL, TILE, 1),
+    (80, 4096, 11008, EPI_RESIDUAL, TILE, 1), (128, 8192, 28672, EPI_STORE_F32, TILE, 1),
+    # the persistent kernel with K in ranges
+    (512, 5120, 13824, EPI_RESIDUAL, STREAM, 4), (640, 4096, 11008, EPI_RESIDUAL, STREAM, 4), (384, 8192, 14336, EPI_RESIDUAL, STREAM, 4),
+    (1024, 8192, 28672, EPI_RESIDUAL, STREAM, 2), (512, 6912, 5120, EPI_SWIGLU, TILE, 1),
 ])
 def test_products_take_the_kernel_that_was_faster(rows, n, k, epi, kernel, split):
     got = plan(rows, n, k, epi)
     assert (got[0], got[2]) == (kernel, split)
+
+
+@pytest.mark.parametrize("n,k", [(5120, 5120), (5120, 8192), (5120, 6912), (6912, 5120)])
+def test_one_row_of_tiles_takes_64_x_64(n, k):
+    assert plan(96, n, k, EPI_RESIDUAL)[:2] == plan(97, n, k, EPI_RESIDUAL)[:2] == (TILE, 1)
 
 
 def test_fewer_compute_units_mean_fewer_tiles_for_the_persistent_kernel():
