@@ -336,7 +336,10 @@ static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C,
 //    chunks of a wave, one behind the other, outweigh the second launch of split K (here / split K: 8192 x 28672
 //    at 48 rows 107 / 112, at 64 122 / 113; 5120 x 13824 in 160 blocks at 32 rows 40.6 / 42.3, at 48 47.6 / 43, at 64 55 / 45;
 //    4096 x 11008 at 64 rows 38 / 45).
-// Only where that kernel takes the product (rows of whole 16-byte pieces, K in whole slices).
+// Both only where those kernels take the product (rows of whole 16-byte pieces, K in whole slices).  An output of other rows
+// (an odd vocabulary) has the register-staged kernel beside it, which is faster than three rounds of blocks and more:
+// here / there, 64 rows 20001 x 4096 45 / 59 us, 32001 x 1024 25 / 20, 32001 x 4096 67 / 66, 50257 x 4096 112 / 94; 48 rows 32001 x 1024
+// 22 / 20, 32001 x 4096 61 / 65; 24 rows 32001 x 1024 18 / 19, 50257 x 768 24 / 20; 16 rows 50257 x 768 18 / 20.
 // fp32: every aligned shape.  Against the 64 x 64 FMA kernel, 256-wide layer of 4 rows: QKV 28.1 ->
 // 3.8 us, down (K = 688) 60.4 -> 4.0; 4096 x 4096 at 64 rows 469 -> 42 us, at 2048 rows 1803 -> 911 us.
 constexpr int DIRECT_MAX_M16 = 64;
@@ -352,6 +355,8 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
         if (M > 16 && N > 48 * 256) return false;
         const int blocks = N <= 4096 ? N / 16 : N <= 8192 ? N / 32 : N / 48;
         if (M > (blocks >= 224 ? 48 : 32) && K >= 12800 && epi != EPI_STORE_F32) return false;
+    } else if (K % 64 == 0 && epi != EPI_SWIGLU_HALVES) {
+        if (M > (N > 48 * 1024 ? 16 : N > 48 * 512 ? (K <= 2048 ? 32 : 48) : DIRECT_MAX_M16)) return false;
     }
     return true;
 }
@@ -361,11 +366,14 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
 // one per block, up to 512 two, beyond that three (gate/up 22016 x 4096 at 16 rows, blocks of 1 / 2 / 3 / 6 tiles:
 // 36.0 / 44 / 34.6 / 36.0 us; QKV 12288 x 4096 at 64 rows: 53 / 37 / 24.9 us).  DEPTH 2 (16 KB and more on their way per
 // wave) except for the widest blocks, whose single chunk is as large and which would spill.
+// Up to 8 rows (16-bit) one tile and four chunks on their way per wave, whatever the width, where every wave has as many
+// (K of 2048 and more): 22016 x 4096 at 8 rows 33.0 us, 34.8 by the rule above; 4096 x 2048 6.3 and 6.9.  Below that the blocks
+// are too short: 50257 x 768 27 us, 18 by the rule; 32001 x 1024 21 and 14; 8192 x 1024 7.1 and 5.8.
 template <typename T, int MT>
 static hipError_t pick_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
                               int epi, int gate_blk, int divide, float norm_eps, hipStream_t s) {
     if constexpr (MT == 1)
-        if (M <= 8 && sizeof(T) == 2) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
+        if (M <= 8 && sizeof(T) == 2 && K >= 2048) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
     const long long tiles = (long long)((N + 15) / 16) * ((M + 16 * MT - 1) / (16 * MT));
     if (tiles <= 256) return launch_direct<T, MT, 1, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
     if (tiles <= 512) return launch_direct<T, MT, 2, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);

@@ -964,6 +964,14 @@ GemmPlan gemm_mfma_plan(bool stream_ok, bool tile_ok, int M, int N, int K, int e
         const float e = 8.f + per * (slices / s_staged) + 0.4e-6f * (float)s_staged * M * N * sizeof(float);
         if (e < us) { us = e; plan = {GEMM_STAGED, 0, s_staged}; }
     }
+    // ... and of the LM head over a vocabulary of one to two 128-wide tiles per CU: two of its blocks share a CU, where the tile
+    // kernel takes two rounds.  50176 x 768 at 64 / 128 rows 22.8 / 26.5 us, tiles 24.7 / 30.5; x 1600 39.3 / 45, tiles
+    // 40.4 / 48; 32000 x 768 (one round of tiles) 16.6 / 18, tiles 14.2 / 17.1.
+    const long long wide = (N + 127) / 128;
+    if (epi == EPI_STORE_F32 && M <= 128 && wide > n_cus && wide <= 2 * n_cus) {
+        const float e = 10.6f + 1.26f * slices;
+        if (e < us) { us = e; plan = {GEMM_STAGED, 0, 1}; }
+    }
     return plan;
 }
 

@@ -66,7 +66,13 @@ def test_fp32_output_refuses_a_row_factor(rows):
     # outputs of more three-tile blocks than compute units: few rows only up to 16
     (16, 13824, 5120, EPI_SWIGLU, DIRECT, 1), (17, 13824, 5120, EPI_SWIGLU, TILE, 1), (64, 27648, 5120, EPI_SWIGLU, TILE, 1),
     (64, 15360, 5120, EPI_STORE, TILE, 1), (64, 12288, 4096, EPI_STORE, DIRECT, 1), (64, 32000, 4096, EPI_STORE_F32, TILE, 1),
-    (64, 32001, 4096, EPI_STORE_F32, DIRECT, 1), (64, 13824, 200, EPI_SWIGLU_HALVES, DIRECT, 1),
+    # a vocabulary of more 128-wide tiles than compute units
+    (64, 50256, 768, EPI_STORE_F32, STAGED, 1), (128, 50256, 1600, EPI_STORE_F32, STAGED, 1), (129, 50256, 768, EPI_STORE_F32, TILE, 1),
+    (64, 50256, 4096, EPI_STORE_F32, TILE, 1), (128, 32000, 768, EPI_STORE_F32, TILE, 1),
+    # an odd vocabulary
+    (64, 20001, 4096, EPI_STORE_F32, DIRECT, 1), (48, 32001, 4096, EPI_STORE_F32, DIRECT, 1), (49, 32001, 4096, EPI_STORE_F32, STAGED, 2),
+    (32, 32001, 1024, EPI_STORE_F32, DIRECT, 1), (33, 32001, 1024, EPI_STORE_F32, STAGED, 2), (17, 50257, 768, EPI_STORE_F32, STAGED, 1),
+    (64, 13824, 200, EPI_SWIGLU_HALVES, DIRECT, 1),
     # long contractions of few rows
     (32, 5120, 13824, EPI_RESIDUAL, DIRECT, 1), (33, 5120, 13824, EPI_RESIDUAL, STAGED, 8), (64, 5120, 13824, EPI_RESIDUAL, STAGED, 8),
     (48, 8192, 28672, EPI_RESIDUAL, DIRECT, 1), (49, 8192, 28672, EPI_RESIDUAL, STAGED, 4), (64, 4096, 11008, EPI_RESIDUAL, DIRECT, 1),
