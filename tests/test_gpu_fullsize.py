@@ -358,12 +358,14 @@ def test_many_tokens_on_a_narrow_layer_short_contractions_on_the_large_output_ke
     ctx.destroy()
 
 
-@pytest.mark.parametrize("hidden,n_q,n_kv,ffn,T", [(8192, 16, 8, 2048, 777), (4096, 8, 8, 8192, 777), (8192, 16, 8, 2048, 1000)])
+@pytest.mark.parametrize("hidden,n_q,n_kv,ffn,T", [(8192, 16, 8, 2048, 777), (4096, 8, 8, 8192, 777), (8192, 16, 8, 2048, 1000),
+                                                    (8192, 16, 8, 2048, 270)])
 def test_ragged_token_count_on_the_projections_cut_along_the_contraction(hidden, n_q, n_kv, ffn, T):
     """Between a decode batch and a prefill batch (some hundreds of tokens, a count that is no multiple of any tile)
     wide layers send their projections to the large-output GEMM with the contraction cut into ranges and fp32
-    partial sums: with hidden 8192 the QKV product (plain store) and the gate/up product (SwiGLU), with
-    hidden 4096 and an inner width of 8192 the down projection (residual).  Single-token sequences, so the
+    partial sums: with hidden 8192 the QKV product (plain store) and the gate/up product (SwiGLU), in four ranges at 777
+    tokens and in eight at 270, with hidden 4096 and an inner width of 8192 the down projection (residual) in four.  At
+    1000 tokens the same layer runs on tiles of the tile kernel.  Single-token sequences, so the
     attention is the identity on V and the oracle can afford every row."""
     cfg = wl.ModelCfg(n_layers=1, dtype=wl.BF16, hidden=hidden, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, ffn=ffn)
     vals, raws = wl.make_layer_weights(cfg, 7401)

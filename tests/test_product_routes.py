@@ -80,6 +80,8 @@ def test_fp32_output_refuses_a_row_factor(rows):
     (96, 5120, 13824, EPI_RESIDUAL, STAGED, 8), (128, 8192, 28672, EPI_RESIDUAL, STAGED, 4), (129, 8192, 28672, EPI_RESIDUAL, TILE, 1),
     (80, 4096, 11008, EPI_RESIDUAL, TILE, 1), (128, 8192, 28672, EPI_STORE_F32, TILE, 1),
     # the persistent kernel with K in ranges
+    (777, 4096, 8192, EPI_STORE, STREAM, 4), (777, 4096, 8192, EPI_SWIGLU, STREAM, 4), (777, 4096, 8192, EPI_RESIDUAL, STREAM, 4),
+    (270, 4096, 8192, EPI_STORE, STREAM, 8), (270, 4096, 8192, EPI_SWIGLU, STREAM, 8), (1000, 4096, 8192, EPI_STORE, TILE, 1),
     (512, 5120, 13824, EPI_RESIDUAL, STREAM, 4), (640, 4096, 11008, EPI_RESIDUAL, STREAM, 4), (384, 8192, 14336, EPI_RESIDUAL, STREAM, 4),
     (1024, 8192, 28672, EPI_RESIDUAL, STREAM, 2), (512, 6912, 5120, EPI_SWIGLU, TILE, 1),
 ])
@@ -95,3 +97,15 @@ def test_one_row_of_tiles_takes_64_x_64(n, k):
 
 def test_fewer_compute_units_mean_fewer_tiles_for_the_persistent_kernel():
     assert plan(1024, 4096, 4096, cus=256)[0] == TILE and plan(1024, 4096, 4096, cus=64)[0] == STREAM
+
+
+def test_the_parity_tests_reach_every_tile():
+    """The cases of test_gpu_mid_rows.py take the tiles they are listed for: eighteen, with every epilogue of a layer."""
+    import test_gpu_mid_rows as m
+    assert sorted(m.GATE_UP_TILES) == sorted(m.DOWN_TILES) == list(range(18))
+    for tile in range(18):
+        T, hidden, ffn = m.GATE_UP_TILES[tile]
+        assert plan(T, 2 * ffn, hidden, EPI_SWIGLU, ws=WS if T <= 2048 else 0) == (TILE, tile, 1)
+        T, hidden, ffn = m.DOWN_TILES[tile]
+        for epi in (EPI_RESIDUAL, EPI_STORE):
+            assert plan(T, hidden, ffn, epi, ws=WS if T <= 2048 else 0) == (TILE, tile, 1)
