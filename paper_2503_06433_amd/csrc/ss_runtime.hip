@@ -103,8 +103,8 @@ struct MetaSlot {
     ssk::DecodeWork wk{};
 };
 
-// Metadata images of the device-side export / import, page-locked and on the device: two in turn, made with the
-// context (a call that grew them would wait for the whole device to free the old ones).
+// Metadata images of the device-side export / import: the halves of the swap-out lane's metadata region, in turn.  The calls
+// and that lane keep out of each other's way: a call starts when the lanes are idle, a swap-out job waits for `done`.
 struct XferSlot {
     uint8_t* host = nullptr;
     uint8_t* dev = nullptr;
@@ -1062,6 +1062,9 @@ int worker_job(ss_ctx* c, Lane& L, Job& job) {
     if (job.after) {
         HIP_TRY(c, hipStreamWaitEvent(L.side, job.after, 0));
     }
+    // queued exports / imports still read the images in this lane's metadata region
+    if (&L == &c->lane[0])
+        for (XferSlot& x : c->xfer) HIP_TRY(c, hipEventSynchronize(x.done));
     const std::vector<Unit> units = make_units(c, s, job.seqs);
     const size_t run_elems_bytes = c->es * c->m.head_dim;   // per token per head
     // chunks of consecutive units fitting one slot
@@ -1292,6 +1295,7 @@ void worker_main(ss_ctx* c, int li) {
         local_err.clear();
         const auto t_job0 = std::chrono::steady_clock::now();
         const int rc = worker_job(c, L, job);
+        if (rc) (void)hipStreamSynchronize(L.side);          // a failed job may have left copies of its metadata on their way
         if (c->trace_mover) {
             const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_job0).count();
             size_t bytes = 0;
@@ -1642,10 +1646,10 @@ int ss_create(const ss_model_cfg* model, const ss_runtime_cfg* rt, ss_ctx** out)
             for (int i = 0; i < 2; ++i) HIP_TRY(c, hipEventCreateWithFlags(&L.mv_ev[i], hipEventDisableTiming));
         }
         c->xfer_cap = c->mv_meta_cap / 2;
-        for (XferSlot& x : c->xfer) {
-            HIP_TRY(c, hipHostMalloc((void**)&x.host, c->xfer_cap, hipHostMallocDefault));
-            HIP_TRY(c, hipMalloc((void**)&x.dev, c->xfer_cap));
-            HIP_TRY(c, hipEventCreateWithFlags(&x.done, hipEventDisableTiming));
+        for (int i = 0; i < 2; ++i) {
+            c->xfer[i].host = c->lane[0].mv_meta_host + i * c->xfer_cap;
+            c->xfer[i].dev = c->lane[0].mv_meta_dev + i * c->xfer_cap;
+            HIP_TRY(c, hipEventCreateWithFlags(&c->xfer[i].done, hipEventDisableTiming));
         }
         return SS_OK;
     };
@@ -1688,11 +1692,8 @@ int ss_destroy(ss_ctx* c) {
         if (ms.dev) (void)hipFree(ms.dev);
         if (ms.done) (void)hipEventDestroy(ms.done);
     }
-    for (XferSlot& x : c->xfer) {
-        if (x.host) (void)hipHostFree(x.host);
-        if (x.dev) (void)hipFree(x.dev);
+    for (XferSlot& x : c->xfer)
         if (x.done) (void)hipEventDestroy(x.done);
-    }
     for (Lane& L : c->lane) {
         if (L.dev_staging) (void)hipFree(L.dev_staging);
         if (L.mv_meta_dev) (void)hipFree(L.mv_meta_dev);

@@ -32,3 +32,38 @@ def test_queued_imports_and_exports_return_every_byte(dtype, nkv, d, layers):
     for j in range(len(sets)):
         assert torch.equal(src[j], dst[j]), "set %d" % j
     ctx.destroy()
+
+
+def test_swap_out_beside_queued_imports_and_exports():
+    """A swap-out job is asked for while an import and an export are still queued behind a busy stream; the lane that carries
+    it out and those calls share one region for their page lists."""
+    import paper_2503_06433_amd as ss
+    cfg = wl.ModelCfg(hidden=128, n_q_heads=2, n_kv_heads=2, head_dim=128, ffn=64, n_layers=2, dtype=wl.BF16)
+    lens = {1: 700, 2: 333, 3: 1000}
+    tier = sum(lens.values()) * 2 * 2 * 128 * 2 * 2 + (1 << 20)
+    ctx = make_context(cfg, pages=sum(-(-n // 16) for n in lens.values()) + 4, tier_bytes=tier, pinned_bytes=8 << 20, max_seq_len=1024)
+    desc = pp_desc(cfg)
+    gen = torch.Generator(device="cuda").manual_seed(922)
+    src = {i: torch.randint(-30000, 30000, (n * 2 * 2 * 128 * 2,), device="cuda", generator=gen).to(torch.bfloat16) for i, n in lens.items()}
+    dst = {i: torch.full_like(v, 3.0) for i, v in src.items()}
+    ctx.kv_import_dev(desc, [1], [lens[1]], src[1])
+    torch.cuda.synchronize()
+    busy, other = torch.cuda.Stream(), torch.cuda.Stream()
+    a = torch.randn((8192, 8192), device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        for _ in range(20):
+            a = torch.mm(a, a).clamp_(-1, 1)                  # tens of milliseconds in front of the queued kernels
+        ctx.kv_import_dev(desc, [2, 3], [lens[2], lens[3]], torch.cat([src[2], src[3]]), busy.cuda_stream)
+        ctx.kv_export_dev(desc, [2], dst[2], busy.cuda_stream)
+    ctx.kv_swap(desc, ss.SS_OUT, [1], other.cuda_stream)      # pages that nothing on the busy stream touches
+    ctx.sync()
+    ctx.kv_export_dev(desc, [1], dst[1])
+    ctx.kv_export_dev(desc, [3], dst[3], busy.cuda_stream)
+    torch.cuda.synchronize()
+    for i in lens:
+        assert torch.equal(src[i], dst[i]), "sequence %d" % i
+    for l in range(2):
+        want = src[1].view(2, 2, 2, lens[1], 128)[l].view(torch.int16).cpu().numpy()
+        assert (ctx.host_tier_read(1, l, lens[1]).view("int16").reshape(want.shape) == want).all()
+    ctx.destroy()
