@@ -301,7 +301,7 @@ struct ss_ctx {
     std::string err;
     std::map<DescKey, Shard*> shards;
     float* d_rope = nullptr;
-    DevBuf ws_h, ws_qkv, ws_attn, ws_gu, ws_act, ws_x1, ws_scratch, ws_splitk, ws_rs, ws_chain[2];
+    DevBuf ws_h, ws_qkv, ws_attn, ws_act, ws_x1, ws_scratch, ws_splitk, ws_chain[2];
     MetaSlot meta[4];
     int meta_next = 0;
     XferSlot xfer[2];
@@ -819,6 +819,10 @@ int mark_meta_used(ss_ctx* c, MetaSlot* ms, hipStream_t stream) {
             return fail((c), e_ == hipErrorInvalidValue ? SS_EINVAL : SS_EHIP, "%s: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
+// A workspace holds what one phase needs on any of its routes (which of them a batch takes depends on the alignment of its rows
+// too): a call that is captured after an eager one does not allocate.
+size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
+
 // Workspace for partial sums of a layer call's products: 128 MB for 16-bit batches of up to 2048 rows, none beyond, even
 // where an earlier batch left it.  Which kernel a product takes, and with it the order of its sums, is then a function of
 // the batch alone.
@@ -836,20 +840,18 @@ int splitk_ws(ss_ctx* c, int T, SplitWs* w) {
 // C = norm(x) W, T rows of `hidden`.  RMSNorm is not a pass of its own: the gains are folded into the rows of W at load
 // time, the product runs on the raw activations and its epilogue multiplies every token row by
 // rsqrt(mean(x^2) + eps).  Products of few rows work that factor out from the rows that pass through them; for the
-// others a read-only pass over x provides it (T floats).  The floats are there on either route: which of them a batch
-// takes depends on the alignment of x too, and a call that is captured after an eager one must not allocate.
-int norm_gemm(ss_ctx* c, const void* x, const void* wt, void* out, int ldc, int T, int N, int epi, const SplitWs& ws, hipStream_t st) {
+// others a read-only pass over x provides it: `rs`, T floats.
+int norm_gemm(ss_ctx* c, const void* x, const void* wt, void* out, int ldc, int T, int N, int epi, float* rs, const SplitWs& ws,
+              hipStream_t st) {
     const int H = c->m.hidden;
-    int rc;
-    if ((rc = ensure_buf(c, c->ws_rs, (size_t)T * sizeof(float)))) return rc;
     const bool itself = c->m.rms_eps >= 0.f && SSK_CALL(c, gemm_norms_itself, x, H, wt, T, N, H, epi, c->force_generic);
     if (!itself) {
         ProfScope ps(c, 4, st);
-        K_TRY(c, SSK_CALL(c, row_scale, x, (float*)c->ws_rs.p, T, H, c->m.rms_eps, st));
+        K_TRY(c, SSK_CALL(c, row_scale, x, rs, T, H, c->m.rms_eps, st));
     }
     ProfScope ps(c, 0, st);
     K_TRY(c, SSK_CALL(c, gemm_nt, x, H, wt, out, ldc, nullptr, T, N, H, epi, c->force_generic, st, ws.p,
-                      ws.bytes, c->gemm_rounds, itself ? nullptr : (const float*)c->ws_rs.p, itself ? c->m.rms_eps : -1.0f));
+                      ws.bytes, c->gemm_rounds, itself ? nullptr : rs, itself ? c->m.rms_eps : -1.0f));
     return SS_OK;
 }
 
@@ -862,7 +864,9 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     if (rc) return rc;
     const int T = ms->bm.T, H = m.hidden, d = m.head_dim;
     const int nqkv = (s->nq_l + 2 * s->nkv_l) * d;
-    if ((rc = ensure_buf(c, c->ws_qkv, (size_t)T * nqkv * c->es))) return rc;
+    const size_t qkv_bytes = align256((size_t)T * nqkv * c->es);
+    if ((rc = ensure_buf(c, c->ws_qkv, qkv_bytes + (size_t)T * sizeof(float)))) return rc;      // and the RMSNorm factors
+    float* rs = (float*)((uint8_t*)c->ws_qkv.p + qkv_bytes);
     if ((rc = ensure_buf(c, c->ws_attn, (size_t)T * s->nq_l * d * c->es))) return rc;
     if (decode) {
         size_t fl = ssk::attn_decode_scratch_floats(ms->wk.n_items, s->nq_l, d);
@@ -871,7 +875,7 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     SplitWs ws;
     if ((rc = splitk_ws(c, T, &ws))) return rc;
     const ssk::KvLayer kv = kv_layer(c, s, ll);
-    if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, ws, st))) return rc;
+    if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, rs, ws, st))) return rc;
     {
         ProfScope ps(c, 4, st);
         K_TRY(c, SSK_CALL(c, rope_kvwrite, c->ws_qkv.p, s->nq_l, s->nkv_l, c->d_rope, ms->bm, kv, st));
@@ -898,17 +902,20 @@ int run_mlp_phase(ss_ctx* c, Shard* s, int ll, int T, const void* x1, void* out,
     const LayerW& w = s->w[ll];
     const int H = m.hidden, F = s->f_l;
     int rc;
-    if ((rc = ensure_buf(c, c->ws_act, (size_t)T * F * c->es))) return rc;
+    // the activation, gate and up in front of it where a product does not fuse SwiGLU, and the RMSNorm factors
+    const size_t act_bytes = align256((size_t)T * F * c->es), gu_bytes = w.gu_interleaved ? 0 : align256((size_t)T * 2 * F * c->es);
+    if ((rc = ensure_buf(c, c->ws_act, act_bytes + gu_bytes + (size_t)T * sizeof(float)))) return rc;
+    void* gu = (uint8_t*)c->ws_act.p + act_bytes;
+    float* rs = (float*)((uint8_t*)gu + gu_bytes);
     SplitWs ws;
     if ((rc = splitk_ws(c, T, &ws))) return rc;
-    if (!w.gu_interleaved && (rc = ensure_buf(c, c->ws_gu, (size_t)T * 2 * F * c->es))) return rc;   // on either route, as above
     const int halves = w.gu_interleaved ? ssk::EPI_SWIGLU : ssk::EPI_SWIGLU_HALVES;
     if (w.gu_interleaved || (m.rms_eps >= 0.f && SSK_CALL(c, gemm_norms_itself, x1, H, w.wgu_t, T, 2 * F, H, halves, c->force_generic))) {
-        if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_act.p, F, T, 2 * F, halves, ws, st))) return rc;
+        if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_act.p, F, T, 2 * F, halves, rs, ws, st))) return rc;
     } else {
-        if ((rc = norm_gemm(c, x1, w.wgu_t, c->ws_gu.p, 2 * F, T, 2 * F, ssk::EPI_STORE, ws, st))) return rc;
+        if ((rc = norm_gemm(c, x1, w.wgu_t, gu, 2 * F, T, 2 * F, ssk::EPI_STORE, rs, ws, st))) return rc;
         ProfScope ps(c, 4, st);
-        K_TRY(c, SSK_CALL(c, swiglu, c->ws_gu.p, c->ws_act.p, T, F, st));
+        K_TRY(c, SSK_CALL(c, swiglu, gu, c->ws_act.p, T, F, st));
     }
     {
         ProfScope ps(c, 0, st);
@@ -1684,7 +1691,7 @@ int ss_destroy(ss_ctx* c) {
         if (s->w_ready) (void)hipEventDestroy(s->w_ready);
         delete s;
     }
-    for (DevBuf* b : {&c->ws_h, &c->ws_qkv, &c->ws_attn, &c->ws_gu, &c->ws_act, &c->ws_x1, &c->ws_scratch, &c->ws_splitk, &c->ws_rs,
+    for (DevBuf* b : {&c->ws_h, &c->ws_qkv, &c->ws_attn, &c->ws_act, &c->ws_x1, &c->ws_scratch, &c->ws_splitk,
                       &c->ws_chain[0], &c->ws_chain[1]})
         if (b->p) (void)hipFree(b->p);
     for (auto& ms : c->meta) {
