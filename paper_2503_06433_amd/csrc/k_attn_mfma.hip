@@ -493,10 +493,10 @@ hipError_t attn_prefill(int dt, const void* qkv, void* out, int n_q, int n_kv, c
 // zero), so K and V are read from HBM once per group.  Each step covers two pages, A and B.  The rows of the two score
 // products are tokens 0-7 of A and of B, and tokens 8-15 of A and of B, so that lane group g4 = l/16 holds tokens
 // 4*(g4%2) + v and 8 + 4*(g4%2) + v (v = 0..3) of page A (g4 < 2) or B: the eight tokens that are one 16-byte piece of
-// a row of V^T, and the eight k-slots of the group in the second product.  With four tokens of each page per group, two
-// 8-byte loads in place of one, and the merge below in two dependent passes: 1024 sequences on one kv head, a step with
-// its products 530 us, 523 like this; eight sequences of the 7B shape, two layers and the LM head 253 -> 249 us.  Bound by the
-// page reads: 5.5 TB/s with 32 kv heads, 5 with one.  A third wave per SIMD (146 registers) changes neither.
+// a row of V^T, and the eight k-slots of the group in the second product.  One 16-byte load in place of two of 8 bytes (four
+// tokens of each page per group): no more than 0.2 % either way (six steps of 1024 sequences on one kv head 3175 -> 3169 us, of
+// 256 sequences of the 7B shape 8075 -> 8093).  Bound by the page reads: 5.5 TB/s with 32 kv heads, 5 with one.  A third wave
+// per SIMD (146 registers) changes neither.
 // Partial (max, sum, O) of every item go to scratch and are merged per sequence.
 // scratch layout: float [n_items][n_q][D + 4]  (O[D], running max, running sum)
 // ======================================================================
@@ -636,7 +636,9 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
 }
 
 // Merge of the per-item partials: D / 4 threads per (q head, sequence), HB heads per block.  Bound by latency: a
-// sequence has one to a few items, so the maxima, sums and outputs of four of them are requested together.
+// sequence has one to a few items, so the maxima, sums and outputs of four of them are requested together.  Against two
+// dependent passes over them, one item at a time: eight sequences of the 7B shape, two layers and the LM head 251.8 -> 248.4 us
+// a token, 1024 sequences on one kv head 536 -> 528 us a step.
 template <int D, int HB>
 __global__ __launch_bounds__(D / 4 * HB) void attn_decode_merge_kernel(const float* __restrict__ scratch,
                                                                        bf16_t* __restrict__ out, int n_q, BatchMeta bm,

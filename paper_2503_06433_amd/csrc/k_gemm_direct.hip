@@ -364,8 +364,8 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
 // NT (tiles of weight rows per block): more tiles mean fewer times that the token rows are read (every block reads
 // them all), fewer tiles more blocks.  The line is where the blocks still fill the 256 compute units: up to 256 tiles
 // one per block, up to 512 two, beyond that three (gate/up 22016 x 4096 at 16 rows, blocks of 1 / 2 / 3 / 6 tiles:
-// 36.0 / 44 / 34.6 / 36.0 us; QKV 12288 x 4096 at 64 rows: 53 / 37 / 24.9 us).  DEPTH 2 (16 KB and more on their way per
-// wave) except for the widest blocks, whose single chunk is as large and which would spill.
+// 36.0 / 44 / 34.6 / 36.0 us; QKV 12288 x 4096 at 64 rows: 53 / 37 / 24.9 us).  A chunk is 2 (NT + MT) KB, so with DEPTH 2 a wave
+// has 8 to 24 KB on their way (eight waves a block); the widest blocks keep one chunk, 8 to 14 KB, as two would spill.
 // Up to 8 rows (16-bit) one tile and four chunks on their way per wave, whatever the width, where every wave has as many
 // (K of 2048 and more): 22016 x 4096 at 8 rows 33.0 us, 34.8 by the rule above; 4096 x 2048 6.3 and 6.9.  Below that the blocks
 // are too short: 50257 x 768 27 us, 18 by the rule; 32001 x 1024 21 and 14; 8192 x 1024 7.1 and 5.8.
