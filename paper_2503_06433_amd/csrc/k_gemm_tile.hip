@@ -307,9 +307,9 @@ bool gemm_tile_supported(const void* A, const void* Wt, const void* C, const voi
 // spends on a K slice the larger of what its lines take (1.8 ns per token line, which the L2 mostly has, 3.3 ns per weight
 // line, which it mostly has not) and what its products take (0.024 ns per output element, 15 % more where one group of
 // waves does all k-steps); 7 us go to launch, first loads and epilogue, 8 more to every further round of tiles.  The four
-// numbers were fitted to 31 shapes of 100 to 2000 rows, every tile timed on each: the choice is within 1 % of the
-// fastest tile on average, 5 % at worst.  Later, over 44 shapes of 65 to 1280 rows: 15 to 25 % above the measured time
-// nearly everywhere, which leaves the order of the tiles as it is, but right for the 96 x 32 tile with one row of tiles,
+// numbers were fitted to 31 shapes of 100 to 2000 rows, every tile timed on each.  Over 44 shapes of 65 to 1280 rows the choice,
+// split kernels included, is within 1.2 % of the fastest on average, 7 % in 95 of 100, 16 % at worst; the estimate is 15 to 25 %
+// above the measured time nearly everywhere, which leaves the order as it is, but right for the 96 x 32 tile with one row of tiles,
 // whose weight lines no second block of the XCD shares: its token lines count 2.4 ns there (64 x 64 tiles instead, 96 rows:
 // 5120 x 13824 65 -> 56 us, 8192 x 14336 72 -> 63, 5120 x 8192 37 -> 33, 6912 x 5120 28.5 -> 26.7; 5120 x 1280 at 80 rows
 // loses 0.3 us of 7).

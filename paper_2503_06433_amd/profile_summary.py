@@ -51,12 +51,14 @@ import statistics
 
 WORKLOAD = {2: "c2_llama2_7b_layer", 3: "c3_llama2_13b_tp4", 4: "c4_llama3_70b_tp8", 5: "c5_llama3_70b_pp8_slice"}
 
-# kernel class of the bench line <- substring of the kernel name
+# kernel class of the bench line <- substring of the kernel name.  The persistent kernel serves prefill batches; its
+# instance that writes partial sums, and all of it in a run without a prefill batch, belongs to the decode products.
+PARTIAL_SUMS = "gemm_mfma_stream_kernel<100>"
 CLASSES = (
     ("prefill_gemms", ("gemm_mfma_stream_kernel",)),
     ("prefill_attention", ("attn_prefill_lds_kernel", "attn_prefill_mfma_kernel")),
     ("decode_attention", ("attn_decode_mfma_kernel", "attn_decode_merge_kernel")),
-    ("decode_gemms", ("gemm_mfma_kernel<", "splitk_reduce_kernel")),
+    ("decode_gemms", ("gemm_mfma_kernel<", "gemm_direct_kernel", "gemm_tile_kernel", "splitk_reduce_kernel", PARTIAL_SUMS)),
     ("kv_repack", ("kv_repack_kernel",)),
 )
 
@@ -64,6 +66,7 @@ CLASSES = (
 def short(name):
     name = re.sub(r"^void ", "", name)
     name = re.sub(r"^ssk(16)?::", "", name)
+    name = name.replace("(anonymous namespace)::", "").replace("ssk::", "").replace("ssk16::", "")
     name = re.sub(r"\(.*$", "", name)
     return name[:64]
 
@@ -226,6 +229,10 @@ def class_bytes(total, config):
     out = {}
     for cls, subs in CLASSES:
         b = size(subs)
+        if cls == "prefill_gemms":
+            b -= size((PARTIAL_SUMS,))
+        if cls == "decode_gemms" and not n_prefill:
+            b += size(("gemm_mfma_stream_kernel",)) - size((PARTIAL_SUMS,))
         if not b:
             continue
         if cls == "kv_repack" and config not in (2, 5):
