@@ -91,8 +91,8 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const T* __restrict__
 // eight tokens through two layers in 612 us with this kernel and 750 us with the tiled one.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __restrict__ qkv, T* __restrict__ out, int n_q,
-                                                                  int n_kv, BatchMeta bm, const T* __restrict__ k_pool,
-                                                                  const T* __restrict__ v_pool, float scale) {
+                                                                  int n_kv, BatchMeta bm, const float* __restrict__ rope,
+                                                                  T* k_pool, T* v_pool, float scale) {
     constexpr int PS = 16, DS = D / 4, DR = D / 64;
     constexpr int EV = 16 / (int)sizeof(T);             // elements of a 16-byte load
     __shared__ float sm[4], sl[4], so[4][D];
@@ -104,13 +104,32 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int tok = lane >> 2, sub = lane & 3;
     float q[DS], acc[DR];
-    {
-        const T* qp = qkv + (size_t)q_begin * ((size_t)(n_q + 2 * n_kv) * D) + (size_t)a * D + sub * DS;
+    const T* row = qkv + (size_t)q_begin * ((size_t)(n_q + 2 * n_kv) * D);
+    // this lane's quarter of a head of the new token; rotated (and rounded as stored) where the batch comes unrotated
+    auto quarter = [&](const T* head, float* f) {
 #pragma unroll
-        for (int i = 0; i < DS / EV; ++i) unpack16<T>(*reinterpret_cast<const vec16*>(qp + i * EV), q + i * EV);
+        for (int i = 0; i < DS / EV; ++i) unpack16<T>(*reinterpret_cast<const vec16*>(head + sub * DS + i * EV), f + i * EV);
+        if (!rope) return;
+        const float* cs = rope + (size_t)p * D + 2 * (sub & 1) * DS;
 #pragma unroll
-        for (int e = 0; e < DS; ++e) q[e] *= scale;
-    }
+        for (int i = 0; i < DS / EV; ++i) {
+            float o[EV];
+            unpack16<T>(*reinterpret_cast<const vec16*>(head + (sub ^ 2) * DS + i * EV), o);
+#pragma unroll
+            for (int e = 0; e < EV; ++e) {
+                float r[2], own = f[i * EV + e];
+                const float c = cs[2 * (i * EV + e)], sn = cs[2 * (i * EV + e) + 1];
+                if (sub < 2) rope_rotate(own, o[e], c, sn, r[0], r[1]);
+                else rope_rotate(o[e], own, c, sn, r[1], r[0]);
+                T st;
+                stf(&st, r[0]);
+                f[i * EV + e] = ldf(&st);
+            }
+        }
+    };
+    quarter(row + (size_t)a * D, q);
+#pragma unroll
+    for (int e = 0; e < DS; ++e) q[e] *= scale;
 #pragma unroll
     for (int r = 0; r < DR; ++r) acc[r] = 0.f;
     float m = -INFINITY, l = 0.f;
@@ -126,6 +145,22 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
         for (int r = 0; r < DR; ++r)
 #pragma unroll
             for (int i = 0; i < PS / EV; ++i) vr[r][i] = *reinterpret_cast<const vec16*>(vp + r * 64 * PS + i * EV);
+        // The new token's key and value come from the products, for every head of the group; the first head's block writes
+        // them into the page.
+        const bool fresh = rope && j == n_pages - 1;
+        const int slot = p % PS;
+        if (fresh) {
+            if (tok == slot) {
+                float kn[DS];
+                quarter(row + (size_t)(n_q + g) * D, kn);
+#pragma unroll
+                for (int i = 0; i < DS / EV; ++i) {
+                    kr[i] = pack16<T>(kn + i * EV);
+                    if (a % (n_q / n_kv) == 0)
+                        *reinterpret_cast<vec16*>(k_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D + tok * D + sub * DS + i * EV) = kr[i];
+                }
+            }
+        }
         float d = 0.f;
 #pragma unroll
         for (int i = 0; i < DS / EV; ++i) {
@@ -150,6 +185,13 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
             float v[PS], sum = acc[r] * alpha;
 #pragma unroll
             for (int i = 0; i < PS / EV; ++i) unpack16<T>(vr[r][i], v + i * EV);
+            if (fresh) {
+                const int e = r * 64 + lane, at = vpos(slot, e);
+                const T vn = row[(size_t)(n_q + n_kv + g) * D + e];
+#pragma unroll
+                for (int t = 0; t < PS; ++t) v[t] = t == at ? ldf(&vn) : v[t];
+                if (a % (n_q / n_kv) == 0) v_pool[(size_t)pt[j] * page_elems + (size_t)g * PS * D + e * PS + at] = vn;
+            }
 #pragma unroll
             for (int t = 0; t < PS; ++t) sum = fmaf(__shfl(w, 4 * vtok(t, lane), 64), v[t], sum);   // rows lane, lane + 64: one order
             acc[r] = sum;
@@ -174,20 +216,22 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
     }
 }
 
+// With a rope table the new tokens come unrotated and their pages are written here: batches of one query per sequence only.
 hipError_t attn_generic(int dt, const void* qkv, void* out, int n_q, int n_kv, const BatchMeta& bm,
-                        const KvLayer& kv, hipStream_t s) {
+                        const KvLayer& kv, const float* rope_table, hipStream_t s) {
     if (bm.T <= 0 || bm.n_seqs <= 0) return hipSuccess;
     if (kv.page_size != 16 || (kv.d != 64 && kv.d != 128) || n_kv <= 0 || n_q % n_kv != 0 || kv.n_heads != n_kv)
         return hipErrorInvalidValue;
     if (bm.n_seqs > 65535 || n_q > 65535) return hipErrorInvalidValue;
     // every sequence brings one query: the kernel made for that, whatever the number of cached tokens
     const bool one = bm.max_q_len == 1;
+    if (rope_table && !one) return hipErrorInvalidValue;
     dim3 grid((bm.max_q_len + 63) / 64, n_q, bm.n_seqs);
     const float scale = 1.0f / sqrtf((float)kv.d);
 #define SS_GO(TT, DD)                                                                                       \
     if (one)                                                                                                \
         attn_generic_decode_kernel<TT, DD><<<dim3(n_q, bm.n_seqs), 256, 0, s>>>(                            \
-            (const TT*)qkv, (TT*)out, n_q, n_kv, bm, (const TT*)kv.k_pool, (const TT*)kv.v_pool, scale);    \
+            (const TT*)qkv, (TT*)out, n_q, n_kv, bm, rope_table, (TT*)kv.k_pool, (TT*)kv.v_pool, scale);    \
     else                                                                                                    \
         attn_generic_kernel<TT, DD><<<grid, 256, 0, s>>>((const TT*)qkv, (TT*)out, n_q, n_kv, bm,           \
                                                          (const TT*)kv.k_pool, (const TT*)kv.v_pool, scale)

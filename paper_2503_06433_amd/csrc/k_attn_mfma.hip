@@ -458,12 +458,12 @@ __global__ __launch_bounds__(512) void attn_prefill_lds_kernel(const bf16_t* __r
 }
 
 hipError_t attn_generic(int dt, const void* qkv, void* out, int n_q, int n_kv, const BatchMeta& bm,
-                        const KvLayer& kv, hipStream_t s);
+                        const KvLayer& kv, const float* rope_table, hipStream_t s);
 
 hipError_t attn_prefill(int dt, const void* qkv, void* out, int n_q, int n_kv, const BatchMeta& bm,
                         const KvLayer& kv, bool force_generic, hipStream_t s) {
     if (bm.T <= 0 || bm.n_seqs <= 0) return hipSuccess;
-    if (dt != BF16 || force_generic || kv.d != 128) return attn_generic(dt, qkv, out, n_q, n_kv, bm, kv, s);
+    if (dt != BF16 || force_generic || kv.d != 128) return attn_generic(dt, qkv, out, n_q, n_kv, bm, kv, nullptr, s);
     if (kv.page_size != 16 || n_kv <= 0 || n_q % n_kv != 0 || kv.n_heads != n_kv) return hipErrorInvalidValue;
     if (bm.n_seqs > 65535 || n_q > 65535) return hipErrorInvalidValue;
     const float sl2 = 1.4426950408889634f / sqrtf((float)kv.d);
@@ -497,31 +497,40 @@ hipError_t attn_prefill(int dt, const void* qkv, void* out, int n_q, int n_kv, c
 // tokens of each page per group): no more than 0.2 % either way (six steps of 1024 sequences on one kv head 3175 -> 3169 us, of
 // 256 sequences of the 7B shape 8075 -> 8093).  Bound by the page reads: 5.5 TB/s with 32 kv heads, 5 with one.  A third wave
 // per SIMD (146 registers) changes neither.
+// The new token's q, k and v come unrotated from the products.  Every wave rotates its q fragments in registers (k-step
+// ks holds the partners of ks + 2 in the same lane); the one whose item has the new token's page starts its sums with the
+// new token, out of registers.  The merge kernel writes its key and value into the page: that takes a launch out of the
+// chain (eight chat users of the 7B shape, eight tokens through two layers 1995 -> 1932 us; six steps of 1024 sequences on one
+// kv head 3161 -> 3114, of 512 on ten heads 7306 -> 7279, of 256 on 32 heads 8081 -> 8034).  Written by this kernel the value
+// alone, in stores of two bytes or as whole 4 KB pieces of the page, cost 50 us a step of 256 sequences on 32 heads: writes
+// between the page reads of the other waves.
 // Partial (max, sum, O) of every item go to scratch and are merged per sequence.
 // scratch layout: float [n_items][n_q][D + 4]  (O[D], running max, running sum)
 // ======================================================================
 template <int D>
 __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __restrict__ qkv, int n_q, int n_kv,
-                                                              BatchMeta bm, DecodeWork wk,
+                                                              BatchMeta bm, DecodeWork wk, const float* __restrict__ rope,
                                                               const bf16_t* __restrict__ k_pool,
                                                               const bf16_t* __restrict__ v_pool,
                                                               float* __restrict__ scratch, float scale_log2e) {
     constexpr int KS = D / 32;
     constexpr int DT = D / 16;
+    static_assert(D == 128, "the rotation pairs k-step ks with ks + 2");
     const int item = wk.item_order[blockIdx.x / n_kv], g = blockIdx.x % n_kv;     // the heads of an item side by side
     const int G = n_q / n_kv;
     const int sq = wk.item_seq[item];
     // an item is pages page0, page0 + stride, ... (npg of them) of its sequence: the items of a sequence interleave
     const int page0 = wk.item_page0[item], npg = wk.item_npages[item] & 0xffff;
     const int stride = (wk.item_npages[item] >> 16) > 0 ? (wk.item_npages[item] >> 16) : 1;
-    const int kv_len = bm.kv_before[sq] + 1;
+    const int n_old = bm.kv_before[sq];                  // cached tokens; the new one has this position
     const int lane = threadIdx.x;
     const int lq = lane & 15, g4 = lane >> 4;
     const size_t row_stride = (size_t)(n_q + 2 * n_kv) * D;
 
     Frag qf[KS];
+    const bf16_t* tok = qkv + (size_t)bm.cu_q[sq] * row_stride;
     if (lq < G) {
-        const bf16_t* qp = qkv + (size_t)bm.cu_q[sq] * row_stride + (size_t)(g * G + lq) * D + g4 * 8;
+        const bf16_t* qp = tok + (size_t)(g * G + lq) * D + g4 * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[ks].q = *reinterpret_cast<const vec16*>(qp + ks * 32);
     } else {
@@ -580,13 +589,13 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
         float mx = m;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            sA[v] = (there && pos0 + v < kv_len) ? sA[v] * scale_log2e : -INFINITY;
-            sB[v] = (there && pos0 + 8 + v < kv_len) ? sB[v] * scale_log2e : -INFINITY;
+            sA[v] = (there && pos0 + v < n_old) ? sA[v] * scale_log2e : -INFINITY;
+            sB[v] = (there && pos0 + 8 + v < n_old) ? sB[v] * scale_log2e : -INFINITY;
             mx = fmaxf(mx, fmaxf(sA[v], sB[v]));
         }
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        // the first page of an item always holds a visible token: mx is finite
+        // the item's first page holds a visible token, or the new one came first: mx is finite
         const float alpha = fast_exp2(m - mx);
         m = mx;
         float rs = 0.f;
@@ -597,6 +606,17 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
             rs += sA[v] + sB[v];
         }
         l = l * alpha + rs;
+        // The page of the new token: its own slot and those behind it hold what the page's last user left.  Weight 0 would
+        // not keep a value that is not finite out of the sums; nor one of a page that is only repeated.
+        if ((page0 + (pi + 1) * stride) * 16 + 16 > n_old || !hasB) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const int p = pos0 + 2 * (w & 1) + 8 * (w >> 1);
+                const uint32_t keep = there ? (p < n_old ? 0xffffu : 0u) | (p + 1 < n_old ? 0xffff0000u : 0u) : 0u;
+#pragma unroll
+                for (int t = 0; t < DT; ++t) vf[t].w[w] &= keep;
+            }
+        }
         Frag pf;
         pf.w[0] = pack_bf16x2(sA[0], sA[1]);
         pf.w[1] = pack_bf16x2(sA[2], sA[3]);
@@ -615,6 +635,56 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
     pair_pages(0, pA, pB);
     Frag k0a[KS], k0b[KS], k1a[KS], k1b[KS];
     load_k(pA, pB, k0a, k0b);
+    // cos / sin of this lane's element pairs: k-steps ks and ks + 2 hold the two halves
+    float cs[KS / 2][16];
+    {
+        const float* rp = rope + (size_t)n_old * D + 16 * g4;             // [D / 2][2] = cos, sin of the new token's position
+#pragma unroll
+        for (int h = 0; h < KS / 2; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(rp + 64 * h + 4 * j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) cs[h][4 * j + e] = v[e];
+            }
+    }
+    auto rotate = [&](Frag* f) {
+#pragma unroll
+        for (int h = 0; h < KS / 2; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float x[4], r[4];
+                unpack_bf16x2(f[h].w[j], x[0], x[1]);
+                unpack_bf16x2(f[h + 2].w[j], x[2], x[3]);
+#pragma unroll
+                for (int e = 0; e < 2; ++e) rope_rotate(x[e], x[2 + e], cs[h][4 * j + 2 * e], cs[h][4 * j + 2 * e + 1], r[e], r[2 + e]);
+                f[h].w[j] = pack_bf16x2(r[0], r[1]);
+                f[h + 2].w[j] = pack_bf16x2(r[2], r[3]);
+            }
+    };
+    rotate(qf);
+    // The new token is the first term of the wave whose item has its page, taken from registers: weight 1 at its own score.
+    const int past0 = n_old / 16 - page0;
+    if (past0 >= 0 && past0 % stride == 0 && past0 / stride < npg) {
+        const bf16_t *kn = tok + (size_t)(n_q + g) * D, *vn = kn + (size_t)n_kv * D;
+        Frag kf[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kf[ks].q = *reinterpret_cast<const vec16*>(kn + ks * 32 + g4 * 8);
+#pragma unroll
+        for (int t = 0; t < DT; ++t) {
+            const vec8 v = *reinterpret_cast<const vec8*>(vn + t * 16 + 4 * g4);
+            float x[4];
+            unpack_bf16x2(v.w[0], x[0], x[1]);
+            unpack_bf16x2(v.w[1], x[2], x[3]);
+            o[t] = f32x4_t{x[0], x[1], x[2], x[3]};
+        }
+        rotate(kf);
+        f32x4_t sn = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) sn = SS_MFMA_16x16x32(kf[ks].v, qf[ks].v, sn, 0, 0, 0);      // every row is the new token
+        m = sn[0] * scale_log2e;
+        l = g4 == 0 ? 1.f : 0.f;
+    }
     int pi = 0;
     for (; pi + 2 < npg; pi += 4) {
         int nA, nB;
@@ -639,11 +709,45 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
 // sequence has one to a few items, so the maxima, sums and outputs of four of them are requested together.  Against two
 // dependent passes over them, one item at a time: eight sequences of the 7B shape, two layers and the LM head 251.8 -> 248.4 us
 // a token, 1024 sequences on one kv head 536 -> 528 us a step.
+// Blocks behind the merging ones write the new tokens' keys (rotated again, the same operations as in the attention kernel)
+// and values into their pages, HB kv heads each.  Blocks of their own: in front of the merge in the same blocks 1 % of a
+// chat user's token slower.
 template <int D, int HB>
 __global__ __launch_bounds__(D / 4 * HB) void attn_decode_merge_kernel(const float* __restrict__ scratch,
-                                                                       bf16_t* __restrict__ out, int n_q, BatchMeta bm,
-                                                                       DecodeWork wk) {
-    const int a = blockIdx.x * HB + threadIdx.x / (D / 4), sq = blockIdx.y, e = threadIdx.x % (D / 4) * 4;
+                                                                       bf16_t* __restrict__ out, int n_q, int n_kv, BatchMeta bm,
+                                                                       DecodeWork wk, const bf16_t* __restrict__ qkv,
+                                                                       const float* __restrict__ rope, bf16_t* __restrict__ k_pool,
+                                                                       bf16_t* __restrict__ v_pool) {
+    const int sq = blockIdx.y, e = threadIdx.x % (D / 4) * 4;
+    const int merge_blocks = (n_q + HB - 1) / HB;
+    if ((int)blockIdx.x >= merge_blocks) {
+        const int g = ((int)blockIdx.x - merge_blocks) * HB + threadIdx.x / (D / 4), pos = bm.kv_before[sq], slot = pos & 15;
+        if (g >= n_kv) return;
+        const bf16_t* kn = qkv + (size_t)bm.cu_q[sq] * ((size_t)(n_q + 2 * n_kv) * D) + (size_t)(n_q + g) * D;
+        const bf16_t* vn = kn + (size_t)n_kv * D;
+        const size_t page = ((size_t)bm.page_tables[(size_t)sq * bm.pt_stride + pos / 16] * n_kv + g) * 16 * D;
+        const int i0 = e % (D / 2);                  // both halves' threads form the pair and keep their own
+        const f32x4_t c0 = *reinterpret_cast<const f32x4_t*>(rope + (size_t)pos * D + 2 * i0);
+        const f32x4_t c1 = *reinterpret_cast<const f32x4_t*>(rope + (size_t)pos * D + 2 * i0 + 4);
+        const vec8 lo = *reinterpret_cast<const vec8*>(kn + i0), hi = *reinterpret_cast<const vec8*>(kn + i0 + D / 2);
+        const vec8 v = *reinterpret_cast<const vec8*>(vn + e);
+        vec8 k;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float x[4], r[4];
+            unpack_bf16x2(lo.w[j], x[0], x[1]);
+            unpack_bf16x2(hi.w[j], x[2], x[3]);
+            const f32x4_t c = j ? c1 : c0;
+            rope_rotate(x[0], x[2], c[0], c[1], r[0], r[2]);
+            rope_rotate(x[1], x[3], c[2], c[3], r[1], r[3]);
+            k.w[j] = e < D / 2 ? pack_bf16x2(r[0], r[1]) : pack_bf16x2(r[2], r[3]);
+        }
+        *reinterpret_cast<vec8*>(k_pool + page + slot * D + e) = k;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v_pool[page + (size_t)(e + j) * 16 + vpos(slot, e + j)] = (bf16_t)(v.w[j >> 1] >> (16 * (j & 1)));
+        return;
+    }
+    const int a = blockIdx.x * HB + threadIdx.x / (D / 4);
     if (a >= n_q) return;
     const int i0 = wk.seq_item0[sq], i1 = wk.seq_item0[sq + 1];
     float M = -INFINITY, den = 0.f;
@@ -688,21 +792,22 @@ __global__ __launch_bounds__(D / 4 * HB) void attn_decode_merge_kernel(const flo
 size_t attn_decode_scratch_floats(int n_items, int n_q, int d) { return (size_t)n_items * n_q * (d + 4); }
 
 hipError_t attn_decode(int dt, const void* qkv, void* out, int n_q, int n_kv, const BatchMeta& bm,
-                       const KvLayer& kv, const DecodeWork& wk, float* scratch, bool force_generic,
+                       const KvLayer& kv, const DecodeWork& wk, const float* rope_table, float* scratch, bool force_generic,
                        hipStream_t s) {
     if (bm.n_seqs <= 0) return hipSuccess;
-    if (n_kv <= 0 || n_q % n_kv != 0) return hipErrorInvalidValue;
+    if (n_kv <= 0 || n_q % n_kv != 0 || !rope_table) return hipErrorInvalidValue;
     const int G = n_q / n_kv;
-    if (dt != BF16 || force_generic || kv.d != 128 || G > 16) return attn_generic(dt, qkv, out, n_q, n_kv, bm, kv, s);
+    if (dt != BF16 || force_generic || kv.d != 128 || G > 16) return attn_generic(dt, qkv, out, n_q, n_kv, bm, kv, rope_table, s);
     if (kv.page_size != 16 || kv.n_heads != n_kv || !scratch || wk.n_items <= 0) return hipErrorInvalidValue;
     if (n_kv > 65535 || bm.n_seqs > 65535) return hipErrorInvalidValue;
     const float sl2 = 1.4426950408889634f / sqrtf((float)kv.d);
     if ((long long)wk.n_items * n_kv > 0x7fffffffll) return hipErrorInvalidValue;
     dim3 grid((unsigned)(wk.n_items * n_kv));
-    attn_decode_mfma_kernel<128><<<grid, 64, 0, s>>>((const bf16_t*)qkv, n_q, n_kv, bm, wk,
+    attn_decode_mfma_kernel<128><<<grid, 64, 0, s>>>((const bf16_t*)qkv, n_q, n_kv, bm, wk, rope_table,
                                                      (const bf16_t*)kv.k_pool, (const bf16_t*)kv.v_pool, scratch, sl2);
-    dim3 mgrid((n_q + 7) / 8, bm.n_seqs);
-    attn_decode_merge_kernel<128, 8><<<mgrid, 256, 0, s>>>(scratch, (bf16_t*)out, n_q, bm, wk);
+    dim3 mgrid((n_q + 7) / 8 + (n_kv + 7) / 8, bm.n_seqs);
+    attn_decode_merge_kernel<128, 8><<<mgrid, 256, 0, s>>>(scratch, (bf16_t*)out, n_q, n_kv, bm, wk, (const bf16_t*)qkv, rope_table,
+                                                         (bf16_t*)kv.k_pool, (bf16_t*)kv.v_pool);
     return hipGetLastError();
 }
 

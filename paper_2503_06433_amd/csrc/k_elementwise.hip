@@ -304,10 +304,7 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(T* __restrict__ qkv, 
             unpack16<T>(*reinterpret_cast<const vec16*>(lo_p), lo);
             unpack16<T>(*reinterpret_cast<const vec16*>(hi_p), hi);
 #pragma unroll
-            for (int j = 0; j < V; ++j) {
-                olo[j] = lo[j] * c[j] - hi[j] * sn[j];
-                ohi[j] = hi[j] * c[j] + lo[j] * sn[j];
-            }
+            for (int j = 0; j < V; ++j) rope_rotate(lo[j], hi[j], c[j], sn[j], olo[j], ohi[j]);
             const vec16 plo = pack16<T>(olo), phi = pack16<T>(ohi);
             if (hh < G) {
                 *reinterpret_cast<vec16*>(lo_p) = plo;

@@ -122,6 +122,13 @@ __device__ __forceinline__ int vslot(int s) { return (s & 3) | ((s & 4) << 1) | 
 __device__ __forceinline__ int vpos(int s, int e) { return vslot(s) ^ (e & 8); }
 __device__ __forceinline__ int vtok(int p, int e) { return vslot(p ^ (e & 8)); }
 
+// The rotation of one element pair (i, i + d / 2) of a head.  One definition, and no contraction left to the compiler: the
+// kernels that write a token's key into its page store the same bits.
+__device__ __forceinline__ void rope_rotate(float lo, float hi, float c, float s, float& olo, float& ohi) {
+    olo = fmaf(lo, c, -(hi * s));
+    ohi = fmaf(hi, c, lo * s);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

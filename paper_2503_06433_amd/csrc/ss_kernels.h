@@ -171,8 +171,10 @@ hipError_t attn_prefill(int dt, const void* qkv, void* out, int n_q, int n_kv,
 
 size_t attn_decode_scratch_floats(int n_items, int n_q, int d);
 
+// One new token per sequence: rotates its q and k, writes k and v into the token's page, attends to the cache with it.
+// qkv is as the products leave it (rope_kvwrite has not run) and stays that way.
 hipError_t attn_decode(int dt, const void* qkv, void* out, int n_q, int n_kv,
-                       const BatchMeta& bm, const KvLayer& kv, const DecodeWork& wk,
+                       const BatchMeta& bm, const KvLayer& kv, const DecodeWork& wk, const float* rope_table,
                        float* scratch, bool force_generic, hipStream_t s);
 
 hipError_t kv_gather(int dt, void* const* k_pools, void* const* v_pools, int n_heads, int d,

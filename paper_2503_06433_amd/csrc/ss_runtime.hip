@@ -876,15 +876,15 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     if ((rc = splitk_ws(c, T, &ws))) return rc;
     const ssk::KvLayer kv = kv_layer(c, s, ll);
     if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, rs, ws, st))) return rc;
-    {
-        ProfScope ps(c, 4, st);
-        K_TRY(c, SSK_CALL(c, rope_kvwrite, c->ws_qkv.p, s->nq_l, s->nkv_l, c->d_rope, ms->bm, kv, st));
-    }
     if (decode) {
         ProfScope ps(c, 2, st);
-        K_TRY(c, SSK_CALL(c, attn_decode, c->ws_qkv.p, c->ws_attn.p, s->nq_l, s->nkv_l, ms->bm, kv, ms->wk,
+        K_TRY(c, SSK_CALL(c, attn_decode, c->ws_qkv.p, c->ws_attn.p, s->nq_l, s->nkv_l, ms->bm, kv, ms->wk, c->d_rope,
                                   (float*)c->ws_scratch.p, c->force_generic, st));
     } else {
+        {
+            ProfScope ps(c, 4, st);
+            K_TRY(c, SSK_CALL(c, rope_kvwrite, c->ws_qkv.p, s->nq_l, s->nkv_l, c->d_rope, ms->bm, kv, st));
+        }
         ProfScope ps(c, 1, st);
         K_TRY(c, SSK_CALL(c, attn_prefill, c->ws_qkv.p, c->ws_attn.p, s->nq_l, s->nkv_l, ms->bm, kv,
                                    c->force_generic, st));
