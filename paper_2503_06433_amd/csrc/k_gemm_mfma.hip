@@ -735,6 +735,28 @@ static hipError_t device_cus(int* out) {
     return hipSuccess;
 }
 
+// Tile rows per group of the walk: the 32 CUs of an XCD cover GM x 32/GM tiles at a time, so an XCD re-fetches its token
+// slices (tiles_n * GM / 32) times and the weight slices once per group from beyond its L2; with the eight XCDs sweeping
+// the columns in step (8 GM tile rows and more) those re-fetches are served by the memory-side cache (the 8 GM tile rows in
+// use and the 32/GM tile columns of weights fit it), and HBM sees the weights once per 8 GM tile rows.  Groups of 4.  Outputs
+// of 64 tile columns and more (us of a launch with groups of 2 / 4 / 8, or as named):
+//  - 17 to 29 tile rows: groups of 2, with which 16 of the rows are walked in step (18 rows 27648 x 5120 958 / 1102 / 1020,
+//    57344 x 8192 3103 / 3255 / 3117; 31 rows 1665 / 1623 / 1677, 5794 / 5489 / 5447; 79 rows of 57344 x 8192 13964 / 13022
+//    / 13540, 47 rows 8606 / 7883 / 8572, 22016 x 4096 2612 / 2549 / 2578);
+//  - fewer than 16: no XCD is in step with another, each has a run of whole columns where a group holds all rows; one or
+//    two groups of equal height (9 rows 57344 x 8192 1891 / 1775 / 1728, groups of 5 1537; 13 rows 2655 / 2466 / 2312, of 7
+//    2267; 27648 x 5120 790 / 730 / 703, of 7 715; 22016 x 4096 458 / 451 / 452, of 7 452);
+//    8 rows stay at 4 (27648 x 5120 448 / 448 / 461, 57344 x 8192 1358 / 1322 / 1339);
+//  - fewer than 6 and contractions shorter than 8192: groups of 2, 5 rows 4 (4 rows 27648 x 5120 228 / 242 / 242, 22016 x 4096
+//    197 / 194 / 195; 57344 x 8192 775 / 715 / 725; 5 rows 27648 x 5120 348 / 345 / 362, groups of 5 361; 57344 x 8192 1043 /
+//    974 / 894).
+static int group_rows(int tiles_m, int tiles_n, int K) {
+    if (tiles_n < 64 || tiles_m >= 30 || tiles_m == 16 || tiles_m == 8) return 4;
+    if (tiles_m > 16) return 2;
+    if (tiles_m < 6 && K < 8192) return tiles_m == 5 ? 4 : 2;
+    return tiles_m < 8 ? tiles_m : (tiles_m + 1) / 2;
+}
+
 // Blocks of the persistent kernel own their CU (all registers, all LDS) until they are done, so a kernel
 // of another stream can only start at a launch boundary.  `max_rounds` > 0 cuts the walk into launches
 // of at most that many tiles per block, for callers that have latency-bound work on other streams.
@@ -757,16 +779,8 @@ static hipError_t launch_stream(const bf16_t* A, int lda, const bf16_t* Wt, bf16
     hipError_t e_cus = device_cus(&n_cus);
     if (e_cus != hipSuccess) return e_cus;
     const int cus_per_xcd = n_cus / 8;
-    // Tile rows per group of the walk: the 32 CUs of an XCD cover GM x 32/GM tiles at a time, so an XCD re-fetches
-    // its token slices (tiles_n * GM / 32) times and the weight slices once per group from beyond its L2; with the
-    // eight XCDs sweeping the columns in step those re-fetches are served by the memory-side cache (the 8 GM tile
-    // rows in use and the 32/GM tile columns of weights fit it), and HBM sees the weights once per 8 GM tile rows.
-    // Measured (fraction of the MFMA peak over the four GEMMs of a layer, GM = 2 / 4 / 8 / 16): 70B-shape slice of
-    // 75 k tokens 0.518 / 0.529 / 0.501 / 0.477, 13B shape 0.503 / 0.510 / 0.518 / 0.457, 7B shape of 20 k tokens
-    // 0.524 / 0.516 / 0.508 / 0.488; without the XCDs in step (each on a contiguous run of tiles): 0.499 on the
-    // 70B shape.  Groups of 4, of 2 for wide outputs of few tile rows.
     static const int gm_env = getenv("SS_GEMM_GROUP_ROWS") ? atoi(getenv("SS_GEMM_GROUP_ROWS")) : 0;
-    const int gm_rows = gm_env > 0 ? gm_env : (tiles_n >= 64 && tiles_m < 100 ? 2 : 4);
+    const int gm_rows = gm_env > 0 ? gm_env : group_rows(tiles_m, tiles_n, K);
     // the longest list of an XCD: its whole groups plus its share of the left-over rows (same arithmetic as the kernel)
     static const int sync_walk = getenv("SS_GEMM_SYNC_WALK") ? atoi(getenv("SS_GEMM_SYNC_WALK")) : 1;
     // L2 prefetch distance in slices (0 = off; the kernel needs at least 2).  Measured on the 70B-shape slice
