@@ -87,6 +87,7 @@ hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int l
 bool gemm_mfma_supported(int M, int N, int K, int lda, int ldc, int epi);
 bool gemm_mfma_stream_supported(const void* C, const void* R, int ldc, int M, int N, int K, int lda, int epi);
 bool gemm_tile_supported(const void* A, const void* Wt, const void* C, const void* R, int ldc, int M, int N, int K, int lda, int epi);
+int gemm_stream_columns(int M, int N, int K, int n_cus, int* pick);
 GemmPlan gemm_mfma_plan(bool stream_ok, bool tile_ok, int M, int N, int K, int epi, size_t ws_bytes, int n_cus);
 bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int K, int lda, int epi);
 hipError_t gemm_direct(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
@@ -127,4 +128,5 @@ extern "C" int ssk_gemm_plan(int dt, int M, int N, int K, int epi, long long ws_
     *split = plan.split;
     return plan.kernel;
 }
+extern "C" int ssk_gemm_stream_columns(int M, int N, int K, int n_cus, int* pick) { return ssk::gemm_stream_columns(M, N, K, n_cus, pick); }
 #endif

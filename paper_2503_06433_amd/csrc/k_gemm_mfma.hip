@@ -989,6 +989,30 @@ GemmPlan gemm_mfma_plan(bool stream_ok, bool tile_ok, int M, int N, int K, int e
     return plan;
 }
 
+// Output columns that the persistent kernel takes, the others go to tile `*pick` of the tile kernel.  The last round of tiles
+// costs the persistent kernel a whole round (1.5 us a slice) however few of the compute units have one.  So it gets the
+// columns of its whole rounds, and the tile kernel, which has a tile for every unit, the rest, where its estimate is low enough
+// against the 1.5 us: 1.2 with one whole round; with more of them the second launch has less to win, and the estimate, 15 to 25 %
+// high on contractions of 64 to 160 slices, is right on others: 1.1 and 1.  Whole / cut, by the rounds:
+//   520 x 22016 x 4096 (1.01) 173 / 114 us, 1400 x 12288 x 4096 (1.12) 184 / 140, 5000 x 4096 x 11008 (1.25) 480 / 389,
+//   864 x 22016 x 4096 (1.34) 179 / 152, 2840 x 8192 x 8192 (1.5) 351 / 321, 1760 x 14336 x 8192 (1.53) 359 / 314,
+//   2400 x 22016 x 4096 (2.36) 366 / 352, 3650 x 15360 x 5120 (3.52) 488 / 450, 6400 x 22016 x 4096 (8.4) 853 / 848.
+// Beyond the lines: 2750 x 8192 x 1024 (1.38) 59.2 / 60.5, 9740 x 4096 x 2752 (2.44) 194 / 200, 10970 x 5120 x 13824 (3.36)
+// 1267 / 1295, 5000 x 57344 x 8192 (17.5) 3551 / 3567.
+int gemm_stream_columns(int M, int N, int K, int n_cus, int* pick) {
+    const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
+    const long long tiles = (long long)tiles_m * tiles_n, rounds = tiles / n_cus;
+    *pick = -1;
+    if (rounds < 1 || tiles % n_cus == 0) return N;
+    const long long cols = rounds * n_cus / tiles_m;
+    if (cols < 1 || cols >= tiles_n) return N;
+    const int n1 = (int)cols * 256;
+    const float us = gemm_tile_estimate(M, N - n1, K, n_cus, pick);
+    const int slices = K / 64;
+    if (*pick < 0 || us > (rounds == 1 ? 1.2f : slices >= 64 && slices < 160 ? 1.1f : 1.0f) * slices) return N;
+    return n1;
+}
+
 hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N,
                           int K, int epi, hipStream_t s, float* ws, size_t ws_bytes, int max_rounds, const float* rs) {
     const bf16_t* a = (const bf16_t*)A;
@@ -1005,7 +1029,14 @@ hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int l
                                       ws_ok ? ws_bytes : 0, n_cus);
     if (p.kernel == GEMM_TILE) return gemm_tile(p.pick, a, lda, w, C, ldc, r, M, N, K, epi, rs, s);
     if (p.kernel == GEMM_STAGED) return launch_cfg<128, 128, 2, 2>(a, lda, w, c, ldc, r, M, N, K, epi, s, p.split, ws, rs);
-    if (p.split == 1) return launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs);
+    if (p.split == 1) {
+        int pick = -1;
+        const int n1 = tile_ok ? gemm_stream_columns(M, N, K, n_cus, &pick) : N;
+        e = launch_stream(a, lda, w, c, ldc, r, M, n1, K, epi, s, max_rounds, rs);
+        if (e != hipSuccess || n1 == N) return e;
+        const int o1 = epi == EPI_SWIGLU ? n1 / 2 : n1;
+        return gemm_tile(pick, a, lda, w + (size_t)n1 * K, c + o1, ldc, r ? r + o1 : nullptr, M, N - n1, K, epi, rs, s);
+    }
     e = launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs, p.split, ws);
     if (e != hipSuccess) return e;
     return reduce_partials(ws, p.split, c, ldc, r, M, N, epi, rs, s);

@@ -90,6 +90,32 @@ def test_products_take_the_kernel_that_was_faster(rows, n, k, epi, kernel, split
     assert (got[0], got[2]) == (kernel, split)
 
 
+def stream_columns(rows, n, k, cus=256):
+    f = C.CDLL(_library()).ssk_gemm_stream_columns
+    f.argtypes = [C.c_int] * 4 + [C.POINTER(C.c_int)]
+    return f(rows, n, k, cus, C.byref(C.c_int()))
+
+
+@pytest.mark.parametrize("rows,n,k,columns", [
+    (520, 22016, 4096, 21760), (864, 22016, 4096, 16384), (1400, 12288, 4096, 10752), (1800, 12288, 4096, 8192),
+    (5000, 4096, 11008, 3072), (1400, 27648, 5120, 21760), (6400, 22016, 4096, 20736),
+    # whole: a last round of more than a half or so, no last round, less than one round
+    (1200, 22016, 4096, 22016), (5000, 15360, 5120, 15360), (4096, 12288, 4096, 12288), (864, 12288, 4096, 12288),
+    # a contraction so short that a launch costs more than the round
+    (520, 22016, 256, 22016),
+])
+def test_columns_of_the_whole_rounds(rows, n, k, columns):
+    assert stream_columns(rows, n, k) == columns
+
+
+@pytest.mark.parametrize("rows,cus", [(r, c) for r in (257, 640, 1111, 4123, 9000, 70000) for c in (8, 64, 256, 304)])
+def test_a_cut_product_keeps_whole_tiles_and_whole_rounds(rows, cus):
+    for n in (256, 1280, 4224, 12288, 22016, 57344):
+        for k in (128, 4096, 28672):
+            c, tiles_m = stream_columns(rows, n, k, cus), -(-rows // 256)
+            assert c == n or (0 < c < n and c % 256 == 0 and tiles_m * c // 256 <= tiles_m * -(-n // 256) // cus * cus)
+
+
 @pytest.mark.parametrize("n,k", [(5120, 5120), (5120, 8192), (5120, 6912), (6912, 5120)])
 def test_one_row_of_tiles_takes_64_x_64(n, k):
     assert plan(96, n, k, EPI_RESIDUAL)[:2] == plan(97, n, k, EPI_RESIDUAL)[:2] == (TILE, 1)
