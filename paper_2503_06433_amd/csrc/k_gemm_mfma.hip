@@ -858,14 +858,67 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     }
 }
 
+// The same sums, eight output columns a thread: whole 16-byte pieces of every plane, result and residual row.  Bound by the way
+// of the partial sums back in; against four bytes a load (us of a product with this launch): four ranges of 864 x 4096 x 11008
+// 93 -> 86, eight of 1280 x 1280 x 8192 53 -> 48, eight of 640 x 2560 x 8192 52 -> 47.
+template <int EPI>
+__global__ __launch_bounds__(256) void splitk_reduce8_kernel(const float* __restrict__ P, int S, bf16_t* __restrict__ C, int ldc,
+                                                             const bf16_t* __restrict__ R, int M, int N,
+                                                             const float* __restrict__ RS) {
+    const int n8 = ((EPI == EPI_SWIGLU) ? N / 2 : N) / 8;
+    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (size_t)M * n8) return;
+    const int m = (int)(idx / n8), j = (int)(idx % n8) * 8;
+    const size_t plane = (size_t)M * N;
+    const float* p = P + (size_t)m * N + (EPI == EPI_SWIGLU ? (j >> 5) * 64 + (j & 31) : j);
+    constexpr int NV = EPI == EPI_SWIGLU ? 4 : 2;                       // gate pieces, then up pieces 32 columns on
+    f32x4_t o[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) o[v] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) o[v] += *reinterpret_cast<const f32x4_t*>(p + s * plane + (v >> 1) * 32 + (v & 1) * 4);
+    const float rs = RS ? RS[m] : 1.0f;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) o[v] *= rs;
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = EPI == EPI_SWIGLU ? swiglu_act(o[e >> 2][e & 3], o[(NV - 2) + (e >> 2)][e & 3]) : o[e >> 2][e & 3];
+    if (EPI == EPI_RESIDUAL) {
+        float r[8];
+        unpack16<bf16_t>(*reinterpret_cast<const vec16*>(R + (size_t)m * ldc + j), r);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] += r[e];
+    }
+    vec16 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w.w[e] = pack_bf16x2(x[2 * e], x[2 * e + 1]);
+    *reinterpret_cast<vec16*>(C + (size_t)m * ldc + j) = w;
+}
+
 static hipError_t reduce_partials(const float* ws, int ksplit, bf16_t* C, int ldc, const bf16_t* R, int M, int N, int epi,
                                   const float* rs, hipStream_t s) {
-    const size_t n_out = (size_t)M * (epi == EPI_SWIGLU ? N / 2 : N);
+    if (epi == EPI_RESIDUAL && !R) return hipErrorInvalidValue;
+    const int cols = epi == EPI_SWIGLU ? N / 2 : N;
+    const size_t n_out = (size_t)M * cols;
     const unsigned rgrid = (unsigned)((n_out + 255) / 256);
+    // rows and buffers of whole 16-byte pieces; an odd vocabulary (of all heads only those are cut) or a buffer off the grid takes
+    // the kernel of single columns
+    if (epi != EPI_STORE_F32 && N % 8 == 0 && cols % 8 == 0 && ldc % 8 == 0 &&
+        (((uintptr_t)ws | (uintptr_t)C | (epi == EPI_RESIDUAL ? (uintptr_t)R : 0)) & 15) == 0) {
+        const unsigned g8 = (unsigned)((n_out / 8 + 255) / 256);
+        switch (epi) {
+            case EPI_STORE: splitk_reduce8_kernel<EPI_STORE><<<g8, 256, 0, s>>>(ws, ksplit, C, ldc, R, M, N, rs); break;
+            case EPI_RESIDUAL: splitk_reduce8_kernel<EPI_RESIDUAL><<<g8, 256, 0, s>>>(ws, ksplit, C, ldc, R, M, N, rs); break;
+            case EPI_SWIGLU: splitk_reduce8_kernel<EPI_SWIGLU><<<g8, 256, 0, s>>>(ws, ksplit, C, ldc, R, M, N, rs); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     switch (epi) {
         case EPI_STORE: splitk_reduce_kernel<EPI_STORE><<<rgrid, 256, 0, s>>>(ws, ksplit, C, ldc, R, M, N, rs); break;
         case EPI_RESIDUAL:
-            if (!R) return hipErrorInvalidValue;
             splitk_reduce_kernel<EPI_RESIDUAL><<<rgrid, 256, 0, s>>>(ws, ksplit, C, ldc, R, M, N, rs);
             break;
         case EPI_SWIGLU: splitk_reduce_kernel<EPI_SWIGLU><<<rgrid, 256, 0, s>>>(ws, ksplit, C, ldc, R, M, N, rs); break;
