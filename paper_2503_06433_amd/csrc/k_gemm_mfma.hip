@@ -972,8 +972,9 @@ static hipError_t launch_cfg(const bf16_t* A, int lda, const bf16_t* Wt, bf16_t*
 
 bool gemm_tile_supported(const void* A, const void* Wt, const void* C, const void* R, int ldc, int M, int N, int K, int lda, int epi);
 float gemm_tile_estimate(int M, int N, int K, int n_cus, int* pick);
+float gemm_tile_split_estimate(int M, int N, int K, int n_cus, size_t ws_bytes, int pick_now, float* now, int* pick, int* split);
 hipError_t gemm_tile(int pick, const bf16_t* A, int lda, const bf16_t* Wt, void* C, int ldc, const bf16_t* R, int M, int N, int K,
-                     int epi, const float* rs, hipStream_t s);
+                     int epi, int ksplit, const float* rs, hipStream_t s);
 
 // Ranges of K for the register-staged kernel: until every CU has a block, but only while the fp32 partials (8*S*M*N bytes
 // written and read back) stay below twice the weight bytes (2*N*K) they help to stream: S <= K / (2 M).  (With the bound at
@@ -1031,6 +1032,21 @@ GemmPlan gemm_mfma_plan(bool stream_ok, bool tile_ok, int M, int N, int K, int e
         const float e = 8.f + per * (slices / s_staged) + 0.4e-6f * (float)s_staged * M * N * sizeof(float);
         if (e < us) { us = e; plan = {GEMM_STAGED, 0, s_staged}; }
     }
+    // Tiles with K in ranges, where they are estimated at a tenth less: contractions of 96 slices and more, up to 128 rows of 80
+    // (129 x 5120 x 5120 21.4 us unsplit, 24.4 in ranges; 200 x 3072 x 4096 16.8 and 18.7), from 112 rows on or, where the output is at
+    // most 2560 wide, 65 (80 x 8192 x 8192 31 and 33).  Unsplit / in ranges: 333 x 4096 x 11008 60 / 45 us, 256 rows 52 / 41,
+    // 512 73 / 57; 81 x 1280 x 8192 21.5 / 13.6, 256 rows 25 / 19, 1000 44 / 34; 512 x 2560 x 8192 45 / 35; 200 x 5120 x 13824 74 / 50;
+    // 170 x 8192 x 8192 48 / 42; 129 x 7168 x 8192 (SwiGLU) 47 / 37; 112 x 5120 x 5120 28 / 22.  In place of the persistent
+    // kernel's ranges only below 4096 columns (864 x 1280 x 8192 45 / 32, 450 x 2560 x 8192 47 / 34).  Weights of more than 128 M
+    // elements (8192 x 28672) were not measured and stay with what they had.
+    if (epi != EPI_STORE_F32 && slices >= (M <= 128 ? 80 : 96) && M >= (N <= 2560 ? 65 : 112) && (long long)N * K <= (1ll << 27) &&
+        (plan.kernel == GEMM_TILE || (plan.kernel == GEMM_STREAM && plan.split > 1 && N < 4096))) {
+        int pick = -1, split = 1;
+        float now = 0.f;
+        const float e = gemm_tile_split_estimate(M, N, K, n_cus, ws_bytes, plan.kernel == GEMM_TILE ? plan.pick : -1, &now, &pick, &split);
+        if (plan.kernel == GEMM_STREAM) now = 9.4f + 1.5f * (slices / plan.split) + (float)plan.split * M * N * sizeof(float) / 2.2e6f;
+        if (pick >= 0 && e < 0.9f * now) return {GEMM_TILE, pick, split};
+    }
     // ... and of the LM head over a vocabulary of one to two 128-wide tiles per CU: two of its blocks share a CU, where the tile
     // kernel takes two rounds.  50176 x 768 at 64 / 128 rows 22.8 / 26.5 us, tiles 24.7 / 30.5; x 1600 39.3 / 45, tiles
     // 40.4 / 48; 32000 x 768 (one round of tiles) 16.6 / 18, tiles 14.2 / 17.1.
@@ -1080,7 +1096,11 @@ hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int l
     const bool ws_ok = ws && ((uintptr_t)ws & 15) == 0;
     const GemmPlan p = gemm_mfma_plan(gemm_mfma_stream_supported(C, R, ldc, M, N, K, lda, epi), tile_ok, M, N, K, epi,
                                       ws_ok ? ws_bytes : 0, n_cus);
-    if (p.kernel == GEMM_TILE) return gemm_tile(p.pick, a, lda, w, C, ldc, r, M, N, K, epi, rs, s);
+    if (p.kernel == GEMM_TILE && p.split == 1) return gemm_tile(p.pick, a, lda, w, C, ldc, r, M, N, K, epi, 1, rs, s);
+    if (p.kernel == GEMM_TILE) {
+        e = gemm_tile(p.pick, a, lda, w, ws, N, nullptr, M, N, K, EPI_STORE_F32, p.split, nullptr, s);
+        return e != hipSuccess ? e : reduce_partials(ws, p.split, c, ldc, r, M, N, epi, rs, s);
+    }
     if (p.kernel == GEMM_STAGED) return launch_cfg<128, 128, 2, 2>(a, lda, w, c, ldc, r, M, N, K, epi, s, p.split, ws, rs);
     if (p.split == 1) {
         int pick = -1;
@@ -1088,7 +1108,7 @@ hipError_t gemm_mfma_bf16(const void* A, int lda, const void* Wt, void* C, int l
         e = launch_stream(a, lda, w, c, ldc, r, M, n1, K, epi, s, max_rounds, rs);
         if (e != hipSuccess || n1 == N) return e;
         const int o1 = epi == EPI_SWIGLU ? n1 / 2 : n1;
-        return gemm_tile(pick, a, lda, w + (size_t)n1 * K, c + o1, ldc, r ? r + o1 : nullptr, M, N - n1, K, epi, rs, s);
+        return gemm_tile(pick, a, lda, w + (size_t)n1 * K, c + o1, ldc, r ? r + o1 : nullptr, M, N - n1, K, epi, 1, rs, s);
     }
     e = launch_stream(a, lda, w, c, ldc, r, M, N, K, epi, s, max_rounds, rs, p.split, ws);
     if (e != hipSuccess) return e;

@@ -72,12 +72,16 @@ template <class G>
 __global__ __launch_bounds__(64 * G::NW) void gemm_tile_kernel(const bf16_t* __restrict__ A, int lda,
                                                                const bf16_t* __restrict__ Wt, void* __restrict__ Cv, int ldc,
                                                                const bf16_t* __restrict__ R, int M, int N, int K, int epi,
-                                                               int tiles_m, int n_tiles, int per_xcd,
+                                                               int tiles_m, int n_tiles, int ksplit, int per_xcd,
                                                                const float* __restrict__ RS) {
     constexpr int BM = G::BM, BN = G::BN, TM = G::TM, TN = G::TN, P = G::P, NS = G::NS;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const int logical = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per_xcd || logical >= n_tiles) return;
+    // K in ranges: the tiles of one range after those of another, so that an XCD has one or two ranges of many tiles and not
+    // all ranges of a few; a range's fp32 sums go to its plane of C, [ksplit][M][N]
+    int logical = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || logical >= n_tiles * ksplit) return;
+    const int range = logical / n_tiles;
+    logical -= range * n_tiles;
     const int tile_m = logical % tiles_m, tile_n = logical / tiles_m;
     const bool swi = epi == EPI_SWIGLU;
     const int m0 = tile_m * BM, n0 = tile_n * BN, oc0 = tile_n * (BN / 2);
@@ -88,14 +92,15 @@ __global__ __launch_bounds__(64 * G::NW) void gemm_tile_kernel(const bf16_t* __r
     const uint32_t lds_base = (uint32_t)(uintptr_t)smem;
 
     // ---- loads
-    const int nst = K / 64 / G::SL;
+    const int nst = K / 64 / G::SL / ksplit;
     // The XCDs start at eight different places of K and wrap around: rows of a power-of-two length put one K slice of
     // all rows into few memory channels, and the whole chip walking K in step would ask for one slice at a time (7B
     // shapes of 256 rows: 3-5 % less time).  Blocks of one XCD stay in step, what they share they find in its L2.
     const int rot = (int)(blockIdx.x & 7) * nst / 8;
     const int wrow0 = swi ? (oc0 >> 5) * 64 : n0;
-    const uint8_t* abase = reinterpret_cast<const uint8_t*>(A + (size_t)m0 * lda);
-    const uint8_t* wbase = reinterpret_cast<const uint8_t*>(Wt + (size_t)wrow0 * K);
+    const size_t k0 = (size_t)range * nst * (64 * G::SL);
+    const uint8_t* abase = reinterpret_cast<const uint8_t*>(A + (size_t)m0 * lda + k0);
+    const uint8_t* wbase = reinterpret_cast<const uint8_t*>(Wt + (size_t)wrow0 * K + k0);
     // byte offset of token row / weight row r of the tile from its base; rows beyond the matrix are clamped (their
     // products are never stored)
     auto a_row = [&](int r) -> uint32_t { return (uint32_t)(m0 + r < M ? r : M - 1 - m0) * (uint32_t)lda * 2u; };
@@ -238,7 +243,7 @@ __global__ __launch_bounds__(64 * G::NW) void gemm_tile_kernel(const bf16_t* __r
             };
             f32x4_t o[2] = {sum4(0), sum4(4)};
             if (epi == EPI_STORE_F32) {
-                float* cp = reinterpret_cast<float*>(Cv) + (size_t)m * ldc + c;
+                float* cp = reinterpret_cast<float*>(Cv) + ((size_t)range * M + m) * ldc + c;
                 *reinterpret_cast<f32x4_t*>(cp) = o[0];
                 *reinterpret_cast<f32x4_t*>(cp + 4) = o[1];
                 continue;
@@ -270,19 +275,21 @@ __global__ __launch_bounds__(64 * G::NW) void gemm_tile_kernel(const bf16_t* __r
 
 template <class G>
 static hipError_t launch_tile(const bf16_t* A, int lda, const bf16_t* Wt, void* C, int ldc, const bf16_t* R, int M, int N, int K,
-                              int epi, const float* rs, hipStream_t s) {
+                              int epi, int ksplit, const float* rs, hipStream_t s) {
     if (epi == EPI_RESIDUAL && !R) return hipErrorInvalidValue;
+    if (ksplit < 1 || (ksplit > 1 && epi != EPI_STORE_F32)) return hipErrorInvalidValue;
     const int tiles_m = (M + G::BM - 1) / G::BM, tiles_n = (N + G::BN - 1) / G::BN;
     const long long n_tiles = (long long)tiles_m * tiles_n;
-    if (n_tiles > (1ll << 27) || K % (64 * G::SL) != 0) return hipErrorInvalidValue;
+    if (n_tiles * ksplit > (1ll << 27) || K % (64 * G::SL * ksplit) != 0) return hipErrorInvalidValue;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)gemm_tile_kernel<G>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const int per_xcd = (int)((n_tiles + 7) / 8);
-    gemm_tile_kernel<G><<<8 * per_xcd, 64 * G::NW, G::LDS, s>>>(A, lda, Wt, C, ldc, R, M, N, K, epi, tiles_m, (int)n_tiles, per_xcd, rs);
+    const int per_xcd = (int)((n_tiles * ksplit + 7) / 8);
+    gemm_tile_kernel<G><<<8 * per_xcd, 64 * G::NW, G::LDS, s>>>(A, lda, Wt, C, ldc, R, M, N, K, epi, tiles_m, (int)n_tiles, ksplit,
+                                                                per_xcd, rs);
     return hipGetLastError();
 }
 
@@ -331,11 +338,43 @@ float gemm_tile_estimate(int M, int N, int K, int n_cus, int* pick) {
     return best;
 }
 
+// Tile and ranges of K for a product whose ranges meet in memory: a compute unit loads token and weight lines at one rate
+// whatever they are for (1.07 ns a line out of the L2, and the XCD another 0.13 ns for each that the L2 has not), and four ranges
+// of tiles of twice the height and width have half the lines of one range.  Worth it for long contractions of narrow outputs:
+// 4.4 us + 1.54 / 2.49 ns a token / weight line and slice (or the products, as above) + 2.4 us and 2.2 TB/s for the partial
+// sums on their way out and in; fitted to 782 launches of 17 products at 80 to 1536 rows, 7 % off (12 % over unsplit ones).  One
+// round of tiles, eight slices a range or more.  `*now` is the same estimate for tile `pick_now` unsplit.
+float gemm_tile_split_estimate(int M, int N, int K, int n_cus, size_t ws_bytes, int pick_now, float* now, int* pick, int* split) {
+    float best = 0.f;
+    *pick = -1;
+    *split = 1;
+    *now = 0.f;
+    int at = 0;
+#define X(BM, BN, WM, WN, KG, SL, NS)                                                                                       \
+    {                                                                                                                       \
+        const long long tiles = (long long)((M + BM - 1) / BM) * ((N + BN - 1) / BN);                                       \
+        const float lines = (BN == 32 && BM == 96 && M <= BM ? 2.4f : 1.54f) * BM + 2.49f * BN, mul = 0.95f * (KG == 1 ? 0.0276f : 0.024f) * BM * BN; \
+        const float slice = (lines > mul ? lines : mul) * 1e-3f;                                                            \
+        const float rounds = (float)((tiles + n_cus - 1) / n_cus);                                                          \
+        if (at == pick_now) *now = 4.4f + 8.f * (rounds - 1.f) + rounds * (K / 64) * slice;                                 \
+        for (int s = 2; s <= 8; s *= 2) {                                                                                   \
+            const size_t bytes = (size_t)s * M * N * sizeof(float);                                                         \
+            if (K % (64 * SL * s) != 0 || K / 64 / s < 8 || tiles * s > n_cus || bytes > ws_bytes) continue;                \
+            const float us = 6.8f + (K / 64 / s) * slice + (float)bytes / 2.2e6f;                                           \
+            if (*pick < 0 || us < best) { best = us; *pick = at; *split = s; }                                              \
+        }                                                                                                                   \
+        ++at;                                                                                                               \
+    }
+    SS_TILES(X)
+#undef X
+    return best;
+}
+
 hipError_t gemm_tile(int pick, const bf16_t* A, int lda, const bf16_t* Wt, void* C, int ldc, const bf16_t* R, int M, int N, int K,
-                     int epi, const float* rs, hipStream_t s) {
+                     int epi, int ksplit, const float* rs, hipStream_t s) {
     int at = 0;
 #define X(BM, BN, WM, WN, KG, SL, NS) \
-    if (pick == at++) return launch_tile<TileCfg<BM, BN, WM, WN, KG, SL, NS>>(A, lda, Wt, C, ldc, R, M, N, K, epi, rs, s);
+    if (pick == at++) return launch_tile<TileCfg<BM, BN, WM, WN, KG, SL, NS>>(A, lda, Wt, C, ldc, R, M, N, K, epi, ksplit, rs, s);
     SS_TILES(X)
 #undef X
     return hipErrorInvalidValue;

@@ -1,5 +1,6 @@
-"""Products whose K ranges meet in memory: the kernel that sums them eight columns a thread, where the last of its blocks is
-partly empty, through the MLP phase of a layer and against the CPU oracle."""
+"""Products whose K ranges meet in memory: tiles over ranges of K, ragged in rows and columns, and the kernel that sums the
+ranges eight columns a thread, where the last of its blocks is partly empty; through the MLP phase of a layer and against the
+CPU oracle.  (test_product_routes.py checks that these products are cut as said here.)"""
 import pytest
 import torch
 
@@ -16,6 +17,10 @@ if torch.cuda.is_available():
 @pytest.mark.parametrize("dtype,T,hidden,ffn", [
     (wl.BF16, 261, 12288, 1056),       # gate / up in eight ranges: 261 x 132 pieces, 134.6 blocks
     (wl.F16, 97, 1096, 12800),         # down in eight ranges, with and without a residual: 97 x 137 pieces, 51.9 blocks
+    (wl.BF16, 81, 8192, 640),          # tiles of the gate / up product in eight ranges
+    (wl.F16, 141, 1096, 12288),        # ... of the down projection in eight, the last ones wider than what is left of the output
+    (wl.BF16, 333, 2088, 8192),        # ... in four
+    (wl.BF16, 120, 5120, 1056),        # ... of the gate / up product in eight ranges of ten slices
 ])
 def test_summed_ranges_match_oracle(dtype, T, hidden, ffn):
     cfg = wl.ModelCfg(hidden=hidden, n_q_heads=1, n_kv_heads=1, head_dim=64, ffn=ffn, n_layers=1, dtype=dtype)

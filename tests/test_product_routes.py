@@ -90,6 +90,19 @@ def test_products_take_the_kernel_that_was_faster(rows, n, k, epi, kernel, split
     assert (got[0], got[2]) == (kernel, split)
 
 
+@pytest.mark.parametrize("rows,n,k,epi,split", [
+    (81, 1280, 8192, EPI_SWIGLU, 8), (141, 1096, 12288, EPI_RESIDUAL, 8), (333, 2088, 8192, EPI_STORE, 4), (120, 2112, 5120, EPI_SWIGLU, 8),
+    (333, 4096, 11008, EPI_RESIDUAL, 4), (1000, 1280, 8192, EPI_STORE, 4), (864, 1280, 8192, EPI_STORE, 4), (170, 8192, 8192, EPI_RESIDUAL, 4),
+    # unsplit: shorter contractions, fewer rows, heads
+    (129, 5120, 5120, EPI_RESIDUAL, 1), (200, 3072, 4096, EPI_STORE, 1), (111, 5120, 5120, EPI_RESIDUAL, 1), (111, 8192, 8192, EPI_RESIDUAL, 1),
+    (81, 1280, 8192, EPI_STORE_F32, 1),
+])
+def test_tiles_over_ranges_of_long_contractions(rows, n, k, epi, split):
+    kernel, _, got = plan(rows, n, k, epi)
+    assert (kernel, got) == (TILE, split)
+    assert plan(rows, n, k, epi, ws=0)[2] == 1                    # nowhere to put the sums
+
+
 def stream_columns(rows, n, k, cus=256):
     f = C.CDLL(_library()).ssk_gemm_stream_columns
     f.argtypes = [C.c_int] * 4 + [C.POINTER(C.c_int)]
