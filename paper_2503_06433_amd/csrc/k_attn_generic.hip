@@ -105,60 +105,91 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
     const int tok = lane >> 2, sub = lane & 3;
     float q[DS], acc[DR];
     const T* row = qkv + (size_t)q_begin * ((size_t)(n_q + 2 * n_kv) * D);
-    // this lane's quarter of a head of the new token; rotated (and rounded as stored) where the batch comes unrotated
-    auto quarter = [&](const T* head, float* f) {
+    const int32_t* pt = bm.page_tables + (size_t)sq * bm.pt_stride;
+    const size_t page_elems = (size_t)n_kv * PS * D;
+    vec16 kr[DS / EV], vr[DR][PS / EV];
+    auto load_page = [&](int j) {
+        const size_t page = (size_t)pt[j] * page_elems + (size_t)g * PS * D;
 #pragma unroll
-        for (int i = 0; i < DS / EV; ++i) unpack16<T>(*reinterpret_cast<const vec16*>(head + sub * DS + i * EV), f + i * EV);
-        if (!rope) return;
-        const float* cs = rope + (size_t)p * D + 2 * (sub & 1) * DS;
+        for (int i = 0; i < DS / EV; ++i) kr[i] = *reinterpret_cast<const vec16*>(k_pool + page + tok * D + sub * DS + i * EV);
+#pragma unroll
+        for (int r = 0; r < DR; ++r)
+#pragma unroll
+            for (int i = 0; i < PS / EV; ++i) vr[r][i] = *reinterpret_cast<const vec16*>(v_pool + page + (r * 64 + lane) * PS + i * EV);
+    };
+    // Everything that does not depend on something loaded is requested together: a lane's quarter of the new token's q and (the
+    // wave that has the new token's page) k, the quarters they are rotated with, cos / sin, the new value, the first page.
+    const bool last_here = rope && (n_pages - 1) % 4 == wave;
+    const T *qh = row + (size_t)a * D, *kh = row + (size_t)(n_q + g) * D, *vh = kh + (size_t)n_kv * D;
+    vec16 q_own[DS / EV], q_other[DS / EV], k_own[DS / EV], k_other[DS / EV];
+    T v_new[DR];
+    float cs[2 * DS];
+#pragma unroll
+    for (int i = 0; i < DS / EV; ++i) q_own[i] = *reinterpret_cast<const vec16*>(qh + sub * DS + i * EV);
+    if (rope) {
+#pragma unroll
+        for (int i = 0; i < DS / EV; ++i) q_other[i] = *reinterpret_cast<const vec16*>(qh + (sub ^ 2) * DS + i * EV);
+#pragma unroll
+        for (int i = 0; i < DS / 2; ++i)
+            unpack16<float>(*reinterpret_cast<const vec16*>(rope + (size_t)p * D + 2 * (sub & 1) * DS + 4 * i), cs + 4 * i);
+    }
+    if (last_here) {
+#pragma unroll
+        for (int i = 0; i < DS / EV; ++i) {
+            k_own[i] = *reinterpret_cast<const vec16*>(kh + sub * DS + i * EV);
+            k_other[i] = *reinterpret_cast<const vec16*>(kh + (sub ^ 2) * DS + i * EV);
+        }
+#pragma unroll
+        for (int r = 0; r < DR; ++r) v_new[r] = vh[r * 64 + lane];
+    }
+    if (wave < n_pages) load_page(wave);
+    // rotated, rounded as stored
+    auto rotate = [&](const vec16* own, const vec16* other, float* f) {
 #pragma unroll
         for (int i = 0; i < DS / EV; ++i) {
             float o[EV];
-            unpack16<T>(*reinterpret_cast<const vec16*>(head + (sub ^ 2) * DS + i * EV), o);
+            unpack16<T>(own[i], f + i * EV);
+            unpack16<T>(other[i], o);
 #pragma unroll
             for (int e = 0; e < EV; ++e) {
-                float r[2], own = f[i * EV + e];
+                float r[2], mine = f[i * EV + e];
                 const float c = cs[2 * (i * EV + e)], sn = cs[2 * (i * EV + e) + 1];
-                if (sub < 2) rope_rotate(own, o[e], c, sn, r[0], r[1]);
-                else rope_rotate(o[e], own, c, sn, r[1], r[0]);
+                if (sub < 2) rope_rotate(mine, o[e], c, sn, r[0], r[1]);
+                else rope_rotate(o[e], mine, c, sn, r[1], r[0]);
                 T st;
                 stf(&st, r[0]);
                 f[i * EV + e] = ldf(&st);
             }
         }
     };
-    quarter(row + (size_t)a * D, q);
+    if (rope) {
+        rotate(q_own, q_other, q);
+    } else {
+#pragma unroll
+        for (int i = 0; i < DS / EV; ++i) unpack16<T>(q_own[i], q + i * EV);
+    }
 #pragma unroll
     for (int e = 0; e < DS; ++e) q[e] *= scale;
+    const int slot = p % PS;
+    if (last_here) {
+        float kn[DS];
+        rotate(k_own, k_other, kn);
+#pragma unroll
+        for (int i = 0; i < DS / EV; ++i) k_own[i] = pack16<T>(kn + i * EV);
+    }
 #pragma unroll
     for (int r = 0; r < DR; ++r) acc[r] = 0.f;
     float m = -INFINITY, l = 0.f;
-    const int32_t* pt = bm.page_tables + (size_t)sq * bm.pt_stride;
-    const size_t page_elems = (size_t)n_kv * PS * D;
     for (int j = wave; j < n_pages; j += 4) {
-        const T* kp = k_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D + tok * D + sub * DS;
-        const T* vp = v_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D + lane * PS;
-        vec16 kr[DS / EV], vr[DR][PS / EV];
-#pragma unroll
-        for (int i = 0; i < DS / EV; ++i) kr[i] = *reinterpret_cast<const vec16*>(kp + i * EV);
-#pragma unroll
-        for (int r = 0; r < DR; ++r)
-#pragma unroll
-            for (int i = 0; i < PS / EV; ++i) vr[r][i] = *reinterpret_cast<const vec16*>(vp + r * 64 * PS + i * EV);
         // The new token's key and value come from the products, for every head of the group; the first head's block writes
         // them into the page.
-        const bool fresh = rope && j == n_pages - 1;
-        const int slot = p % PS;
-        if (fresh) {
-            if (tok == slot) {
-                float kn[DS];
-                quarter(row + (size_t)(n_q + g) * D, kn);
+        const bool fresh = last_here && j == n_pages - 1;
+        if (fresh && tok == slot) {
 #pragma unroll
-                for (int i = 0; i < DS / EV; ++i) {
-                    kr[i] = pack16<T>(kn + i * EV);
-                    if (a % (n_q / n_kv) == 0)
-                        *reinterpret_cast<vec16*>(k_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D + tok * D + sub * DS + i * EV) = kr[i];
-                }
+            for (int i = 0; i < DS / EV; ++i) {
+                kr[i] = k_own[i];
+                if (a % (n_q / n_kv) == 0)
+                    *reinterpret_cast<vec16*>(k_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D + tok * D + sub * DS + i * EV) = kr[i];
             }
         }
         float d = 0.f;
@@ -187,15 +218,15 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
             for (int i = 0; i < PS / EV; ++i) unpack16<T>(vr[r][i], v + i * EV);
             if (fresh) {
                 const int e = r * 64 + lane, at = vpos(slot, e);
-                const T vn = row[(size_t)(n_q + n_kv + g) * D + e];
 #pragma unroll
-                for (int t = 0; t < PS; ++t) v[t] = t == at ? ldf(&vn) : v[t];
-                if (a % (n_q / n_kv) == 0) v_pool[(size_t)pt[j] * page_elems + (size_t)g * PS * D + e * PS + at] = vn;
+                for (int t = 0; t < PS; ++t) v[t] = t == at ? ldf(&v_new[r]) : v[t];
+                if (a % (n_q / n_kv) == 0) v_pool[(size_t)pt[j] * page_elems + (size_t)g * PS * D + e * PS + at] = v_new[r];
             }
 #pragma unroll
             for (int t = 0; t < PS; ++t) sum = fmaf(__shfl(w, 4 * vtok(t, lane), 64), v[t], sum);   // rows lane, lane + 64: one order
             acc[r] = sum;
         }
+        if (j + 4 < n_pages) load_page(j + 4);
     }
 #pragma unroll
     for (int o = 4; o < 64; o <<= 1) l += __shfl_xor(l, o, 64);

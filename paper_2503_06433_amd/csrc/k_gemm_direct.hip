@@ -73,18 +73,32 @@ template <> __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, const floa
     *reinterpret_cast<uint2*>(p) = w;
 }
 
+// 16 bytes of scaled activations, rounded to nearest (pack16 tests every value for NaN: 4 us more in the head below)
+template <typename T> __device__ __forceinline__ u32x4_t pack_row(const float* x);
+template <> __device__ __forceinline__ u32x4_t pack_row<float>(const float* x) { return __builtin_bit_cast(u32x4_t, pack16<float>(x)); }
+template <> __device__ __forceinline__ u32x4_t pack_row<bf16_t>(const float* x) {
+    return u32x4_t{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
+}
+
 }  // namespace
 
+constexpr int EPI_HEAD = 100;      // internal: EPI_STORE_F32 of rows that are scaled by `gain`, column by column, on their way in
+
+// EPI_HEAD: final norm and LM head in one launch.  The rows meet their gains in registers, in the order they are loaded in, and
+// are rounded once to the storage type like the separate norm's result, but before the row's factor instead of behind it; the
+// sums of squares come from the unscaled values there (a row's 128-byte chunk lies in eight neighbouring lanes).  Eight
+// rows, 2048 x 4096: TODO
+//
 // SwiGLU: a tile is 8 gate rows and the 8 up rows that belong to them, so a block of NT tiles has 8 NT output columns.
 // Gate rows come in blocks of gate_blk, each followed by its up rows (gate_blk = N / 2: all gate rows first).
 template <typename T, int MT, int NT, int W, int DEPTH, int EPI>
 __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict__ A, int lda, const T* __restrict__ Wt,
                                                              void* __restrict__ Cv, int ldc, const T* __restrict__ R,
                                                              int M, int N, int K, int gate_blk, int divide,
-                                                             float norm_eps, int vec_ok) {
+                                                             float norm_eps, const T* __restrict__ gain, int vec_ok) {
     constexpr int CH = DirectOp<T>::CH;
     constexpr int EV = VecOf<T>::N;
-    constexpr bool SWI = EPI == EPI_SWIGLU;
+    constexpr bool SWI = EPI == EPI_SWIGLU, HEAD = EPI == EPI_HEAD;
     constexpr int TO = SWI ? 8 : 16;                                         // output columns of a tile
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);                         // [W][NT * MT][64]
@@ -144,9 +158,14 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
 
     // chunks of this wave: wave, wave + W, ...; the pieces of the last one that lie beyond K count as zeros
     const int nch = (K + CH - 1) / CH;
-    struct Buf { u32x4_t w[NT][2], x[MT][2]; } buf[DEPTH];
+    struct Buf { u32x4_t w[NT][2], x[MT][2], g[HEAD ? 1 : 0]; } buf[DEPTH];
+    float xx[HEAD ? MT : 1][2];
+    if constexpr (HEAD)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) xx[i][0] = xx[i][1] = 0.f;
     auto load_full = [&](int d, int c) {
         const size_t k0 = (size_t)c * CH + sp * EV;
+        if constexpr (HEAD) buf[d].g[0] = *reinterpret_cast<const u32x4_t*>(gain + k0);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
@@ -159,6 +178,10 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
         const u32x4_t z = {0u, 0u, 0u, 0u};
         const bool in = (long long)c * CH + sp * EV < K;
         const size_t k0 = in ? (size_t)c * CH + sp * EV : 0;                 // some piece of the row, dropped below
+        if constexpr (HEAD) {
+            const u32x4_t v = *reinterpret_cast<const u32x4_t*>(gain + k0);
+            buf[d].g[0] = in ? v : z;
+        }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
@@ -175,6 +198,24 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
     };
     // through the transposer into operand order (a wave's LDS operations execute in order: no barrier)
     auto multiply = [&](int d) {
+        if constexpr (HEAD) {
+            float g[EV];
+            unpack16<T>(__builtin_bit_cast(vec16, buf[d].g[0]), g);
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (m0 + 16 * i + 8 * h >= M) continue;                  // repeated rows
+                    float x[EV];
+                    unpack16<T>(__builtin_bit_cast(vec16, buf[d].x[i][h]), x);
+#pragma unroll
+                    for (int e = 0; e < EV; ++e) {
+                        xx[i][h] = fmaf(x[e], x[e], xx[i][h]);
+                        x[e] *= g[e];
+                    }
+                    buf[d].x[i][h] = pack_row<T>(x);
+                }
+        }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
@@ -194,7 +235,7 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
         for (int i = 0; i < MT; ++i) {
 #pragma unroll
             for (int j = 0; j < NT; ++j) acc[j][i] = DirectOp<T>::mul(wf[j], xf[i], acc[j][i]);
-            if (norm) gram[i] = DirectOp<T>::mul(xf[i], xf[i], gram[i]);
+            if (!HEAD && norm) gram[i] = DirectOp<T>::mul(xf[i], xf[i], gram[i]);
         }
     };
     // whole rounds of DEPTH chunks that lie inside K run a round ahead without a test; what is left (fewer than DEPTH
@@ -233,7 +274,17 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
     for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int i = 0; i < MT; ++i) red[(wave * (NT * MT) + j * MT + i) * 64 + lane] = acc[j][i];
-    if (norm) {
+    if constexpr (HEAD) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float v = xx[i][h];
+#pragma unroll
+                for (int o = 1; o < 8; o <<= 1) v += __shfl_xor(v, o, 64);
+                if (sp == 0) sq[wave * (MT * 16) + i * 16 + 8 * h + sr] = v;
+            }
+    } else if (norm) {
         const int v = lr - 4 * lg;                                           // register that holds the diagonal
 #pragma unroll
         for (int i = 0; i < MT; ++i)
@@ -272,7 +323,7 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
         const int cols = n_out - col < 4 ? n_out - col : 4;
         if (EPI == EPI_RESIDUAL)
             for (int e = 0; e < cols; ++e) o[e] += ldf(R + off + e);
-        if (EPI == EPI_STORE_F32) {
+        if (EPI == EPI_STORE_F32 || HEAD) {
             float* C = reinterpret_cast<float*>(Cv);
             if (vec_ok && cols == 4) store4<float>(C + off, o);
             else for (int e = 0; e < cols; ++e) C[off + e] = o[e];
@@ -286,7 +337,7 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
 
 template <typename T, int MT, int NT, int W, int DEPTH>
 static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
-                                int epi, int gate_blk, int divide, float norm_eps, hipStream_t s) {
+                                int epi, int gate_blk, int divide, float norm_eps, const void* gain, hipStream_t s) {
     const int n_out = epi == EPI_SWIGLU ? N / 2 : N, per = (epi == EPI_SWIGLU ? 8 : 16) * NT;
     const dim3 grid((unsigned)((n_out + per - 1) / per), (unsigned)((M + 16 * MT - 1) / (16 * MT)));
     if (grid.y > 65535) return hipErrorInvalidValue;
@@ -308,14 +359,16 @@ static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C,
                 attr_set = true;                                                                                \
             }                                                                                                   \
         }                                                                                                       \
-        kfn<<<grid, 64 * W, LDS, s>>>(a, lda, w, C, ldc, r, M, N, K, gate_blk, divide, norm_eps, vec_ok);       \
+        kfn<<<grid, 64 * W, LDS, s>>>(a, lda, w, C, ldc, r, M, N, K, gate_blk, divide, norm_eps, (const T*)gain, vec_ok); \
     }
     switch (epi) {
         case EPI_STORE: SS_GO(EPI_STORE) break;
         case EPI_RESIDUAL:
             if (!R) return hipErrorInvalidValue;
             SS_GO(EPI_RESIDUAL) break;
-        case EPI_STORE_F32: SS_GO(EPI_STORE_F32) break;
+        case EPI_STORE_F32:
+            if (gain) SS_GO(EPI_HEAD) else SS_GO(EPI_STORE_F32)
+            break;
         case EPI_SWIGLU: SS_GO(EPI_SWIGLU) break;
         default: return hipErrorInvalidValue;
     }
@@ -371,22 +424,23 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
 // are too short: 50257 x 768 27 us, 18 by the rule; 32001 x 1024 21 and 14; 8192 x 1024 7.1 and 5.8.
 template <typename T, int MT>
 static hipError_t pick_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
-                              int epi, int gate_blk, int divide, float norm_eps, hipStream_t s) {
+                              int epi, int gate_blk, int divide, float norm_eps, const void* gain, hipStream_t s) {
     if constexpr (MT == 1)
-        if (M <= 8 && sizeof(T) == 2 && K >= 2048) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
+        if (M <= 8 && sizeof(T) == 2 && K >= 2048) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s);
     const long long tiles = (long long)((N + 15) / 16) * ((M + 16 * MT - 1) / (16 * MT));
-    if (tiles <= 256) return launch_direct<T, MT, 1, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
-    if (tiles <= 512) return launch_direct<T, MT, 2, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
-    return launch_direct<T, MT, 3, 8, 1>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s);
+    if (tiles <= 256) return launch_direct<T, MT, 1, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s);
+    if (tiles <= 512) return launch_direct<T, MT, 2, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s);
+    return launch_direct<T, MT, 3, 8, 1>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s);
 }
 
 hipError_t gemm_direct(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
-                       int epi, float norm_eps, hipStream_t s) {
+                       int epi, float norm_eps, const void* gain, hipStream_t s) {
     if (!gemm_direct_takes(dt, A, Wt, M, N, K, lda, epi)) return hipErrorInvalidValue;
+    if (gain && (epi != EPI_STORE_F32 || norm_eps < 0.f || ((uintptr_t)gain & 15) != 0)) return hipErrorInvalidValue;
     const int gate_blk = epi == EPI_SWIGLU ? 32 : N / 2;
     const int divide = epi == EPI_SWIGLU_HALVES;
     if (divide) epi = EPI_SWIGLU;
-#define SS_GO(TT, MT) return pick_direct<TT, MT>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, s)
+#define SS_GO(TT, MT) return pick_direct<TT, MT>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s)
 #ifndef SS_HALF_F16          // fp32 is the same code in both builds of this file: only the first has it
     if (dt == F32) {
         if (M <= 16) SS_GO(float, 1);

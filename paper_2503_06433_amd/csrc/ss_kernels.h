@@ -135,6 +135,12 @@ hipError_t gemm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int 
                    hipStream_t s, float* ws = nullptr, size_t ws_bytes = 0, int max_rounds = 0,
                    const float* row_scale = nullptr, float norm_eps = -1.0f);
 
+// Final norm and LM head in one: C (fp32) = norm(A) * gain * Wt^T, gain of K values of the model dtype.  Only where
+// head_norms_itself says so (few rows), refused elsewhere.
+bool head_norms_itself(int dt, const void* A, int lda, const void* Wt, const void* gain, int M, int N, int K, bool force_generic);
+hipError_t head_nt(int dt, const void* A, int lda, const void* Wt, float* C, int ldc, int M, int N, int K, float norm_eps,
+                   const void* gain, hipStream_t s);
+
 // out[t,:] = x[t,:] * rsqrt(mean(x[t,:]^2) + eps) * g
 hipError_t rmsnorm(int dt, const void* x, const void* g, void* out, int T, int H, float eps,
                    hipStream_t s);

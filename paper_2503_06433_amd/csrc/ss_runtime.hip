@@ -2289,12 +2289,22 @@ int ss_embed(ss_ctx* c, const int32_t* ids, int n, void* x_out, void* stream) {
     return SS_OK;
 }
 
+// The final norm inside the head's product, where the product's kernel does it (few rows, or fp32): *done.
+static int head_with_norm(ss_ctx* c, const void* x, int n, float* logits, hipStream_t st, bool* done) {
+    const int H = c->m.hidden, V = c->m.vocab;
+    *done = c->m.rms_eps >= 0.f && SSK_CALL(c, head_norms_itself, x, H, c->d_wlm_t, c->d_gf, n, V, H, c->force_generic);
+    if (*done) K_TRY(c, SSK_CALL(c, head_nt, x, H, c->d_wlm_t, logits, V, n, V, H, c->m.rms_eps, c->d_gf, st));
+    return SS_OK;
+}
+
 int ss_lm_head(ss_ctx* c, const void* x, int n, float* logits, void* stream) {
     if (!c || !x || !logits || n <= 0) return SS_EINVAL;
     if (!c->d_wlm_t) return fail(c, SS_EINVAL, "head weights not loaded");
     hipStream_t st = (hipStream_t)stream;
-    int rc = ensure_buf(c, c->ws_h, (size_t)n * c->m.hidden * c->es);
+    int rc = ensure_buf(c, c->ws_h, (size_t)n * c->m.hidden * c->es);      // whichever route: a captured call of another alignment does not allocate
     if (rc) return rc;
+    bool done = false;
+    if ((rc = head_with_norm(c, x, n, logits, st, &done)) || done) return rc;
     K_TRY(c, SSK_CALL(c, rmsnorm, x, c->d_gf, c->ws_h.p, n, c->m.hidden, c->m.rms_eps, st));
     K_TRY(c, SSK_CALL(c, gemm_nt, c->ws_h.p, c->m.hidden, c->d_wlm_t, logits, c->m.vocab, nullptr, n, c->m.vocab,
                           c->m.hidden, ssk::EPI_STORE_F32, c->force_generic, st, (float*)c->ws_splitk.p, c->ws_splitk.cap));
@@ -2311,6 +2321,8 @@ int ss_lm_head_noalloc(ss_ctx* c, const void* x, int n, float* logits, void* str
         return fail(c, SS_EINVAL, "ss_lm_head_noalloc: %d rows of %d elements need %zu bytes of scratch, the fixed limit is %zu",
                     n, c->m.hidden, rows_bytes, NOALLOC_ROWS_BYTES);
     hipStream_t st = (hipStream_t)stream;
+    bool done = false;
+    if (int e = head_with_norm(c, x, n, logits, st, &done); e || done) return e;
     void* rows = base;
     float* partials = (float*)(base + NOALLOC_ROWS_BYTES);
     const size_t partial_bytes = NOALLOC_SCRATCH_BYTES - NOALLOC_ROWS_BYTES;
