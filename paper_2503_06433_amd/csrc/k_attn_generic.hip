@@ -152,12 +152,10 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
             unpack16<T>(other[i], o);
 #pragma unroll
             for (int e = 0; e < EV; ++e) {
-                float r[2], mine = f[i * EV + e];
-                const float c = cs[2 * (i * EV + e)], sn = cs[2 * (i * EV + e) + 1];
-                if (sub < 2) rope_rotate(mine, o[e], c, sn, r[0], r[1]);
-                else rope_rotate(o[e], mine, c, sn, r[1], r[0]);
+                // rope_rotate's half that this lane has: the first quarters subtract the other half, the last add it
+                const float other = sub < 2 ? -o[e] : o[e];
                 T st;
-                stf(&st, r[0]);
+                stf(&st, fmaf(f[i * EV + e], cs[2 * (i * EV + e)], other * cs[2 * (i * EV + e) + 1]));
                 f[i * EV + e] = ldf(&st);
             }
         }

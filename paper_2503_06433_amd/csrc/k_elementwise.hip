@@ -1,6 +1,8 @@
 // RMSNorm, SwiGLU (unfused form), embedding gather, rotary embedding + KV page
 // write, and the load-time weight slicing.  All of these are HBM-bound
 // element-wise passes: one wave-coalesced read and write per element.
+#include <algorithm>
+
 #include "ss_device.h"
 #include "ss_kernels.h"
 
@@ -68,12 +70,20 @@ hipError_t rmsnorm(int dt, const void* x, const void* g, void* out, int T, int H
 // (norm(x) W = r * (x (g W))), so the normalised activations are never written.  One read of x, T floats out.
 // WPR waves per row, up to four 16-byte loads of a lane on their way at once: at decode sizes the launch is a chain of memory
 // latencies (256 rows of 4096: one wave per row and one load at a time 6.5 us, four loads 4.7; 1024 rows of 8192: 10.7 and 4.9).
+// The first up_blocks blocks take a batch's metadata along (UploadJob): a launch of its own, on the compute stream as well, is 4 to
+// 8 us in front of this one, 29 for the megabyte of 1024 sequences (a kernel and not the copy engine, which costs two
+// hand-overs between queues).
 template <typename T, int WPR>
 __global__ __launch_bounds__(256) void row_scale_kernel(const T* __restrict__ x, float* __restrict__ r, int n_rows, int H,
-                                                        float eps) {
+                                                        float eps, int up_blocks, const vec16* __restrict__ up_src,
+                                                        vec16* __restrict__ up_dst, int64_t up_n) {
     constexpr int V = VecOf<T>::N, STEP = 64 * WPR * V;
+    if ((int)blockIdx.x < up_blocks) {
+        upload_pieces(up_src, up_dst, up_n, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)up_blocks * 256);
+        return;
+    }
     const int wave = threadIdx.x >> 6;
-    const int t = blockIdx.x * (4 / WPR) + wave / WPR;
+    const int t = (blockIdx.x - up_blocks) * (4 / WPR) + wave / WPR;
     if (t >= n_rows) return;
     const int tid = (wave % WPR) * 64 + (threadIdx.x & 63);      // thread of the row
     const T* row = x + (size_t)t * H;
@@ -115,14 +125,15 @@ __global__ __launch_bounds__(256) void row_scale_kernel(const T* __restrict__ x,
     if (tid == 0) r[t] = 1.0f / sqrtf(ss / (float)H + eps);
 }
 
-hipError_t row_scale(int dt, const void* x, float* r, int T, int H, float eps, hipStream_t s) {
-    if (T <= 0) return hipSuccess;
-    if (H <= 0) return hipErrorInvalidValue;
+hipError_t row_scale(int dt, const void* x, float* r, int T, int H, float eps, hipStream_t s, const UploadJob& job) {
+    if (T <= 0) return job.n16 ? hipErrorInvalidValue : hipSuccess;
+    if (H <= 0 || job.n16 < 0 || (((uintptr_t)job.src | (uintptr_t)job.dst) & 15) != 0) return hipErrorInvalidValue;
     // A block per row up to 2048 rows (eight blocks per compute unit), beyond that one wave per row fills the chip.  In a chain of
     // layers the block is 0.1 us a launch faster at 100 to 1000 rows of 4096 and 0.35 at 2000, the wave 0.3 at 2600 and 0.8 at 4000.
     const bool few = T <= 2048;
-    const unsigned grid = few ? (unsigned)T : (unsigned)((T + 3) / 4);
-#define SS_GO(TT, WPR) row_scale_kernel<TT, WPR><<<grid, 256, 0, s>>>((const TT*)x, r, T, H, eps)
+    const int up = (int)std::min<int64_t>((job.n16 + 255) / 256, 1024);
+    const unsigned grid = (unsigned)up + (few ? (unsigned)T : (unsigned)((T + 3) / 4));
+#define SS_GO(TT, WPR) row_scale_kernel<TT, WPR><<<grid, 256, 0, s>>>((const TT*)x, r, T, H, eps, up, (const vec16*)job.src, (vec16*)job.dst, job.n16)
     if (dt == F32) { if (few) SS_GO(float, 4); else SS_GO(float, 1); }
     else { if (few) SS_GO(bf16_t, 4); else SS_GO(bf16_t, 1); }
 #undef SS_GO
@@ -202,9 +213,8 @@ hipError_t embed_ids(int dt, const void* table, const int32_t* ids, void* out, i
 }
 
 // ---------------------------------------------------------------- batch metadata to the device
-// Page-locked host memory -> device memory, 16 bytes per lane straight over the link.  Bound by the link for a megabyte
-// (1024 sequences: a decode step 638 us with the copy engine, 541 with this), by its latency for a few kilobytes (the
-// layer call of one prompt of 333 tokens 248 -> 234 us).
+// Page-locked host memory -> device memory, 16 bytes per lane straight over the link (page lists of the device-side export /
+// import; the metadata of a batch rides in the first launch of its attention phase).
 __global__ __launch_bounds__(256) void upload_kernel(const vec16* __restrict__ src, vec16* __restrict__ dst, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) dst[i] = src[i];

@@ -20,6 +20,8 @@
 //
 // The product is formed transposed (weights as the row operand): accumulator register v of lane l is
 // column 4 * (l / 16) + v of token l % 16, four consecutive output columns per lane.
+#include <algorithm>
+
 #include "ss_device.h"
 #include "ss_kernels.h"
 
@@ -95,7 +97,8 @@ template <typename T, int MT, int NT, int W, int DEPTH, int EPI>
 __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict__ A, int lda, const T* __restrict__ Wt,
                                                              void* __restrict__ Cv, int ldc, const T* __restrict__ R,
                                                              int M, int N, int K, int gate_blk, int divide,
-                                                             float norm_eps, const T* __restrict__ gain, int vec_ok) {
+                                                             float norm_eps, const T* __restrict__ gain, int vec_ok, int up_blocks,
+                                                             const vec16* __restrict__ up_src, vec16* __restrict__ up_dst, int64_t up_n) {
     constexpr int CH = DirectOp<T>::CH;
     constexpr int EV = VecOf<T>::N;
     constexpr bool SWI = EPI == EPI_SWIGLU, HEAD = EPI == EPI_HEAD;
@@ -106,9 +109,19 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lr = lane & 15, lg = lane >> 4;
+    // Plain products (the QKV projection): the first blocks of the first row of blocks take a batch's metadata along (UploadJob).
+    // Only there: the test alone, in front of the first loads, costs every launch 0.2 to 0.5 us.
+    int bx = blockIdx.x;
+    if constexpr (EPI == EPI_STORE) {
+        if (bx < up_blocks) {
+            if (blockIdx.y == 0) upload_pieces(up_src, up_dst, up_n, (int64_t)bx * (64 * W) + threadIdx.x, (int64_t)up_blocks * (64 * W));
+            return;
+        }
+        bx -= up_blocks;
+    }
     const int m0 = blockIdx.y * (16 * MT);
     const int n_out = SWI ? N / 2 : N;
-    const int o0 = blockIdx.x * (TO * NT);                                   // first output column of the block
+    const int o0 = bx * (TO * NT);                                           // first output column of the block
     const bool norm = norm_eps >= 0.f;
 
     // Loads cover whole 128-byte lines with neighbouring lanes: load h of a tile brings rows 8h .. 8h + 7, lane l row
@@ -337,9 +350,11 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
 
 template <typename T, int MT, int NT, int W, int DEPTH>
 static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
-                                int epi, int gate_blk, int divide, float norm_eps, const void* gain, hipStream_t s) {
+                                int epi, int gate_blk, int divide, float norm_eps, const void* gain, const UploadJob& job, hipStream_t s) {
     const int n_out = epi == EPI_SWIGLU ? N / 2 : N, per = (epi == EPI_SWIGLU ? 8 : 16) * NT;
-    const dim3 grid((unsigned)((n_out + per - 1) / per), (unsigned)((M + 16 * MT - 1) / (16 * MT)));
+    // four pieces a thread: the batches of few rows bring a few kilobytes, at most some hundred
+    const int up = (int)std::min<int64_t>((job.n16 + 256 * W - 1) / (256 * W), 64);
+    const dim3 grid((unsigned)((n_out + per - 1) / per + up), (unsigned)((M + 16 * MT - 1) / (16 * MT)));
     if (grid.y > 65535) return hipErrorInvalidValue;
     constexpr size_t LDS_TR = (size_t)W * (NT + MT) * 2048, LDS_RED = (size_t)W * NT * MT * 1024 + (size_t)W * MT * 64;
     constexpr size_t LDS = LDS_TR > LDS_RED ? LDS_TR : LDS_RED;
@@ -359,7 +374,8 @@ static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C,
                 attr_set = true;                                                                                \
             }                                                                                                   \
         }                                                                                                       \
-        kfn<<<grid, 64 * W, LDS, s>>>(a, lda, w, C, ldc, r, M, N, K, gate_blk, divide, norm_eps, (const T*)gain, vec_ok); \
+        kfn<<<grid, 64 * W, LDS, s>>>(a, lda, w, C, ldc, r, M, N, K, gate_blk, divide, norm_eps, (const T*)gain, vec_ok, up, (const vec16*)job.src, \
+                                      (vec16*)job.dst, job.n16);                                               \
     }
     switch (epi) {
         case EPI_STORE: SS_GO(EPI_STORE) break;
@@ -424,23 +440,24 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
 // are too short: 50257 x 768 27 us, 18 by the rule; 32001 x 1024 21 and 14; 8192 x 1024 7.1 and 5.8.
 template <typename T, int MT>
 static hipError_t pick_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
-                              int epi, int gate_blk, int divide, float norm_eps, const void* gain, hipStream_t s) {
+                              int epi, int gate_blk, int divide, float norm_eps, const void* gain, const UploadJob& job, hipStream_t s) {
     if constexpr (MT == 1)
-        if (M <= 8 && sizeof(T) == 2 && K >= 2048) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s);
+        if (M <= 8 && sizeof(T) == 2 && K >= 2048) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s);
     const long long tiles = (long long)((N + 15) / 16) * ((M + 16 * MT - 1) / (16 * MT));
-    if (tiles <= 256) return launch_direct<T, MT, 1, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s);
-    if (tiles <= 512) return launch_direct<T, MT, 2, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s);
-    return launch_direct<T, MT, 3, 8, 1>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s);
+    if (tiles <= 256) return launch_direct<T, MT, 1, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s);
+    if (tiles <= 512) return launch_direct<T, MT, 2, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s);
+    return launch_direct<T, MT, 3, 8, 1>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s);
 }
 
 hipError_t gemm_direct(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
-                       int epi, float norm_eps, const void* gain, hipStream_t s) {
+                       int epi, float norm_eps, const void* gain, const UploadJob& job, hipStream_t s) {
     if (!gemm_direct_takes(dt, A, Wt, M, N, K, lda, epi)) return hipErrorInvalidValue;
+    if (job.n16 < 0 || (job.n16 > 0 && epi != EPI_STORE) || (((uintptr_t)job.src | (uintptr_t)job.dst) & 15) != 0) return hipErrorInvalidValue;
     if (gain && (epi != EPI_STORE_F32 || norm_eps < 0.f || ((uintptr_t)gain & 15) != 0)) return hipErrorInvalidValue;
     const int gate_blk = epi == EPI_SWIGLU ? 32 : N / 2;
     const int divide = epi == EPI_SWIGLU_HALVES;
     if (divide) epi = EPI_SWIGLU;
-#define SS_GO(TT, MT) return pick_direct<TT, MT>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, s)
+#define SS_GO(TT, MT) return pick_direct<TT, MT>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s)
 #ifndef SS_HALF_F16          // fp32 is the same code in both builds of this file: only the first has it
     if (dt == F32) {
         if (M <= 16) SS_GO(float, 1);

@@ -91,10 +91,17 @@ int gemm_stream_columns(int M, int N, int K, int n_cus, int* pick);
 GemmPlan gemm_mfma_plan(bool stream_ok, bool tile_ok, int M, int N, int K, int epi, size_t ws_bytes, int n_cus);
 bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int K, int lda, int epi);
 hipError_t gemm_direct(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
-                       int epi, float norm_eps, const void* gain, hipStream_t s);
+                       int epi, float norm_eps, const void* gain, const UploadJob& job, hipStream_t s);
 
 bool gemm_norms_itself(int dt, const void* A, int lda, const void* Wt, int M, int N, int K, int epi, bool force_generic) {
     return !force_generic && gemm_direct_takes(dt, A, Wt, M, N, K, lda, epi);
+}
+
+hipError_t norm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, int M, int N, int K, int epi, float norm_eps,
+                   const UploadJob& job, hipStream_t s) {
+    if (M <= 0 || N <= 0) return job.n16 ? hipErrorInvalidValue : hipSuccess;
+    if (K <= 0 || lda < K || !A || !Wt || !C || norm_eps < 0.f || !gemm_norms_itself(dt, A, lda, Wt, M, N, K, epi, false)) return hipErrorInvalidValue;
+    return gemm_direct(dt, A, lda, Wt, C, ldc, nullptr, M, N, K, epi, norm_eps, nullptr, job, s);
 }
 
 // Few rows: every column block scales the rows again.  IEEE half keeps the norm apart: a row times its gains has to fit the type
@@ -110,7 +117,7 @@ hipError_t head_nt(int dt, const void* A, int lda, const void* Wt, float* C, int
                    const void* gain, hipStream_t s) {
     if (M <= 0 || N <= 0) return hipSuccess;
     if (K <= 0 || lda < K || !A || !Wt || !C || !gain || !head_norms_itself(dt, A, lda, Wt, gain, M, N, K, false)) return hipErrorInvalidValue;
-    return gemm_direct(dt, A, lda, Wt, C, ldc, nullptr, M, N, K, EPI_STORE_F32, norm_eps, gain, s);
+    return gemm_direct(dt, A, lda, Wt, C, ldc, nullptr, M, N, K, EPI_STORE_F32, norm_eps, gain, UploadJob(), s);
 }
 
 hipError_t gemm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N,
@@ -119,7 +126,7 @@ hipError_t gemm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int 
     if (M <= 0 || N <= 0) return hipSuccess;
     if (K <= 0 || lda < K || !A || !Wt || !C) return hipErrorInvalidValue;
     if (!row_scale && gemm_norms_itself(dt, A, lda, Wt, M, N, K, epi, force_generic))
-        return gemm_direct(dt, A, lda, Wt, C, ldc, R, M, N, K, epi, norm_eps, nullptr, s);
+        return gemm_direct(dt, A, lda, Wt, C, ldc, R, M, N, K, epi, norm_eps, nullptr, UploadJob(), s);
     if (norm_eps >= 0.f || epi == EPI_SWIGLU_HALVES) return hipErrorInvalidValue;     // only the kernel above does these
     if (dt == BF16 && !force_generic && gemm_mfma_supported(M, N, K, lda, ldc, epi))
         return gemm_mfma_bf16(A, lda, Wt, C, ldc, R, M, N, K, epi, s, ws, ws_bytes, max_rounds, row_scale);

@@ -129,6 +129,12 @@ __device__ __forceinline__ void rope_rotate(float lo, float hi, float c, float s
     ohi = fmaf(hi, c, lo * s);
 }
 
+// pieces first, first + step, ... of `n` from page-locked host memory: a few requests of a thread cross the link together
+__device__ __forceinline__ void upload_pieces(const vec16* __restrict__ src, vec16* __restrict__ dst, int64_t n, int64_t first, int64_t step) {
+#pragma unroll 4
+    for (int64_t i = first; i < n; i += step) dst[i] = src[i];
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -87,6 +87,14 @@ struct DecodeWork {
     int max_items_per_seq;
 };
 
+// Metadata of a batch on its way from page-locked memory (its device address) to the device: 16-byte pieces that the first
+// launch of an attention phase takes along, in blocks of their own.  Nothing in that launch reads them.
+struct UploadJob {
+    const void* src = nullptr;
+    void* dst = nullptr;
+    int64_t n16 = 0;
+};
+
 // KV repack between pages and heads-major staging.
 // unit u = one (sequence, local layer): a staging block [2][n_heads][len][d] at
 // element offset unit_off[u]; its page list starts at pages[unit_pt[u]]; the
@@ -135,6 +143,10 @@ hipError_t gemm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int 
                    hipStream_t s, float* ws = nullptr, size_t ws_bytes = 0, int max_rounds = 0,
                    const float* row_scale = nullptr, float norm_eps = -1.0f);
 
+// gemm_nt of a product that works its rows' RMSNorm factor out itself (gemm_norms_itself), with an upload.
+hipError_t norm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, int M, int N, int K, int epi, float norm_eps,
+                   const UploadJob& job, hipStream_t s);
+
 // Final norm and LM head in one: C (fp32) = norm(A) * gain * Wt^T, gain of K values of the model dtype.  Only where
 // head_norms_itself says so (few rows), refused elsewhere.
 bool head_norms_itself(int dt, const void* A, int lda, const void* Wt, const void* gain, int M, int N, int K, bool force_generic);
@@ -146,7 +158,7 @@ hipError_t rmsnorm(int dt, const void* x, const void* g, void* out, int T, int H
                    hipStream_t s);
 
 // r[t] = rsqrt(mean(x[t,:]^2) + eps)
-hipError_t row_scale(int dt, const void* x, float* r, int T, int H, float eps, hipStream_t s);
+hipError_t row_scale(int dt, const void* x, float* r, int T, int H, float eps, hipStream_t s, const UploadJob& job = UploadJob());
 
 // out[t, j] = silu(gu[t, j]) * gu[t, F + j]   (unfused form used by the generic GEMM path)
 hipError_t swiglu(int dt, const void* gu, void* out, int T, int F, hipStream_t s);
@@ -160,6 +172,7 @@ struct EmbedIds {
     int32_t v[N];
 };
 hipError_t embed_ids(int dt, const void* table, const int32_t* ids_host, void* out, int n, int H, hipStream_t s);
+
 // Copy of a multiple of 16 bytes from page-locked host memory (its device address), by a kernel.
 hipError_t upload(const void* src_mapped, void* dst, size_t bytes, hipStream_t s);
 

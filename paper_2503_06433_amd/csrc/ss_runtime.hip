@@ -93,6 +93,8 @@ struct MetaSlot {
     size_t cap = 0;
     hipEvent_t done = nullptr;
     bool in_flight = false;
+    ssk::UploadJob job;                // host -> dev, taken along by the first launch that uses the slot
+    bool pending = false;              // ... which has not been made yet
     // cache key
     Shard* shard = nullptr;
     uint64_t version = 0;
@@ -527,8 +529,8 @@ static int decode_item_pages(int64_t total_pages, int n_kv_local) {
     return (int)(n & ~1);
 }
 
-// Builds (or reuses) the device metadata of a batch.  Returns the slot.
-int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, hipStream_t stream, MetaSlot** out) {
+// Builds (or reuses) the metadata of a batch.  Returns the slot, whose upload may still have to be made (`pending`).
+int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot** out) {
     const int n = b->n_seqs;
     // ---- validation + page allocation (idempotent)
     int64_t T = 0;
@@ -766,10 +768,11 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, hipStream
     memcpy(ms.host + off_upos, unit_pos0.data(), 4 * n_units);
     memcpy(ms.host + off_ucnt, unit_cnt.data(), 4 * n_units);
     if (!pf_items.empty()) memcpy(ms.host + off_pf, pf_items.data(), 4 * pf_items.size());
-    {   // by a kernel: it queues behind the launch before it, where the copy engine costs two hand-overs between queues
+    {
         void* mapped = nullptr;
         HIP_TRY(c, hipHostGetDevicePointer(&mapped, ms.host, 0));
-        HIP_TRY(c, ssk::upload(mapped, ms.dev, total, stream));
+        ms.job = {mapped, ms.dev, (int64_t)(total / 16)};
+        ms.pending = true;
     }
     ms.bm.tok_seq = (const int32_t*)(ms.dev + off_tok_seq);
     ms.bm.tok_pos = (const int32_t*)(ms.dev + off_tok_pos);
@@ -841,17 +844,22 @@ int splitk_ws(ss_ctx* c, int T, SplitWs* w) {
 // time, the product runs on the raw activations and its epilogue multiplies every token row by
 // rsqrt(mean(x^2) + eps).  Products of few rows work that factor out from the rows that pass through them; for the
 // others a read-only pass over x provides it: `rs`, T floats.
+// The first of its launches takes `job` along.
 int norm_gemm(ss_ctx* c, const void* x, const void* wt, void* out, int ldc, int T, int N, int epi, float* rs, const SplitWs& ws,
-              hipStream_t st) {
+              hipStream_t st, const ssk::UploadJob& job = ssk::UploadJob()) {
     const int H = c->m.hidden;
-    const bool itself = c->m.rms_eps >= 0.f && SSK_CALL(c, gemm_norms_itself, x, H, wt, T, N, H, epi, c->force_generic);
-    if (!itself) {
+    if (c->m.rms_eps >= 0.f && SSK_CALL(c, gemm_norms_itself, x, H, wt, T, N, H, epi, c->force_generic)) {
+        ProfScope ps(c, 0, st);
+        K_TRY(c, SSK_CALL(c, norm_nt, x, H, wt, out, ldc, T, N, H, epi, c->m.rms_eps, job, st));
+        return SS_OK;
+    }
+    {
         ProfScope ps(c, 4, st);
-        K_TRY(c, SSK_CALL(c, row_scale, x, rs, T, H, c->m.rms_eps, st));
+        K_TRY(c, SSK_CALL(c, row_scale, x, rs, T, H, c->m.rms_eps, st, job));
     }
     ProfScope ps(c, 0, st);
     K_TRY(c, SSK_CALL(c, gemm_nt, x, H, wt, out, ldc, nullptr, T, N, H, epi, c->force_generic, st, ws.p,
-                      ws.bytes, c->gemm_rounds, itself ? nullptr : rs, itself ? c->m.rms_eps : -1.0f));
+                      ws.bytes, c->gemm_rounds, rs));
     return SS_OK;
 }
 
@@ -860,7 +868,7 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     const ss_model_cfg& m = c->m;
     const LayerW& w = s->w[ll];
     MetaSlot* ms = nullptr;
-    int rc = prepare_batch(c, s, b, decode, st, &ms);
+    int rc = prepare_batch(c, s, b, decode, &ms);
     if (rc) return rc;
     const int T = ms->bm.T, H = m.hidden, d = m.head_dim;
     const int nqkv = (s->nq_l + 2 * s->nkv_l) * d;
@@ -875,7 +883,9 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     SplitWs ws;
     if ((rc = splitk_ws(c, T, &ws))) return rc;
     const ssk::KvLayer kv = kv_layer(c, s, ll);
-    if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, rs, ws, st))) return rc;
+    // the product does not read the batch's metadata, what comes behind it does
+    if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, rs, ws, st, ms->pending ? ms->job : ssk::UploadJob()))) return rc;
+    ms->pending = false;
     if (decode) {
         ProfScope ps(c, 2, st);
         K_TRY(c, SSK_CALL(c, attn_decode, c->ws_qkv.p, c->ws_attn.p, s->nq_l, s->nkv_l, ms->bm, kv, ms->wk, c->d_rope,
