@@ -256,7 +256,11 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
     const int whole = K / CH;
     const int full = (whole > wave ? (whole - wave + W - 1) / W : 0) / DEPTH;
     int c = wave;
-    auto load_rest = [&](int d, int at) { if (at < nch) load(d, at); };
+    // (the zeros of a cut chunk are chosen behind its loads, that is by waiting for them: only where a chunk is cut)
+    auto load_rest = [&](int d, int at) {
+        if (at < whole) load_full(d, at);
+        else if (at < nch) load(d, at);
+    };
     if (full > 0) {
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) load_full(d, c + d * W);
@@ -435,18 +439,38 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
 // one per block, up to 512 two, beyond that three (gate/up 22016 x 4096 at 16 rows, blocks of 1 / 2 / 3 / 6 tiles:
 // 36.0 / 44 / 34.6 / 36.0 us; QKV 12288 x 4096 at 64 rows: 53 / 37 / 24.9 us).  A chunk is 2 (NT + MT) KB, so with DEPTH 2 a wave
 // has 8 to 24 KB on their way (eight waves a block); the widest blocks keep one chunk, 8 to 14 KB, as two would spill.
-// Up to 8 rows (16-bit) one tile and four chunks on their way per wave, whatever the width, where every wave has as many
-// (K of 2048 and more): 22016 x 4096 at 8 rows 33.0 us, 34.8 by the rule above; 4096 x 2048 6.3 and 6.9.  Below that the blocks
-// are too short: 50257 x 768 27 us, 18 by the rule; 32001 x 1024 21 and 14; 8192 x 1024 7.1 and 5.8.
+// Up to 16 rows (16-bit) and K of 2048 and more:
+//  - 129 to 256 tiles, a block for each: sixteen waves (4096 x 4096 at 8 / 16 rows 9.0 / 9.5 -> 8.5 / 8.9 us, 4096 x 11008 22.6 / 23.4
+//    -> 21.4 / 22.5; 80 tiles, 1280 x 8192 10.5 -> 10.8, stay with eight);
+//  - up to 8 rows one tile and four chunks on their way per wave, whatever the width (22016 x 4096 33.0 us, 34.8 by the rule
+//    above, 12288 x 4096 19.4 and 21.4), but two tiles where one would give a quarter to a half of the units a second long block
+//    (5120 x 13824 36.1 -> 30.6; not 5504 x 4096, 12.4 and 13.8, nor 7168 x 8192, 25.6 and 28.4);
+//  - 9 to 16 rows, SwiGLU over 257 to 512 tiles: sixteen waves (7168 x 8192 28.4 -> 25.4, 5504 x 4096 13.8 -> 12.7; without SwiGLU 5120 x
+//    13824 33.3 -> 33.8, 8192 x 3584 12.9 -> 13.1);
+//  - 9 to 16 rows, wider: four tiles where they fill the last round of blocks better than three (14336 x 8192 59.5 -> 47.2, 27648 x
+//    5120 58.1 -> 53.4; 22016 x 4096 stays at three, 35.2, 12288 x 4096 as well, 21.3 and 21.5).
+// Shorter: 50257 x 768 one tile 27 us, by the rule above 18; 32001 x 1024 21 and 14.
 template <typename T, int MT>
 static hipError_t pick_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
                               int epi, int gate_blk, int divide, float norm_eps, const void* gain, const UploadJob& job, hipStream_t s) {
-    if constexpr (MT == 1)
-        if (M <= 8 && sizeof(T) == 2 && K >= 2048) return launch_direct<T, 1, 1, 8, 4>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s);
     const long long tiles = (long long)((N + 15) / 16) * ((M + 16 * MT - 1) / (16 * MT));
-    if (tiles <= 256) return launch_direct<T, MT, 1, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s);
-    if (tiles <= 512) return launch_direct<T, MT, 2, 8, 2>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s);
-    return launch_direct<T, MT, 3, 8, 1>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s);
+#define SS_GO(NT, W, D) return launch_direct<T, MT, NT, W, D>(A, lda, Wt, C, ldc, R, M, N, K, epi, gate_blk, divide, norm_eps, gain, job, s)
+    if constexpr (MT == 1 && sizeof(T) == 2) {
+        if (K >= 2048) {
+            if (tiles > 128 && tiles <= 256) SS_GO(1, 16, 2);
+            if (M <= 8 && tiles > 256 && tiles <= 384 && K >= 8192) SS_GO(2, 8, 2);
+            if (M <= 8) SS_GO(1, 8, 4);
+            if (tiles > 256 && tiles <= 512 && epi == EPI_SWIGLU) SS_GO(2, 16, 2);
+            if (tiles > 512) {      // three or four tiles a block: the one whose last round of blocks is fuller
+                const long long b3 = (tiles + 2) / 3, b4 = (tiles + 3) / 4;
+                if (b4 * ((b3 + 255) / 256) > b3 * ((b4 + 255) / 256)) SS_GO(4, 8, 2);
+            }
+        }
+    }
+    if (tiles <= 256) SS_GO(1, 8, 2);
+    if (tiles <= 512) SS_GO(2, 8, 2);
+    SS_GO(3, 8, 1);
+#undef SS_GO
 }
 
 hipError_t gemm_direct(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,

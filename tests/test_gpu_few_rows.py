@@ -23,6 +23,10 @@ if torch.cuda.is_available():
     (wl.F16, 128, 8224),       # three up to 16 rows, and a long contraction for one wave's share
     (wl.BF16, 128, 12800),     # gate / up so wide that more than 16 rows take the tile kernel, a contraction so long that more
                                # than 32 take split K in front of it
+    (wl.BF16, 2112, 4128),     # contractions of 2048 and more: three tiles; down sixteen waves that share 65 chunks, the last cut
+    (wl.F16, 2048, 2752),      # sixteen waves of two tiles from 9 rows on
+    (wl.BF16, 2080, 7200),     # four tiles; a cut chunk behind whole ones that are no multiple of those on their way
+    (wl.BF16, 4160, 8200),     # down up to 8 rows two tiles
     (wl.BF16, 200, 72),        # hidden no multiple of 64: gate rows first, up rows behind; chunks cut on both sides
     (wl.F32, 256, 688),
     (wl.F32, 36, 4100),        # fp32 with three tiles per block and a contraction of little more than one chunk
