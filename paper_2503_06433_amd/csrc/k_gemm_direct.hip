@@ -89,7 +89,9 @@ constexpr int EPI_HEAD = 100;      // internal: EPI_STORE_F32 of rows that are s
 // EPI_HEAD: final norm and LM head in one launch.  The rows meet their gains in registers, in the order they are loaded in, and
 // are rounded once to the storage type like the separate norm's result, but before the row's factor instead of behind it; the
 // sums of squares come from the unscaled values there (a row's 128-byte chunk lies in eight neighbouring lanes).  Eight
-// rows, 2048 x 4096: TODO
+// rows, 2048 x 4096: norm kernel and product apart 12.7 us, together 7.6.
+// 32-bit rows: the factor meets the finished sum, one rounding more that a whole row shares, so it is worked out in 64 bits:
+// error against 64 bits (256 columns, 64 rows) 1.299e-7 apart, 1.304e-7 together with a 32-bit factor, 1.275e-7 with this one.
 //
 // SwiGLU: a tile is 8 gate rows and the 8 up rows that belong to them, so a block of NT tiles has 8 NT output columns.
 // Gate rows come in blocks of gate_blk, each followed by its up rows (gate_blk = N / 2: all gate rows first).
@@ -336,7 +338,8 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
             float ss = 0.f;
 #pragma unroll
             for (int w = 0; w < W; ++w) ss += sq[w * (MT * 16) + i * 16 + (l & 15)];
-            rs = 1.0f / sqrtf(ss / (float)K + norm_eps);
+            if constexpr (HEAD && sizeof(T) == 4) rs = (float)(1.0 / sqrt((double)ss / K + norm_eps));
+            else rs = 1.0f / sqrtf(ss / (float)K + norm_eps);
         }
         float o[4];
         const f32x4_t s = sum(l);
