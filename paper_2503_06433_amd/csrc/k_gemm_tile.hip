@@ -2,8 +2,8 @@
 // C[M,N] = A[M,K] * Wt[N,K]^T, 16-bit types.
 //
 // At these sizes neither the weight stream nor the matrix pipes bound the launch by themselves; a tile for every compute
-// unit does.  So the tile is chosen per shape, such that one round of tiles just covers the chip, K is never cut over
-// blocks (no partial sums in memory, no second kernel), and inside a block the waves are made as large as registers
+// unit does.  So the tile is chosen per shape, such that one round of tiles just covers the chip, K is cut over
+// blocks only for long contractions of narrow outputs (gemm_tile_split_estimate), and inside a block the waves are made as large as registers
 // allow and doubled by splitting the k-steps of every stage between two or four groups of waves: the fragment reads from
 // LDS depend on the wave tile, the latencies are covered by the number of waves.  The groups' sums meet in LDS once.
 //
@@ -12,13 +12,13 @@
 //
 // What bounds it (parts of the loop switched off, 128 x 96 tiles, 256 x 12288 x 4096): whole 40.5 us, loads and
 // barriers alone 38.5, the same with all weights found in the L2 21.9, matrix instructions and fragment reads alone 29.6.
-// It waits for weight lines from beyond the L2: a compute unit takes in about 26 bytes of them per nanosecond next to the
-// token lines, at 3 as at 5 stages.  Touching weight lines ahead (one dword per line, by turns of the blocks that share
+// It waits for lines: a compute unit takes in about 26 bytes of weights per nanosecond next to the token lines, at 3 as at 5
+// stages; the two streams add up, and no layout, stride or K phase of the weights changes that by more than some per cent.  Touching weight lines ahead (one dword per line, by turns of the blocks that share
 // them, singly or in bursts, 6 to 24 stages ahead) made it 5-30 % slower.
 //
 // Measured against the 128 x 128 register-staged kernel or the persistent kernel with split K and their reduce launch:
-// 256 rows: 12288 x 4096 54 -> 39 us, gate/up 22016 x 4096 74 -> 57, 4096 x 11008 47 -> 53 (+ 7 for its reduce), 4096 x 4096
-// 27 -> 22; 333 rows: 73 -> 47, 132 -> 72, 79 -> 63, 34 -> 27; 864 rows: 12288 x 4096 160 -> 97, 4096 x 4096 61 -> 42.
+// 256 rows: 12288 x 4096 54 -> 39 us, gate/up 22016 x 4096 74 -> 57, 4096 x 11008 54 with its reduce -> 41 (four ranges), 4096 x 4096
+// 27 -> 22; 333 rows: 73 -> 47, 132 -> 72, 79 -> 45, 34 -> 27; 864 rows: 12288 x 4096 160 -> 97, 4096 x 4096 61 -> 42.
 #include <type_traits>
 
 #include "ss_device.h"

@@ -58,7 +58,7 @@ CLASSES = (
     ("prefill_gemms", ("gemm_mfma_stream_kernel",)),
     ("prefill_attention", ("attn_prefill_lds_kernel", "attn_prefill_mfma_kernel")),
     ("decode_attention", ("attn_decode_mfma_kernel", "attn_decode_merge_kernel")),
-    ("decode_gemms", ("gemm_mfma_kernel<", "gemm_direct_kernel", "gemm_tile_kernel", "splitk_reduce_kernel", PARTIAL_SUMS)),
+    ("decode_gemms", ("gemm_mfma_kernel<", "gemm_direct_kernel", "gemm_tile_kernel", "splitk_reduce", PARTIAL_SUMS)),
     ("kv_repack", ("kv_repack_kernel",)),
 )
 
