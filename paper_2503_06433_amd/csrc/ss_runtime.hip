@@ -64,6 +64,7 @@ struct DeferredFree {
 struct SeqState {
     std::vector<int32_t> pages;
     int32_t len = 0;
+    uint64_t seen = 0;         // batch that listed the sequence last (ss_ctx::batches)
 };
 
 struct Shard {
@@ -95,6 +96,7 @@ struct MetaSlot {
     bool in_flight = false;
     ssk::UploadJob job;                // host -> dev, taken along by the first launch that uses the slot
     bool pending = false;              // ... which has not been made yet
+    bool repeats = false;              // decode batch that lists a sequence more than once: runs like a prefill batch
     // cache key
     Shard* shard = nullptr;
     uint64_t version = 0;
@@ -340,6 +342,7 @@ struct ss_ctx {
     DevBuf ws_h, ws_qkv, ws_attn, ws_act, ws_x1, ws_scratch, ws_splitk, ws_chain[2];
     MetaSlot meta[4];
     int meta_next = 0;
+    uint64_t batches = 0;      // metadata built so far
     XferSlot xfer[2];
     int xfer_next = 0;
     size_t xfer_cap = 0;               // of each image
@@ -623,14 +626,23 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
     ms.shard = nullptr;
     int pt_stride = 1;
     std::vector<const SeqState*> sts(n);
+    // A decode batch may list a sequence at several of its positions (tokens that are in the cache already, taken again).  The
+    // decode kernels write a new token's key and value behind or next to the reads of the others, so such a batch takes
+    // the way of prefill batches, where all new tokens are in their pages before the first is attended to.
+    ms.repeats = false;
+    ++c->batches;
     for (int i = 0; i < n; ++i) {
-        sts[i] = &s->seqs[b->seq_ids[i]];
-        pt_stride = std::max<int>(pt_stride, (int)sts[i]->pages.size());
+        SeqState& st = s->seqs[b->seq_ids[i]];
+        ms.repeats |= decode && st.seen == c->batches;
+        st.seen = c->batches;
+        sts[i] = &st;
+        pt_stride = std::max<int>(pt_stride, (int)st.pages.size());
     }
+    const bool items = decode && !ms.repeats;
     // decode work items
     std::vector<int32_t> item_seq, item_page0, item_np, seq_item0;
     int max_items = 0;
-    if (decode) {
+    if (items) {
         seq_item0.resize(n + 1);
         int64_t total_pages = 0;
         for (int i = 0; i < n; ++i) total_pages += (b->kv_lens_before[i] + 1 + c->m.page_size - 1) / c->m.page_size;
@@ -791,7 +803,7 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
         std::fill(row + pg.size(), row + pt_stride, pg.empty() ? 0 : pg.back());
     }
     cu[n] = t;
-    if (decode) {
+    if (items) {
         memcpy(ms.host + off_iseq, item_seq.data(), 4 * n_items);
         memcpy(ms.host + off_ip0, item_page0.data(), 4 * n_items);
         memcpy(ms.host + off_inp, item_np.data(), 4 * n_items);
@@ -905,6 +917,7 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     MetaSlot* ms = nullptr;
     int rc = prepare_batch(c, s, b, decode, &ms);
     if (rc) return rc;
+    if (ms->repeats) decode = false;
     const int T = ms->bm.T, H = m.hidden, d = m.head_dim;
     const int nqkv = (s->nq_l + 2 * s->nkv_l) * d;
     const size_t qkv_bytes = align256((size_t)T * nqkv * c->es);
