@@ -7,6 +7,9 @@
 // walks the sequence's pages in order; a page's K [16][D] and V^T [D][16]
 // chunks are staged through LDS as floats; softmax is the streaming
 // (running max / running sum) form in fp32.
+//
+// Slots of the last page behind the last visible token hold what an earlier owner of the page left, which may not be finite:
+// their values count as zeros (weight 0 alone would not keep them out of the sums), here and in the matrix-core kernels.
 #include "ss_device.h"
 #include "ss_kernels.h"
 
@@ -45,7 +48,7 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const T* __restrict__
         const T* vp = v_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D;
         for (int i = threadIdx.x; i < PS * D; i += 256) {
             (&Ks[0][0])[i] = ldf(kp + i);
-            Vs[i / PS][i % PS] = ldf(vp + i);
+            Vs[i / PS][i % PS] = j * PS + vtok(i % PS, i / PS) <= before + last_q ? ldf(vp + i) : 0.f;
         }
         __syncthreads();
         float s[PS];
@@ -219,6 +222,10 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
 #pragma unroll
                 for (int t = 0; t < PS; ++t) v[t] = t == at ? ldf(&v_new[r]) : v[t];
                 if (a % (n_q / n_kv) == 0) v_pool[(size_t)pt[j] * page_elems + (size_t)g * PS * D + e * PS + at] = v_new[r];
+            }
+            if (j == n_pages - 1) {
+#pragma unroll
+                for (int t = 0; t < PS; ++t) v[t] = vtok(t, lane) <= slot ? v[t] : 0.f;
             }
 #pragma unroll
             for (int t = 0; t < PS; ++t) sum = fmaf(__shfl(w, 4 * vtok(t, lane), 64), v[t], sum);   // rows lane, lane + 64: one order

@@ -158,6 +158,15 @@ __global__ __launch_bounds__(256) void attn_prefill_mfma_kernel(const bf16_t* __
             Frag va, vb;
             va.q = *reinterpret_cast<const vec16*>(vA + u * 32 * 16);
             vb.q = *reinterpret_cast<const vec16*>(vB + u * 32 * 16);
+            // tokens behind the last one that the wave sees: what the page's last user left, or a page that is only repeated
+            if (t0 + 31 > before + last_q) {
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const int at = t0 + 4 * g2 + 2 * (w & 1) + 8 * (w >> 1), seen = before + last_q;
+                    va.w[w] &= (at <= seen ? 0xffffu : 0u) | (at + 1 <= seen ? 0xffff0000u : 0u);
+                    vb.w[w] &= (at + 16 <= seen ? 0xffffu : 0u) | (at + 17 <= seen ? 0xffff0000u : 0u);
+                }
+            }
 #pragma unroll
             for (int t = 0; t < QT; ++t) {
                 o[t][u] = SS_MFMA_32x32x16(va.v, pfA[t].v, o[t][u], 0, 0, 0);
@@ -354,8 +363,31 @@ __global__ __launch_bounds__(512) void attn_prefill_lds_kernel(const bf16_t* __r
     // No tile is requested past the last one (the block would only have to wait for it at the end), so the
     // last iteration waits for everything and the others for all but the newest tile.
     for (int it = 0; it < n_tiles; ++it) {
-        if (it + 1 < n_tiles) __builtin_amdgcn_s_waitcnt(0x0F74);     // vmcnt <= 4: this wave's part of tile `it` has landed
-        else __builtin_amdgcn_s_waitcnt(0x0F70);
+        if (it + 1 < n_tiles) {
+            __builtin_amdgcn_s_waitcnt(0x0F74);        // vmcnt <= 4: this wave's part of tile `it` has landed
+        } else {
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            // Values behind the block's last token (left there by the page's last user, or of a page that is only repeated)
+            // become zeros in this wave's part of the tile: weight 0 would not keep one that is not finite out of the sums.
+            const int past = it * 64 + (wave >> 1) * 16 + 15 - blk_last;
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" ::: "memory");
+            if (past > 0) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int piece = wave * 2 + i, row = (piece & 3) * 32 + (lane >> 1);
+                    vec16* at = reinterpret_cast<vec16*>(smem + (it % NS) * STAGE + KBYTES + piece * 1024 + lane * 16);
+                    vec16 v = *at;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const int t = vtok(8 * (lane & 1) + 2 * w, row);      // and the token behind it
+                        v.w[w] &= (t <= 15 - past ? 0xffffu : 0u) | (t + 1 <= 15 - past ? 0xffff0000u : 0u);
+                    }
+                    *at = v;
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // written before the others are let on
+            }
+        }
         __builtin_amdgcn_s_barrier();                  // everyone's part landed; stage (it-1)%NS is free
         __builtin_amdgcn_sched_barrier(0);
         if (it + 2 < n_tiles) {

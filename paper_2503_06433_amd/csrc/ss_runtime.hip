@@ -491,7 +491,7 @@ int ensure_pools(ss_ctx* c, Shard* s) {
     for (int l = 0; l < s->n_layers_l; ++l) {
         HIP_TRY(c, hipMalloc(&s->k_pool[l], bytes));
         HIP_TRY(c, hipMalloc(&s->v_pool[l], bytes));
-        // finite contents everywhere: masked slots are multiplied by exact zeros
+        // defined contents from the start (what the attention kernels must not see they mask themselves)
         HIP_TRY(c, hipMemset(s->k_pool[l], 0, bytes));
         HIP_TRY(c, hipMemset(s->v_pool[l], 0, bytes));
     }
