@@ -92,7 +92,14 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const T* __restrict__
 // K: four lanes per token, a quarter of the head dimension each.  V^T: a lane owns whole rows of 16 tokens and fetches
 // their weights from the lanes that hold them.  Four sequences of 32 to 40 tokens, fp32, 4 heads of 64: a run of
 // eight tokens through two layers in 612 us with this kernel and 750 us with the tiled one.
-template <typename T, int D>
+//
+// AHEAD: a wave's first page is requested in front of everything else and the next ones as soon as the registers are free (layer
+// call, fp32, 16 heads of 64, 256 sequences of 800 tokens 449 -> 369 us; 8 heads of 128, 128 of 1600 501 -> 387).  It takes registers
+// (110 in place of 94, heads of 128 159 and 127), so not where no wave has a second page (8 heads of 128, 512 sequences of 8
+// tokens 113 us without and 128 with it), nor for many blocks of a 16-bit type, which wait for the vector ALU (32 heads
+// over one of 128, 256 sequences of 800 tokens 248 and 325; 16 sequences of 1600 70 and 63).
+// ROPE: the new tokens come as the products leave them; the kernel rotates q and k and writes the page (attn_decode_rotates).
+template <typename T, int D, bool ROPE, bool AHEAD>
 __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __restrict__ qkv, T* __restrict__ out, int n_q,
                                                                   int n_kv, BatchMeta bm, const float* __restrict__ rope,
                                                                   T* k_pool, T* v_pool, float scale) {
@@ -102,7 +109,7 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
     const int a = blockIdx.x, sq = blockIdx.y;
     const int q_begin = bm.cu_q[sq];
     if (bm.cu_q[sq + 1] - q_begin != 1) return;
-    const int p = bm.kv_before[sq], n_pages = p / PS + 1;
+    const int p = bm.kv_before[sq], n_pages = p / PS + 1, slot = p % PS;
     const int g = a / (n_q / n_kv);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int tok = lane >> 2, sub = lane & 3;
@@ -122,77 +129,78 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
     };
     // Everything that does not depend on something loaded is requested together: a lane's quarter of the new token's q and (the
     // wave that has the new token's page) k, the quarters they are rotated with, cos / sin, the new value, the first page.
-    const bool last_here = rope && (n_pages - 1) % 4 == wave;
+    const bool last_here = ROPE && (n_pages - 1) % 4 == wave;
     const T *qh = row + (size_t)a * D, *kh = row + (size_t)(n_q + g) * D, *vh = kh + (size_t)n_kv * D;
-    vec16 q_own[DS / EV], q_other[DS / EV], k_own[DS / EV], k_other[DS / EV];
+    vec16 q_own[DS / EV], q_other[ROPE ? DS / EV : 1], k_own[ROPE ? DS / EV : 1], k_other[ROPE ? DS / EV : 1];
     T v_new[DR];
-    float cs[2 * DS];
+    float cs[ROPE ? 2 * DS : 1];
 #pragma unroll
     for (int i = 0; i < DS / EV; ++i) q_own[i] = *reinterpret_cast<const vec16*>(qh + sub * DS + i * EV);
-    if (rope) {
+    if constexpr (ROPE) {
 #pragma unroll
         for (int i = 0; i < DS / EV; ++i) q_other[i] = *reinterpret_cast<const vec16*>(qh + (sub ^ 2) * DS + i * EV);
 #pragma unroll
         for (int i = 0; i < DS / 2; ++i)
             unpack16<float>(*reinterpret_cast<const vec16*>(rope + (size_t)p * D + 2 * (sub & 1) * DS + 4 * i), cs + 4 * i);
-    }
-    if (last_here) {
+        if (last_here) {
 #pragma unroll
-        for (int i = 0; i < DS / EV; ++i) {
-            k_own[i] = *reinterpret_cast<const vec16*>(kh + sub * DS + i * EV);
-            k_other[i] = *reinterpret_cast<const vec16*>(kh + (sub ^ 2) * DS + i * EV);
-        }
-#pragma unroll
-        for (int r = 0; r < DR; ++r) v_new[r] = vh[r * 64 + lane];
-    }
-    if (wave < n_pages) load_page(wave);
-    // rotated, rounded as stored
-    auto rotate = [&](const vec16* own, const vec16* other, float* f) {
-#pragma unroll
-        for (int i = 0; i < DS / EV; ++i) {
-            float o[EV];
-            unpack16<T>(own[i], f + i * EV);
-            unpack16<T>(other[i], o);
-#pragma unroll
-            for (int e = 0; e < EV; ++e) {
-                // rope_rotate's half that this lane has: the first quarters subtract the other half, the last add it
-                const float other = sub < 2 ? -o[e] : o[e];
-                T st;
-                stf(&st, fmaf(f[i * EV + e], cs[2 * (i * EV + e)], other * cs[2 * (i * EV + e) + 1]));
-                f[i * EV + e] = ldf(&st);
+            for (int i = 0; i < DS / EV; ++i) {
+                k_own[i] = *reinterpret_cast<const vec16*>(kh + sub * DS + i * EV);
+                k_other[i] = *reinterpret_cast<const vec16*>(kh + (sub ^ 2) * DS + i * EV);
             }
+#pragma unroll
+            for (int r = 0; r < DR; ++r) v_new[r] = vh[r * 64 + lane];
         }
-    };
-    if (rope) {
+    }
+    if (AHEAD && wave < n_pages) load_page(wave);
+    if constexpr (ROPE) {
+        // rotated, rounded as stored
+        auto rotate = [&](const vec16* own, const vec16* other, float* f) {
+#pragma unroll
+            for (int i = 0; i < DS / EV; ++i) {
+                float o[EV];
+                unpack16<T>(own[i], f + i * EV);
+                unpack16<T>(other[i], o);
+#pragma unroll
+                for (int e = 0; e < EV; ++e) {
+                    // rope_rotate's half that this lane has: the first quarters subtract the other half, the last add it
+                    const float other = sub < 2 ? -o[e] : o[e];
+                    T st;
+                    stf(&st, fmaf(f[i * EV + e], cs[2 * (i * EV + e)], other * cs[2 * (i * EV + e) + 1]));
+                    f[i * EV + e] = ldf(&st);
+                }
+            }
+        };
         rotate(q_own, q_other, q);
+        if (last_here) {
+            float kn[DS];
+            rotate(k_own, k_other, kn);
+#pragma unroll
+            for (int i = 0; i < DS / EV; ++i) k_own[i] = pack16<T>(kn + i * EV);
+        }
     } else {
 #pragma unroll
         for (int i = 0; i < DS / EV; ++i) unpack16<T>(q_own[i], q + i * EV);
     }
 #pragma unroll
     for (int e = 0; e < DS; ++e) q[e] *= scale;
-    const int slot = p % PS;
-    if (last_here) {
-        float kn[DS];
-        rotate(k_own, k_other, kn);
-#pragma unroll
-        for (int i = 0; i < DS / EV; ++i) k_own[i] = pack16<T>(kn + i * EV);
-    }
 #pragma unroll
     for (int r = 0; r < DR; ++r) acc[r] = 0.f;
     float m = -INFINITY, l = 0.f;
     for (int j = wave; j < n_pages; j += 4) {
+        if (!AHEAD) load_page(j);
         // The new token's key and value come from the products, for every head of the group; the first head's block writes
         // them into the page.
         const bool fresh = last_here && j == n_pages - 1;
-        if (fresh && tok == slot) {
+        if constexpr (ROPE)
+            if (fresh && tok == slot) {
 #pragma unroll
-            for (int i = 0; i < DS / EV; ++i) {
-                kr[i] = k_own[i];
-                if (a % (n_q / n_kv) == 0)
-                    *reinterpret_cast<vec16*>(k_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D + tok * D + sub * DS + i * EV) = kr[i];
+                for (int i = 0; i < DS / EV; ++i) {
+                    kr[i] = k_own[i];
+                    if (a % (n_q / n_kv) == 0)
+                        *reinterpret_cast<vec16*>(k_pool + (size_t)pt[j] * page_elems + (size_t)g * PS * D + tok * D + sub * DS + i * EV) = kr[i];
+                }
             }
-        }
         float d = 0.f;
 #pragma unroll
         for (int i = 0; i < DS / EV; ++i) {
@@ -217,21 +225,32 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
             float v[PS], sum = acc[r] * alpha;
 #pragma unroll
             for (int i = 0; i < PS / EV; ++i) unpack16<T>(vr[r][i], v + i * EV);
-            if (fresh) {
-                const int e = r * 64 + lane, at = vpos(slot, e);
+            if constexpr (ROPE)
+                if (fresh) {
+                    const int e = r * 64 + lane, at = vpos(slot, e);
 #pragma unroll
-                for (int t = 0; t < PS; ++t) v[t] = t == at ? ldf(&v_new[r]) : v[t];
-                if (a % (n_q / n_kv) == 0) v_pool[(size_t)pt[j] * page_elems + (size_t)g * PS * D + e * PS + at] = v_new[r];
-            }
-            if (j == n_pages - 1) {
+                    for (int t = 0; t < PS; ++t) v[t] = t == at ? ldf(&v_new[r]) : v[t];
+                    if (a % (n_q / n_kv) == 0) v_pool[(size_t)pt[j] * page_elems + (size_t)g * PS * D + e * PS + at] = v_new[r];
+                }
+            // rows lane, lane + 64: one order.  Slots of the last page that nobody may see count as zeros: fp32 ahead in a loop of its own
+            // (heads of 128 159 registers, 208 with the values chosen in front of one loop: layer call of 16 sequences of 3200 tokens
+            // 214 and 237 us), otherwise in front (16 heads of 64 in 16 bits, 4 sequences of 3200 70 and 84 us the other way).
+            constexpr bool OWN = AHEAD && sizeof(T) == 4;
+            const bool tail = j == n_pages - 1;
+            if (!OWN && tail) {
 #pragma unroll
                 for (int t = 0; t < PS; ++t) v[t] = vtok(t, lane) <= slot ? v[t] : 0.f;
             }
+            if (OWN && tail) {
 #pragma unroll
-            for (int t = 0; t < PS; ++t) sum = fmaf(__shfl(w, 4 * vtok(t, lane), 64), v[t], sum);   // rows lane, lane + 64: one order
+                for (int t = 0; t < PS; ++t) sum = fmaf(__shfl(w, 4 * vtok(t, lane), 64), vtok(t, lane) <= slot ? v[t] : 0.f, sum);
+            } else {
+#pragma unroll
+                for (int t = 0; t < PS; ++t) sum = fmaf(__shfl(w, 4 * vtok(t, lane), 64), v[t], sum);
+            }
             acc[r] = sum;
         }
-        if (j + 4 < n_pages) load_page(j + 4);
+        if (AHEAD && j + 4 < n_pages) load_page(j + 4);
     }
 #pragma unroll
     for (int o = 4; o < 64; o <<= 1) l += __shfl_xor(l, o, 64);
@@ -252,7 +271,7 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
     }
 }
 
-// With a rope table the new tokens come unrotated and their pages are written here: batches of one query per sequence only.
+// With a rope table the new tokens come unrotated and their pages are written here: one query per sequence, heads of 64.
 hipError_t attn_generic(int dt, const void* qkv, void* out, int n_q, int n_kv, const BatchMeta& bm,
                         const KvLayer& kv, const float* rope_table, hipStream_t s) {
     if (bm.T <= 0 || bm.n_seqs <= 0) return hipSuccess;
@@ -261,13 +280,21 @@ hipError_t attn_generic(int dt, const void* qkv, void* out, int n_q, int n_kv, c
     if (bm.n_seqs > 65535 || n_q > 65535) return hipErrorInvalidValue;
     // every sequence brings one query: the kernel made for that, whatever the number of cached tokens
     const bool one = bm.max_q_len == 1;
-    if (rope_table && !one) return hipErrorInvalidValue;
+    if (rope_table && (!one || kv.d != 64)) return hipErrorInvalidValue;
     dim3 grid((bm.max_q_len + 63) / 64, n_q, bm.n_seqs);
+    // the longest sequence has a second page for some wave; two blocks per compute unit or fewer
+    const bool ahead = bm.pt_stride > 4 && (dt == F32 || (long long)n_q * bm.n_seqs <= 512);
     const float scale = 1.0f / sqrtf((float)kv.d);
+#define SS_ONE(TT, DD, ROPE, AHEAD)                                                                         \
+    attn_generic_decode_kernel<TT, DD, ROPE, AHEAD><<<dim3(n_q, bm.n_seqs), 256, 0, s>>>(                          \
+        (const TT*)qkv, (TT*)out, n_q, n_kv, bm, rope_table, (TT*)kv.k_pool, (TT*)kv.v_pool, scale)
 #define SS_GO(TT, DD)                                                                                       \
-    if (one)                                                                                                \
-        attn_generic_decode_kernel<TT, DD><<<dim3(n_q, bm.n_seqs), 256, 0, s>>>(                            \
-            (const TT*)qkv, (TT*)out, n_q, n_kv, bm, rope_table, (TT*)kv.k_pool, (TT*)kv.v_pool, scale);    \
+    if (one && rope_table)                                                                                  \
+        SS_ONE(TT, 64, true, true);                                                                         \
+    else if (one && ahead)                                                                                  \
+        SS_ONE(TT, DD, false, true);                                                                        \
+    else if (one)                                                                                           \
+        SS_ONE(TT, DD, false, false);                                                                            \
     else                                                                                                    \
         attn_generic_kernel<TT, DD><<<grid, 256, 0, s>>>((const TT*)qkv, (TT*)out, n_q, n_kv, bm,           \
                                                          (const TT*)kv.k_pool, (const TT*)kv.v_pool, scale)
@@ -277,6 +304,7 @@ hipError_t attn_generic(int dt, const void* qkv, void* out, int n_q, int n_kv, c
         if (kv.d == 64) { SS_GO(bf16_t, 64); } else { SS_GO(bf16_t, 128); }
     }
 #undef SS_GO
+#undef SS_ONE
     return hipGetLastError();
 }
 

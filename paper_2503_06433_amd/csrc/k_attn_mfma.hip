@@ -821,15 +821,28 @@ __global__ __launch_bounds__(D / 4 * HB) void attn_decode_merge_kernel(const flo
     *reinterpret_cast<vec8*>(out + (size_t)bm.cu_q[sq] * ((size_t)n_q * D) + (size_t)a * D + e) = w;
 }
 
+static bool decode_mfma(int dt, int n_q, int n_kv, int d, bool force_generic) {
+    return dt == BF16 && !force_generic && d == 128 && n_kv > 0 && n_q / n_kv <= 16;
+}
+
+// The plain kernel rotates where the launch saved is worth the registers that the rotation takes (fp32 148 in place of 94 or 128):
+// heads of 64 and few blocks, that is n_q * n_seqs.  Layer call with / without, 16 heads: fp32, 32 sequences of 40 tokens 27.2
+// / 28.4 us, 64 37.3 / 35.1, 256 of 8 tokens 80 / 65; 16-bit, 64 of 40 25.2 / 26.8, 128 37.3 / 34.5, 512 72 / 54; the tiny fp32
+// model's run of four prompts and eight tokens 494 / 522.  Heads of 128 need 256 registers and more with it: 32 heads over one, 256
+// sequences of 40 tokens 165 / 64, and at 1 to 8 sequences no gain either.
+bool attn_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs, bool force_generic) {
+    return decode_mfma(dt, n_q, n_kv, d, force_generic) || (d == 64 && (long long)n_q * n_seqs <= (dt == F32 ? 512 : 1024));
+}
+
 size_t attn_decode_scratch_floats(int n_items, int n_q, int d) { return (size_t)n_items * n_q * (d + 4); }
 
 hipError_t attn_decode(int dt, const void* qkv, void* out, int n_q, int n_kv, const BatchMeta& bm,
                        const KvLayer& kv, const DecodeWork& wk, const float* rope_table, float* scratch, bool force_generic,
                        hipStream_t s) {
     if (bm.n_seqs <= 0) return hipSuccess;
-    if (n_kv <= 0 || n_q % n_kv != 0 || !rope_table) return hipErrorInvalidValue;
-    const int G = n_q / n_kv;
-    if (dt != BF16 || force_generic || kv.d != 128 || G > 16) return attn_generic(dt, qkv, out, n_q, n_kv, bm, kv, rope_table, s);
+    if (n_kv <= 0 || n_q % n_kv != 0) return hipErrorInvalidValue;
+    if ((rope_table != nullptr) != attn_decode_rotates(dt, n_q, n_kv, kv.d, bm.n_seqs, force_generic)) return hipErrorInvalidValue;
+    if (!decode_mfma(dt, n_q, n_kv, kv.d, force_generic)) return attn_generic(dt, qkv, out, n_q, n_kv, bm, kv, rope_table, s);
     if (kv.page_size != 16 || kv.n_heads != n_kv || !scratch || wk.n_items <= 0) return hipErrorInvalidValue;
     if (n_kv > 65535 || bm.n_seqs > 65535) return hipErrorInvalidValue;
     const float sl2 = 1.4426950408889634f / sqrtf((float)kv.d);
@@ -844,3 +857,8 @@ hipError_t attn_decode(int dt, const void* qkv, void* out, int n_q, int n_kv, co
 }
 
 }  // namespace SS_NS
+
+// for the tests of the dispatch
+#ifndef SS_HALF_F16
+extern "C" int ssk_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs) { return ssk::attn_decode_rotates(dt, n_q, n_kv, d, n_seqs, false); }
+#endif

@@ -190,8 +190,11 @@ hipError_t attn_prefill(int dt, const void* qkv, void* out, int n_q, int n_kv,
 
 size_t attn_decode_scratch_floats(int n_items, int n_q, int d);
 
-// One new token per sequence: rotates its q and k, writes k and v into the token's page, attends to the cache with it.
-// qkv is as the products leave it (rope_kvwrite has not run) and stays that way.
+// Whether attn_decode takes the new tokens as the products leave them (else rope_kvwrite has to run in front of it).
+bool attn_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs, bool force_generic);
+
+// One new token per sequence.  With a rope_table, which it wants exactly where attn_decode_rotates says so: rotates its q and k,
+// writes k and v into the token's page, attends to the cache with it; qkv is left as it is.  Without: attends to the cache.
 hipError_t attn_decode(int dt, const void* qkv, void* out, int n_q, int n_kv,
                        const BatchMeta& bm, const KvLayer& kv, const DecodeWork& wk, const float* rope_table,
                        float* scratch, bool force_generic, hipStream_t s);

@@ -934,15 +934,16 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     // the product does not read the batch's metadata, what comes behind it does
     if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, rs, ws, st, ms->pending ? ms->job : ssk::UploadJob()))) return rc;
     ms->pending = false;
+    const bool rotates = decode && SSK_CALL(c, attn_decode_rotates, s->nq_l, s->nkv_l, d, ms->bm.n_seqs, c->force_generic);
+    if (!rotates) {
+        ProfScope ps(c, 4, st);
+        K_TRY(c, SSK_CALL(c, rope_kvwrite, c->ws_qkv.p, s->nq_l, s->nkv_l, c->d_rope, ms->bm, kv, st));
+    }
     if (decode) {
         ProfScope ps(c, 2, st);
-        K_TRY(c, SSK_CALL(c, attn_decode, c->ws_qkv.p, c->ws_attn.p, s->nq_l, s->nkv_l, ms->bm, kv, ms->wk, c->d_rope,
-                                  (float*)c->ws_scratch.p, c->force_generic, st));
+        K_TRY(c, SSK_CALL(c, attn_decode, c->ws_qkv.p, c->ws_attn.p, s->nq_l, s->nkv_l, ms->bm, kv, ms->wk,
+                                  rotates ? c->d_rope : nullptr, (float*)c->ws_scratch.p, c->force_generic, st));
     } else {
-        {
-            ProfScope ps(c, 4, st);
-            K_TRY(c, SSK_CALL(c, rope_kvwrite, c->ws_qkv.p, s->nq_l, s->nkv_l, c->d_rope, ms->bm, kv, st));
-        }
         ProfScope ps(c, 1, st);
         K_TRY(c, SSK_CALL(c, attn_prefill, c->ws_qkv.p, c->ws_attn.p, s->nq_l, s->nkv_l, ms->bm, kv,
                                    c->force_generic, st));

@@ -129,6 +129,17 @@ def test_a_cut_product_keeps_whole_tiles_and_whole_rounds(rows, cus):
             assert c == n or (0 < c < n and c % 256 == 0 and tiles_m * c // 256 <= tiles_m * -(-n // 256) // cus * cus)
 
 
+@pytest.mark.parametrize("dt,heads,d,seqs,rotates", [
+    (F32, 4, 64, 128, True), (F32, 16, 64, 32, True), (F32, 16, 64, 33, False), (F32, 16, 64, 1024, False),
+    (BF16, 16, 64, 64, True), (BF16, 16, 64, 65, False), (F32, 8, 128, 1, False), (BF16, 32, 128, 1, False), (BF16, 32, 128, 256, False),
+])
+def test_the_plain_decode_kernel_rotates_for_few_blocks_only(dt, heads, d, seqs, rotates):
+    f = C.CDLL(_library()).ssk_decode_rotates
+    f.argtypes = [C.c_int] * 5
+    assert bool(f(dt, heads, 1, d, seqs) & 1) == rotates
+    assert f(BF16, 16, 1, 128, seqs) & 1                          # the matrix-core kernel always does
+
+
 @pytest.mark.parametrize("n,k", [(5120, 5120), (5120, 8192), (5120, 6912), (6912, 5120)])
 def test_one_row_of_tiles_takes_64_x_64(n, k):
     assert plan(96, n, k, EPI_RESIDUAL)[:2] == plan(97, n, k, EPI_RESIDUAL)[:2] == (TILE, 1)
