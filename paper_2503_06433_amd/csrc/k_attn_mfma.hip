@@ -539,7 +539,8 @@ hipError_t attn_prefill(int dt, const void* qkv, void* out, int n_q, int n_kv, c
 // Partial (max, sum, O) of every item go to scratch and are merged per sequence.
 // scratch layout: float [n_items][n_q][D + 4]  (O[D], running max, running sum)
 // ======================================================================
-template <int D>
+// ROPE false: the new tokens are rotated and in their pages (attn_decode_rotates).
+template <int D, bool ROPE>
 __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __restrict__ qkv, int n_q, int n_kv,
                                                               BatchMeta bm, DecodeWork wk, const float* __restrict__ rope,
                                                               const bf16_t* __restrict__ k_pool,
@@ -555,6 +556,7 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
     const int page0 = wk.item_page0[item], npg = wk.item_npages[item] & 0xffff;
     const int stride = (wk.item_npages[item] >> 16) > 0 ? (wk.item_npages[item] >> 16) : 1;
     const int n_old = bm.kv_before[sq];                  // cached tokens; the new one has this position
+    const int n_page = ROPE ? n_old : n_old + 1;         // tokens to take from the pages
     const int lane = threadIdx.x;
     const int lq = lane & 15, g4 = lane >> 4;
     const size_t row_stride = (size_t)(n_q + 2 * n_kv) * D;
@@ -568,6 +570,31 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
     } else {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[ks].w[0] = qf[ks].w[1] = qf[ks].w[2] = qf[ks].w[3] = 0u;
+    }
+    // cos / sin of this lane's element pairs: k-steps ks and ks + 2 hold the two halves
+    float cs[KS / 2][16];
+    if constexpr (ROPE) {
+        const float* rp = rope + (size_t)n_old * D + 16 * g4;             // [D / 2][2] = cos, sin of the new token's position
+#pragma unroll
+        for (int h = 0; h < KS / 2; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(rp + 64 * h + 4 * j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) cs[h][4 * j + e] = v[e];
+            }
+    }
+    // the wave whose item has the new token's page: its key and value
+    const int past0 = n_old / 16 - page0;
+    const bool fresh = ROPE && past0 >= 0 && past0 % stride == 0 && past0 / stride < npg;
+    Frag kf[KS];
+    vec8 vn[DT];
+    if (fresh) {
+        const bf16_t* kn = tok + (size_t)(n_q + g) * D;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kf[ks].q = *reinterpret_cast<const vec16*>(kn + ks * 32 + g4 * 8);
+#pragma unroll
+        for (int t = 0; t < DT; ++t) vn[t] = *reinterpret_cast<const vec8*>(kn + (size_t)n_kv * D + t * 16 + 4 * g4);
     }
     f32x4_t o[DT];
 #pragma unroll
@@ -621,8 +648,8 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
         float mx = m;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            sA[v] = (there && pos0 + v < n_old) ? sA[v] * scale_log2e : -INFINITY;
-            sB[v] = (there && pos0 + 8 + v < n_old) ? sB[v] * scale_log2e : -INFINITY;
+            sA[v] = (there && pos0 + v < n_page) ? sA[v] * scale_log2e : -INFINITY;
+            sB[v] = (there && pos0 + 8 + v < n_page) ? sB[v] * scale_log2e : -INFINITY;
             mx = fmaxf(mx, fmaxf(sA[v], sB[v]));
         }
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
@@ -640,11 +667,11 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
         l = l * alpha + rs;
         // The page of the new token: its own slot and those behind it hold what the page's last user left.  Weight 0 would
         // not keep a value that is not finite out of the sums; nor one of a page that is only repeated.
-        if ((page0 + (pi + 1) * stride) * 16 + 16 > n_old || !hasB) {
+        if ((page0 + (pi + 1) * stride) * 16 + 16 > n_page || !hasB) {
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
                 const int p = pos0 + 2 * (w & 1) + 8 * (w >> 1);
-                const uint32_t keep = there ? (p < n_old ? 0xffffu : 0u) | (p + 1 < n_old ? 0xffff0000u : 0u) : 0u;
+                const uint32_t keep = there ? (p < n_page ? 0xffffu : 0u) | (p + 1 < n_page ? 0xffff0000u : 0u) : 0u;
 #pragma unroll
                 for (int t = 0; t < DT; ++t) vf[t].w[w] &= keep;
             }
@@ -667,19 +694,6 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
     pair_pages(0, pA, pB);
     Frag k0a[KS], k0b[KS], k1a[KS], k1b[KS];
     load_k(pA, pB, k0a, k0b);
-    // cos / sin of this lane's element pairs: k-steps ks and ks + 2 hold the two halves
-    float cs[KS / 2][16];
-    {
-        const float* rp = rope + (size_t)n_old * D + 16 * g4;             // [D / 2][2] = cos, sin of the new token's position
-#pragma unroll
-        for (int h = 0; h < KS / 2; ++h)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(rp + 64 * h + 4 * j);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) cs[h][4 * j + e] = v[e];
-            }
-    }
     auto rotate = [&](Frag* f) {
 #pragma unroll
         for (int h = 0; h < KS / 2; ++h)
@@ -694,20 +708,14 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
                 f[h + 2].w[j] = pack_bf16x2(r[2], r[3]);
             }
     };
-    rotate(qf);
-    // The new token is the first term of the wave whose item has its page, taken from registers: weight 1 at its own score.
-    const int past0 = n_old / 16 - page0;
-    if (past0 >= 0 && past0 % stride == 0 && past0 / stride < npg) {
-        const bf16_t *kn = tok + (size_t)(n_q + g) * D, *vn = kn + (size_t)n_kv * D;
-        Frag kf[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) kf[ks].q = *reinterpret_cast<const vec16*>(kn + ks * 32 + g4 * 8);
+    if constexpr (ROPE) rotate(qf);
+    // The new token is the first term of the wave that has its page, taken from registers: weight 1 at its own score.
+    if (fresh) {
 #pragma unroll
         for (int t = 0; t < DT; ++t) {
-            const vec8 v = *reinterpret_cast<const vec8*>(vn + t * 16 + 4 * g4);
             float x[4];
-            unpack_bf16x2(v.w[0], x[0], x[1]);
-            unpack_bf16x2(v.w[1], x[2], x[3]);
+            unpack_bf16x2(vn[t].w[0], x[0], x[1]);
+            unpack_bf16x2(vn[t].w[1], x[2], x[3]);
             o[t] = f32x4_t{x[0], x[1], x[2], x[3]};
         }
         rotate(kf);
@@ -830,8 +838,17 @@ static bool decode_mfma(int dt, int n_q, int n_kv, int d, bool force_generic) {
 // / 28.4 us, 64 37.3 / 35.1, 256 of 8 tokens 80 / 65; 16-bit, 64 of 40 25.2 / 26.8, 128 37.3 / 34.5, 512 72 / 54; the tiny fp32
 // model's run of four prompts and eight tokens 494 / 522.  Heads of 128 need 256 registers and more with it: 32 heads over one, 256
 // sequences of 40 tokens 165 / 64, and at 1 to 8 sequences no gain either.
-bool attn_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs, bool force_generic) {
-    return decode_mfma(dt, n_q, n_kv, d, force_generic) || (d == 64 && (long long)n_q * n_seqs <= (dt == F32 ? 512 : 1024));
+// The matrix-core kernel rotates but for batches of one query head per kv head with 4096 waves and more and about three pages a
+// sequence, or with more than 16384 waves and one page: there its waves are so short that the loads of cos / sin, of the new
+// key and value show.  Layer call with / without: 256 sequences of 8 / 40 / 100 tokens on 32 heads 112 / 107 us, 130.6 / 128.5,
+// 166 / 172; 512 of 40 on 10 heads 109 / 106; 1024 of 24 on 40 heads 402 / 418; 64 of 40 on 32 heads 65.4 / 67.7; 512 of 40 with
+// four query heads each on 8 113 either way.
+bool attn_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs, long long pages, bool force_generic) {
+    if (decode_mfma(dt, n_q, n_kv, d, force_generic)) {
+        const long long waves = (long long)n_seqs * n_kv;
+        return n_q != n_kv || waves < 4096 || 2 * pages > (waves <= 16384 ? 7 : 2) * (long long)n_seqs;
+    }
+    return d == 64 && (long long)n_q * n_seqs <= (dt == F32 ? 512 : 1024);
 }
 
 size_t attn_decode_scratch_floats(int n_items, int n_q, int d) { return (size_t)n_items * n_q * (d + 4); }
@@ -841,16 +858,16 @@ hipError_t attn_decode(int dt, const void* qkv, void* out, int n_q, int n_kv, co
                        hipStream_t s) {
     if (bm.n_seqs <= 0) return hipSuccess;
     if (n_kv <= 0 || n_q % n_kv != 0) return hipErrorInvalidValue;
-    if ((rope_table != nullptr) != attn_decode_rotates(dt, n_q, n_kv, kv.d, bm.n_seqs, force_generic)) return hipErrorInvalidValue;
     if (!decode_mfma(dt, n_q, n_kv, kv.d, force_generic)) return attn_generic(dt, qkv, out, n_q, n_kv, bm, kv, rope_table, s);
     if (kv.page_size != 16 || kv.n_heads != n_kv || !scratch || wk.n_items <= 0) return hipErrorInvalidValue;
     if (n_kv > 65535 || bm.n_seqs > 65535) return hipErrorInvalidValue;
     const float sl2 = 1.4426950408889634f / sqrtf((float)kv.d);
     if ((long long)wk.n_items * n_kv > 0x7fffffffll) return hipErrorInvalidValue;
     dim3 grid((unsigned)(wk.n_items * n_kv));
-    attn_decode_mfma_kernel<128><<<grid, 64, 0, s>>>((const bf16_t*)qkv, n_q, n_kv, bm, wk, rope_table,
-                                                     (const bf16_t*)kv.k_pool, (const bf16_t*)kv.v_pool, scratch, sl2);
-    dim3 mgrid((n_q + 7) / 8 + (n_kv + 7) / 8, bm.n_seqs);
+    const auto kernel = rope_table ? attn_decode_mfma_kernel<128, true> : attn_decode_mfma_kernel<128, false>;
+    kernel<<<grid, 64, 0, s>>>((const bf16_t*)qkv, n_q, n_kv, bm, wk, rope_table, (const bf16_t*)kv.k_pool, (const bf16_t*)kv.v_pool,
+                               scratch, sl2);
+    dim3 mgrid((n_q + 7) / 8 + (rope_table ? (n_kv + 7) / 8 : 0), bm.n_seqs);
     attn_decode_merge_kernel<128, 8><<<mgrid, 256, 0, s>>>(scratch, (bf16_t*)out, n_q, n_kv, bm, wk, (const bf16_t*)qkv, rope_table,
                                                          (bf16_t*)kv.k_pool, (bf16_t*)kv.v_pool);
     return hipGetLastError();
@@ -860,5 +877,7 @@ hipError_t attn_decode(int dt, const void* qkv, void* out, int n_q, int n_kv, co
 
 // for the tests of the dispatch
 #ifndef SS_HALF_F16
-extern "C" int ssk_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs) { return ssk::attn_decode_rotates(dt, n_q, n_kv, d, n_seqs, false); }
+extern "C" bool ssk_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs, long long pages) {
+    return ssk::attn_decode_rotates(dt, n_q, n_kv, d, n_seqs, pages, false);
+}
 #endif

@@ -85,6 +85,7 @@ struct DecodeWork {
     const int32_t* item_order;  // [n_items] launch order (block x works on item item_order[x])
     int n_items;
     int max_items_per_seq;
+    long long n_pages;          // of all sequences
 };
 
 // Metadata of a batch on its way from page-locked memory (its device address) to the device: 16-byte pieces that the first
@@ -190,11 +191,12 @@ hipError_t attn_prefill(int dt, const void* qkv, void* out, int n_q, int n_kv,
 
 size_t attn_decode_scratch_floats(int n_items, int n_q, int d);
 
-// Whether attn_decode takes the new tokens as the products leave them (else rope_kvwrite has to run in front of it).
-bool attn_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs, bool force_generic);
+// Whether attn_decode is to take the new tokens as the products leave them (else rope_kvwrite runs in front of it).  `pages`: of
+// all sequences together, the new tokens' included.
+bool attn_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs, long long pages, bool force_generic);
 
-// One new token per sequence.  With a rope_table, which it wants exactly where attn_decode_rotates says so: rotates its q and k,
-// writes k and v into the token's page, attends to the cache with it; qkv is left as it is.  Without: attends to the cache.
+// One new token per sequence.  With a rope_table: rotates its q and k, writes k and v into the token's page, attends to the cache
+// with it; qkv is left as it is.  Without one: attends to the cache, which has it.
 hipError_t attn_decode(int dt, const void* qkv, void* out, int n_q, int n_kv,
                        const BatchMeta& bm, const KvLayer& kv, const DecodeWork& wk, const float* rope_table,
                        float* scratch, bool force_generic, hipStream_t s);

@@ -642,9 +642,9 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
     // decode work items
     std::vector<int32_t> item_seq, item_page0, item_np, seq_item0;
     int max_items = 0;
+    int64_t total_pages = 0;
     if (items) {
         seq_item0.resize(n + 1);
-        int64_t total_pages = 0;
         for (int i = 0; i < n; ++i) total_pages += (b->kv_lens_before[i] + 1 + c->m.page_size - 1) / c->m.page_size;
         const int ipp = decode_item_pages(total_pages, s->nkv_l);
         for (int i = 0; i < n; ++i) {
@@ -845,6 +845,7 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
     ms.wk.item_order = (const int32_t*)(ms.dev + off_iord);
     ms.wk.n_items = (int)n_items;
     ms.wk.max_items_per_seq = max_items;
+    ms.wk.n_pages = total_pages;
     ms.shard = s;
     ms.version = s->version;
     ms.decode = decode;
@@ -934,7 +935,7 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     // the product does not read the batch's metadata, what comes behind it does
     if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, rs, ws, st, ms->pending ? ms->job : ssk::UploadJob()))) return rc;
     ms->pending = false;
-    const bool rotates = decode && SSK_CALL(c, attn_decode_rotates, s->nq_l, s->nkv_l, d, ms->bm.n_seqs, c->force_generic);
+    const bool rotates = decode && SSK_CALL(c, attn_decode_rotates, s->nq_l, s->nkv_l, d, ms->bm.n_seqs, ms->wk.n_pages, c->force_generic);
     if (!rotates) {
         ProfScope ps(c, 4, st);
         K_TRY(c, SSK_CALL(c, rope_kvwrite, c->ws_qkv.p, s->nq_l, s->nkv_l, c->d_rope, ms->bm, kv, st));

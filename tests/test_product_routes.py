@@ -129,15 +129,20 @@ def test_a_cut_product_keeps_whole_tiles_and_whole_rounds(rows, cus):
             assert c == n or (0 < c < n and c % 256 == 0 and tiles_m * c // 256 <= tiles_m * -(-n // 256) // cus * cus)
 
 
-@pytest.mark.parametrize("dt,heads,d,seqs,rotates", [
-    (F32, 4, 64, 128, True), (F32, 16, 64, 32, True), (F32, 16, 64, 33, False), (F32, 16, 64, 1024, False),
-    (BF16, 16, 64, 64, True), (BF16, 16, 64, 65, False), (F32, 8, 128, 1, False), (BF16, 32, 128, 1, False), (BF16, 32, 128, 256, False),
+@pytest.mark.parametrize("dt,heads,kv_heads,d,seqs,pages,rotates", [
+    # the plain kernel: few blocks of 64-wide heads only
+    (F32, 4, 1, 64, 128, 400, True), (F32, 16, 16, 64, 32, 32, True), (F32, 16, 16, 64, 33, 3300, False), (F32, 16, 1, 64, 1024, 2048, False),
+    (BF16, 16, 4, 64, 64, 64, True), (BF16, 16, 4, 64, 65, 6500, False), (F32, 8, 8, 128, 1, 1, False), (BF16, 32, 1, 128, 1, 9, False),
+    (BF16, 32, 1, 128, 256, 5000, False),
+    # the matrix-core kernel: all but many short sequences of ungrouped heads
+    (BF16, 32, 32, 128, 1, 1, True), (BF16, 32, 32, 128, 127, 127, True), (BF16, 32, 32, 128, 128, 448, False), (BF16, 32, 32, 128, 128, 449, True),
+    (BF16, 32, 32, 128, 512, 1792, False), (BF16, 32, 32, 128, 513, 514, True), (BF16, 32, 32, 128, 1024, 1024, False),
+    (BF16, 64, 8, 128, 1024, 1024, True),
 ])
-def test_the_plain_decode_kernel_rotates_for_few_blocks_only(dt, heads, d, seqs, rotates):
+def test_where_decode_attention_rotates_by_itself(dt, heads, kv_heads, d, seqs, pages, rotates):
     f = C.CDLL(_library()).ssk_decode_rotates
-    f.argtypes = [C.c_int] * 5
-    assert bool(f(dt, heads, 1, d, seqs) & 1) == rotates
-    assert f(BF16, 16, 1, 128, seqs) & 1                          # the matrix-core kernel always does
+    f.argtypes, f.restype = [C.c_int] * 5 + [C.c_longlong], C.c_bool
+    assert f(dt, heads, kv_heads, d, seqs, pages) == rotates
 
 
 @pytest.mark.parametrize("n,k", [(5120, 5120), (5120, 8192), (5120, 6912), (6912, 5120)])
