@@ -163,10 +163,8 @@ __global__ __launch_bounds__(256) void attn_generic_decode_kernel(const T* __res
                 unpack16<T>(other[i], o);
 #pragma unroll
                 for (int e = 0; e < EV; ++e) {
-                    // rope_rotate's half that this lane has: the first quarters subtract the other half, the last add it
-                    const float other = sub < 2 ? -o[e] : o[e];
                     T st;
-                    stf(&st, fmaf(f[i * EV + e], cs[2 * (i * EV + e)], other * cs[2 * (i * EV + e) + 1]));
+                    stf(&st, rope_half(f[i * EV + e], sub < 2 ? -o[e] : o[e], cs[2 * (i * EV + e)], cs[2 * (i * EV + e) + 1]));
                     f[i * EV + e] = ldf(&st);
                 }
             }

@@ -704,8 +704,8 @@ __global__ __launch_bounds__(64) void attn_decode_mfma_kernel(const bf16_t* __re
                 unpack_bf16x2(f[h + 2].w[j], x[2], x[3]);
 #pragma unroll
                 for (int e = 0; e < 2; ++e) rope_rotate(x[e], x[2 + e], cs[h][4 * j + 2 * e], cs[h][4 * j + 2 * e + 1], r[e], r[2 + e]);
-                f[h].w[j] = pack_bf16x2(r[0], r[1]);
-                f[h + 2].w[j] = pack_bf16x2(r[2], r[3]);
+                f[h].w[j] = pack_rotated(r[0], r[1]);
+                f[h + 2].w[j] = pack_rotated(r[2], r[3]);
             }
     };
     if constexpr (ROPE) rotate(qf);
@@ -766,21 +766,20 @@ __global__ __launch_bounds__(D / 4 * HB) void attn_decode_merge_kernel(const flo
         const bf16_t* kn = qkv + (size_t)bm.cu_q[sq] * ((size_t)(n_q + 2 * n_kv) * D) + (size_t)(n_q + g) * D;
         const bf16_t* vn = kn + (size_t)n_kv * D;
         const size_t page = ((size_t)bm.page_tables[(size_t)sq * bm.pt_stride + pos / 16] * n_kv + g) * 16 * D;
-        const int i0 = e % (D / 2);                  // both halves' threads form the pair and keep their own
+        const int i0 = e % (D / 2);
         const f32x4_t c0 = *reinterpret_cast<const f32x4_t*>(rope + (size_t)pos * D + 2 * i0);
         const f32x4_t c1 = *reinterpret_cast<const f32x4_t*>(rope + (size_t)pos * D + 2 * i0 + 4);
-        const vec8 lo = *reinterpret_cast<const vec8*>(kn + i0), hi = *reinterpret_cast<const vec8*>(kn + i0 + D / 2);
+        const bool first = e < D / 2;
+        const vec8 own = *reinterpret_cast<const vec8*>(kn + e), other = *reinterpret_cast<const vec8*>(kn + (first ? e + D / 2 : i0));
         const vec8 v = *reinterpret_cast<const vec8*>(vn + e);
         vec8 k;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            float x[4], r[4];
-            unpack_bf16x2(lo.w[j], x[0], x[1]);
-            unpack_bf16x2(hi.w[j], x[2], x[3]);
+            float x[2], o[2];
+            unpack_bf16x2(own.w[j], x[0], x[1]);
+            unpack_bf16x2(other.w[j], o[0], o[1]);
             const f32x4_t c = j ? c1 : c0;
-            rope_rotate(x[0], x[2], c[0], c[1], r[0], r[2]);
-            rope_rotate(x[1], x[3], c[2], c[3], r[1], r[3]);
-            k.w[j] = e < D / 2 ? pack_bf16x2(r[0], r[1]) : pack_bf16x2(r[2], r[3]);
+            k.w[j] = pack_rotated(rope_half(x[0], first ? -o[0] : o[0], c[0], c[1]), rope_half(x[1], first ? -o[1] : o[1], c[2], c[3]));
         }
         *reinterpret_cast<vec8*>(k_pool + page + slot * D + e) = k;
 #pragma unroll

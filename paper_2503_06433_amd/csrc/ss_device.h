@@ -122,11 +122,23 @@ __device__ __forceinline__ int vslot(int s) { return (s & 3) | ((s & 4) << 1) | 
 __device__ __forceinline__ int vpos(int s, int e) { return vslot(s) ^ (e & 8); }
 __device__ __forceinline__ int vtok(int p, int e) { return vslot(p ^ (e & 8)); }
 
-// The rotation of one element pair (i, i + d / 2) of a head.  One definition, and no contraction left to the compiler: the
-// kernels that write a token's key into its page store the same bits.
+// One element of a rotated head: `other` is the element half a head away, negated for the first half.  One definition, no
+// contraction left to the compiler, and one way of rounding it to storage, pack_rotated or stf right behind it: the kernels
+// that write a token's key into its page, and those that attend to it from registers, have the same bits.
+__device__ __forceinline__ float rope_half(float own, float other, float c, float s) { return fmaf(own, c, other * s); }
 __device__ __forceinline__ void rope_rotate(float lo, float hi, float c, float s, float& olo, float& ohi) {
-    olo = fmaf(lo, c, -(hi * s));
-    ohi = fmaf(hi, c, lo * s);
+    olo = rope_half(lo, -hi, c, s);
+    ohi = rope_half(hi, lo, c, s);
+}
+
+// Half: value by value, which the machine rounds together with the sum (v_fma_mixlo_f16); the packed conversion, or a choice
+// between two sums in front of it, would round to fp32 first, one place off on a tie.
+__device__ __forceinline__ uint32_t pack_rotated(float lo, float hi) {
+#ifdef SS_HALF_F16
+    return (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16);
+#else
+    return pack_bf16x2(lo, hi);
+#endif
 }
 
 // pieces first, first + step, ... of `n` from page-locked host memory: a few requests of a thread cross the link together

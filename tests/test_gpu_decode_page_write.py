@@ -1,6 +1,6 @@
 """Decode attention rotates the new token and writes its page by itself; a prefill call of one token does it in a kernel of
-its own.  Both leave the same bits in the cache (IEEE half: but for ties, see below) and agree on the output, for cached lengths around page edges, page pairs
-and the lengths at which a sequence gets a second and third work item."""
+its own.  Both leave the same bits in the cache and agree on the output, for cached lengths around page edges, page pairs and the
+lengths at which a sequence gets a second and third work item."""
 import numpy as np
 import pytest
 import torch
@@ -27,6 +27,8 @@ LENS = [0, 1, 14, 15, 16, 17, 31, 32, 33, 47, 48, 63, 64, 255, 256, 257, 300, 51
     (wl.F32, 32, 2, 64, LENS),         # so many heads that a kernel of its own rotates and writes for the plain one
     (wl.BF16, 64, 4, 64, LENS),
     (wl.F16, 64, 1, 128, LENS),
+    (wl.F16, 8, 8, 64, LENS),
+    (wl.F16, 16, 16, 128, LENS),       # two thousand key values a token: some land on a tie
     (wl.F32, 80, 2, 64, LENS[:10]),      # no sequence of more than four pages
     (wl.F32, 8, 2, 128, LENS[:10]),
     (wl.BF16, 32, 32, 128, [0] + [1 + i % 40 for i in range(127)]),      # so many waves of few pages that a kernel of its own does it for both
@@ -54,11 +56,5 @@ def test_decode_leaves_the_cache_of_a_one_token_prefill(dtype, nq, nkv, d, lens)
     for i, n in enumerate(lens):
         assert caches[0][i].shape[2] == n + 1
         a, b = (c[i] if dtype == wl.F32 else c[i].astype(np.int32) for c in caches)
-        if dtype == wl.F16:
-            # The machine can round a rotated key to half at once or by way of fp32, which the compiler chooses per kernel.  They
-            # differ by one place where fp32 lands on a tie: one value in 2^13 (13 bits are dropped), a token has up to 256 of them here.
-            same = a == b
-            assert np.abs(a - b).max() <= 1 and same[1].all() and (~same)[:, :, :n].sum() == 0 and (~same).sum() <= 3, "%d cached tokens" % n
-        else:
-            assert np.array_equal(a, b), "%d cached tokens" % n
+        assert np.array_equal(a, b), "%d cached tokens" % n
     parity(outs[0], outs[1], dtype, "decode against a one-token prefill, %d heads over %d of %d" % (nq, nkv, d))
