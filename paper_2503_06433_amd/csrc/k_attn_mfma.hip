@@ -153,26 +153,33 @@ __global__ __launch_bounds__(256) void attn_prefill_mfma_kernel(const bf16_t* __
         const int vhalf = g2 ^ ((lq >> 3) & 1);
         const bf16_t* vA = v_pool + (size_t)pA * page_elems + head_off + (size_t)lq * 16 + 8 * vhalf;
         const bf16_t* vB = v_pool + (size_t)pB * page_elems + head_off + (size_t)lq * 16 + 8 * vhalf;
+        Frag va[DT], vb[DT];
 #pragma unroll
         for (int u = 0; u < DT; ++u) {
-            Frag va, vb;
-            va.q = *reinterpret_cast<const vec16*>(vA + u * 32 * 16);
-            vb.q = *reinterpret_cast<const vec16*>(vB + u * 32 * 16);
-            // tokens behind the last one that the wave sees: what the page's last user left, or a page that is only repeated
-            if (t0 + 31 > before + last_q) {
+            va[u].q = *reinterpret_cast<const vec16*>(vA + u * 32 * 16);
+            vb[u].q = *reinterpret_cast<const vec16*>(vB + u * 32 * 16);
+        }
+        // tokens behind the last one that the wave sees: what the page's last user left, or a page that is only repeated
+        if (t0 + 31 > before + last_q) {
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const int at = t0 + 4 * g2 + 2 * (w & 1) + 8 * (w >> 1), seen = before + last_q;
-                    va.w[w] &= (at <= seen ? 0xffffu : 0u) | (at + 1 <= seen ? 0xffff0000u : 0u);
-                    vb.w[w] &= (at + 16 <= seen ? 0xffffu : 0u) | (at + 17 <= seen ? 0xffff0000u : 0u);
+            for (int w = 0; w < 4; ++w) {
+                const int at = t0 + 4 * g2 + 2 * (w & 1) + 8 * (w >> 1), seen = before + last_q;
+                const uint32_t ka = (at <= seen ? 0xffffu : 0u) | (at + 1 <= seen ? 0xffff0000u : 0u);
+                const uint32_t kb = (at + 16 <= seen ? 0xffffu : 0u) | (at + 17 <= seen ? 0xffff0000u : 0u);
+#pragma unroll
+                for (int u = 0; u < DT; ++u) {
+                    va[u].w[w] &= ka;
+                    vb[u].w[w] &= kb;
                 }
             }
+        }
+#pragma unroll
+        for (int u = 0; u < DT; ++u)
 #pragma unroll
             for (int t = 0; t < QT; ++t) {
-                o[t][u] = SS_MFMA_32x32x16(va.v, pfA[t].v, o[t][u], 0, 0, 0);
-                o[t][u] = SS_MFMA_32x32x16(vb.v, pfB[t].v, o[t][u], 0, 0, 0);
+                o[t][u] = SS_MFMA_32x32x16(va[u].v, pfA[t].v, o[t][u], 0, 0, 0);
+                o[t][u] = SS_MFMA_32x32x16(vb[u].v, pfB[t].v, o[t][u], 0, 0, 0);
             }
-        }
     }
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
