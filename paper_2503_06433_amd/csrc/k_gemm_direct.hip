@@ -84,7 +84,9 @@ template <> __device__ __forceinline__ u32x4_t pack_row<bf16_t>(const float* x) 
 
 }  // namespace
 
-constexpr int EPI_HEAD = 100;      // internal: EPI_STORE_F32 of rows that are scaled by `gain`, column by column, on their way in
+// internal kinds
+constexpr int EPI_HEAD = 100;      // EPI_STORE_F32 of rows that are scaled by `gain`, column by column, on their way in
+constexpr int EPI_UPLOAD = 101;    // EPI_STORE that takes a batch's metadata along
 
 // EPI_HEAD: final norm and LM head in one launch.  The rows meet their gains in registers, in the order they are loaded in, and
 // are rounded once to the storage type like the separate norm's result, but before the row's factor instead of behind it; the
@@ -111,10 +113,10 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(const T* __restrict
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lr = lane & 15, lg = lane >> 4;
-    // Plain products (the QKV projection): the first blocks of the first row of blocks take a batch's metadata along (UploadJob).
-    // Only there: the test alone, in front of the first loads, costs every launch 0.2 to 0.5 us.
+    // The QKV projection of a new batch: the first blocks of the first row of blocks take its metadata along (UploadJob).  A
+    // kernel of its own: the test alone, in front of the first loads, costs every launch 0.2 to 0.5 us.
     int bx = blockIdx.x;
-    if constexpr (EPI == EPI_STORE) {
+    if constexpr (EPI == EPI_UPLOAD) {
         if (bx < up_blocks) {
             if (blockIdx.y == 0) upload_pieces(up_src, up_dst, up_n, (int64_t)bx * (64 * W) + threadIdx.x, (int64_t)up_blocks * (64 * W));
             return;
@@ -401,7 +403,9 @@ static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C,
                                       (vec16*)job.dst, job.n16);                                               \
     }
     switch (epi) {
-        case EPI_STORE: SS_GO(EPI_STORE) break;
+        case EPI_STORE:
+            if (up) SS_GO(EPI_UPLOAD) else SS_GO(EPI_STORE)
+            break;
         case EPI_RESIDUAL:
             if (!R) return hipErrorInvalidValue;
             SS_GO(EPI_RESIDUAL) break;
