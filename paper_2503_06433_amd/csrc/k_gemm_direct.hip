@@ -402,18 +402,31 @@ static hipError_t launch_direct(const void* A, int lda, const void* Wt, void* C,
         kfn<<<grid, 64 * W, LDS, s>>>(a, lda, w, C, ldc, r, M, N, K, gate_blk, divide, norm_eps, (const T*)gain, vec_ok, up, (const vec16*)job.src, \
                                       (vec16*)job.dst, job.n16);                                               \
     }
-    switch (epi) {
-        case EPI_STORE:
-            if (up) SS_GO(EPI_UPLOAD) else SS_GO(EPI_STORE)
-            break;
-        case EPI_RESIDUAL:
-            if (!R) return hipErrorInvalidValue;
-            SS_GO(EPI_RESIDUAL) break;
-        case EPI_STORE_F32:
-            if (gain) SS_GO(EPI_HEAD) else SS_GO(EPI_STORE_F32)
-            break;
-        case EPI_SWIGLU: SS_GO(EPI_SWIGLU) break;
-        default: return hipErrorInvalidValue;
+    if constexpr (NT == 2 && W == 16) {                                      // pick_direct: SwiGLU only
+        if (epi != EPI_SWIGLU) return hipErrorInvalidValue;
+        SS_GO(EPI_SWIGLU)
+    } else {
+        switch (epi) {
+            case EPI_STORE:
+                if (up) SS_GO(EPI_UPLOAD) else SS_GO(EPI_STORE)
+                break;
+            case EPI_RESIDUAL:
+                if (!R) return hipErrorInvalidValue;
+                SS_GO(EPI_RESIDUAL) break;
+            case EPI_STORE_F32:
+                if (!gain) {
+                    SS_GO(EPI_STORE_F32)
+                } else {
+#ifdef SS_HALF_F16
+                    return hipErrorInvalidValue;                             // head_norms_itself: half keeps the norm apart
+#else
+                    SS_GO(EPI_HEAD)
+#endif
+                }
+                break;
+            case EPI_SWIGLU: SS_GO(EPI_SWIGLU) break;
+            default: return hipErrorInvalidValue;
+        }
     }
 #undef SS_GO
     return hipGetLastError();
