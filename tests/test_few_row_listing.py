@@ -1,5 +1,5 @@
 """Checks on the compiler's listing of the few-row products (CPU only: hipcc cross-compiles gfx950 here): the library holds the
-shapes that the dispatch can choose and no others."""
+shapes that the dispatch can choose and no others, and none of them keeps registers in memory."""
 import re
 import shutil
 import subprocess
@@ -41,3 +41,7 @@ def test_only_shapes_that_a_rule_can_choose(kernels):
         assert waves == 8 or (t, mt, waves, chunks) == ("t", 1, 16, 2) and (nt == 1 or (nt, epi) == (2, EPI_SWIGLU))
     for shape in {k[:5] for k in found if (k[2], k[3]) != (2, 16)}:
         assert {k[5] for k in found if k[:5] == shape} == {EPI_STORE, EPI_UPLOAD, EPI_RESIDUAL, EPI_SWIGLU, EPI_STORE_F32} | (set() if half else {EPI_HEAD})
+
+
+def test_no_kernel_spills(kernels):
+    assert {k: v for k, v in kernels[1].items() if v != 0} == {}
