@@ -44,12 +44,8 @@ struct KvLayer {
     int page_size;
 };
 
-// Per-token metadata of a batch (device arrays): tok_seq[t] = index of the
-// sequence inside the batch, tok_pos[t] = absolute position.  page_tables is
-// [n_seqs, pt_stride] int32.
+// Metadata of a batch (device arrays).  page_tables is [n_seqs, pt_stride] int32.
 struct BatchMeta {
-    const int32_t* tok_seq;
-    const int32_t* tok_pos;
     const int32_t* page_tables;
     int pt_stride;
     const int32_t* cu_q;        // [n_seqs+1] first token of each sequence in the batch
@@ -58,7 +54,8 @@ struct BatchMeta {
     int T;
     int max_q_len;
     // page units of the new tokens: unit u = the tokens of sequence unit_seq[u] that fall into one of its
-    // pages: batch tokens [unit_tok0[u], +unit_cnt[u]), absolute positions from unit_pos0[u]
+    // pages: batch tokens [unit_tok0[u], +unit_cnt[u]), absolute positions from unit_pos0[u].  None (n_units 0) where decode
+    // attention rotates and writes the new tokens itself.
     const int32_t* unit_seq;
     const int32_t* unit_tok0;
     const int32_t* unit_pos0;
@@ -85,7 +82,6 @@ struct DecodeWork {
     const int32_t* item_order;  // [n_items] launch order (block x works on item item_order[x])
     int n_items;
     int max_items_per_seq;
-    long long n_pages;          // of all sequences
 };
 
 // Metadata of a batch on its way from page-locked memory (its device address) to the device: 16-byte pieces that the first

@@ -97,6 +97,7 @@ struct MetaSlot {
     ssk::UploadJob job;                // host -> dev, taken along by the first launch that uses the slot
     bool pending = false;              // ... which has not been made yet
     bool repeats = false;              // decode batch that lists a sequence more than once: runs like a prefill batch
+    bool rotates = false;              // decode batch whose attention takes the new tokens as the products leave them
     // cache key
     Shard* shard = nullptr;
     uint64_t version = 0;
@@ -674,9 +675,10 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
         }
         seq_item0[n] = (int32_t)item_seq.size();
     }
-    // page units of the new tokens (for the RoPE + cache-write kernel)
+    // page units of the new tokens (for the RoPE + cache-write kernel, where it runs)
     std::vector<int32_t> unit_seq, unit_tok0, unit_pos0, unit_cnt;
-    {
+    ms.rotates = items && SSK_CALL(c, attn_decode_rotates, s->nq_l, s->nkv_l, c->m.head_dim, n, total_pages, c->force_generic);
+    if (!ms.rotates) {
         int t0 = 0;
         const int ps = c->m.page_size;
         for (int i = 0; i < n; ++i) {
@@ -761,9 +763,7 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
     for (size_t i = 0; i < n_items; ++i) item_order[i] = (int32_t)i;
     std::stable_sort(item_order.begin(), item_order.end(), [&](int32_t a, int32_t b2) { return (item_np[a] & 0xffff) > (item_np[b2] & 0xffff); });
     auto al = [](size_t x) { return (x + 63) & ~(size_t)63; };
-    size_t off_tok_seq = 0;
-    size_t off_tok_pos = off_tok_seq + al(4 * (size_t)T);
-    size_t off_cu = off_tok_pos + al(4 * (size_t)T);
+    size_t off_cu = 0;
     size_t off_before = off_cu + al(4 * (size_t)(n + 1));
     size_t off_pt = off_before + al(4 * (size_t)n);
     size_t off_iseq = off_pt + al(4 * (size_t)n * pt_stride);
@@ -784,8 +784,6 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
         HIP_TRY(c, hipHostMalloc((void**)&ms.host, ms.cap, hipHostMallocDefault));
         HIP_TRY(c, hipMalloc((void**)&ms.dev, ms.cap));
     }
-    int32_t* tok_seq = (int32_t*)(ms.host + off_tok_seq);
-    int32_t* tok_pos = (int32_t*)(ms.host + off_tok_pos);
     int32_t* cu = (int32_t*)(ms.host + off_cu);
     int32_t* before = (int32_t*)(ms.host + off_before);
     int32_t* pt = (int32_t*)(ms.host + off_pt);
@@ -793,10 +791,7 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
     for (int i = 0; i < n; ++i) {
         cu[i] = t;
         before[i] = b->kv_lens_before[i];
-        for (int j = 0; j < b->q_lens[i]; ++j, ++t) {
-            tok_seq[t] = i;
-            tok_pos[t] = b->kv_lens_before[i] + j;
-        }
+        t += b->q_lens[i];
         const auto& pg = sts[i]->pages;
         int32_t* row = pt + (size_t)i * pt_stride;
         std::copy(pg.begin(), pg.end(), row);
@@ -810,10 +805,12 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
         memcpy(ms.host + off_si0, seq_item0.data(), 4 * (size_t)(n + 1));
         memcpy(ms.host + off_iord, item_order.data(), 4 * n_items);
     }
-    memcpy(ms.host + off_useq, unit_seq.data(), 4 * n_units);
-    memcpy(ms.host + off_utok, unit_tok0.data(), 4 * n_units);
-    memcpy(ms.host + off_upos, unit_pos0.data(), 4 * n_units);
-    memcpy(ms.host + off_ucnt, unit_cnt.data(), 4 * n_units);
+    if (n_units) {
+        memcpy(ms.host + off_useq, unit_seq.data(), 4 * n_units);
+        memcpy(ms.host + off_utok, unit_tok0.data(), 4 * n_units);
+        memcpy(ms.host + off_upos, unit_pos0.data(), 4 * n_units);
+        memcpy(ms.host + off_ucnt, unit_cnt.data(), 4 * n_units);
+    }
     if (!pf_items.empty()) memcpy(ms.host + off_pf, pf_items.data(), 4 * pf_items.size());
     {
         void* mapped = nullptr;
@@ -821,8 +818,6 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
         ms.job = {mapped, ms.dev, (int64_t)(total / 16)};
         ms.pending = true;
     }
-    ms.bm.tok_seq = (const int32_t*)(ms.dev + off_tok_seq);
-    ms.bm.tok_pos = (const int32_t*)(ms.dev + off_tok_pos);
     ms.bm.cu_q = (const int32_t*)(ms.dev + off_cu);
     ms.bm.kv_before = (const int32_t*)(ms.dev + off_before);
     ms.bm.page_tables = (const int32_t*)(ms.dev + off_pt);
@@ -845,7 +840,6 @@ int prepare_batch(ss_ctx* c, Shard* s, const ss_batch* b, bool decode, MetaSlot*
     ms.wk.item_order = (const int32_t*)(ms.dev + off_iord);
     ms.wk.n_items = (int)n_items;
     ms.wk.max_items_per_seq = max_items;
-    ms.wk.n_pages = total_pages;
     ms.shard = s;
     ms.version = s->version;
     ms.decode = decode;
@@ -935,15 +929,14 @@ int run_attn_phase(ss_ctx* c, Shard* s, int ll, const ss_batch* b, bool decode, 
     // the product does not read the batch's metadata, what comes behind it does
     if ((rc = norm_gemm(c, x_in, w.wqkv_t, c->ws_qkv.p, nqkv, T, nqkv, ssk::EPI_STORE, rs, ws, st, ms->pending ? ms->job : ssk::UploadJob()))) return rc;
     ms->pending = false;
-    const bool rotates = decode && SSK_CALL(c, attn_decode_rotates, s->nq_l, s->nkv_l, d, ms->bm.n_seqs, ms->wk.n_pages, c->force_generic);
-    if (!rotates) {
+    if (!ms->rotates) {
         ProfScope ps(c, 4, st);
         K_TRY(c, SSK_CALL(c, rope_kvwrite, c->ws_qkv.p, s->nq_l, s->nkv_l, c->d_rope, ms->bm, kv, st));
     }
     if (decode) {
         ProfScope ps(c, 2, st);
         K_TRY(c, SSK_CALL(c, attn_decode, c->ws_qkv.p, c->ws_attn.p, s->nq_l, s->nkv_l, ms->bm, kv, ms->wk,
-                                  rotates ? c->d_rope : nullptr, (float*)c->ws_scratch.p, c->force_generic, st));
+                                  ms->rotates ? c->d_rope : nullptr, (float*)c->ws_scratch.p, c->force_generic, st));
     } else {
         ProfScope ps(c, 1, st);
         K_TRY(c, SSK_CALL(c, attn_prefill, c->ws_qkv.p, c->ws_attn.p, s->nq_l, s->nkv_l, ms->bm, kv,
