@@ -122,12 +122,12 @@ hipError_t head_nt(int dt, const void* A, int lda, const void* Wt, float* C, int
 
 hipError_t gemm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N,
                    int K, int epi, bool force_generic, hipStream_t s, float* ws, size_t ws_bytes, int max_rounds,
-                   const float* row_scale, float norm_eps) {
+                   const float* row_scale) {
     if (M <= 0 || N <= 0) return hipSuccess;
     if (K <= 0 || lda < K || !A || !Wt || !C) return hipErrorInvalidValue;
     if (!row_scale && gemm_norms_itself(dt, A, lda, Wt, M, N, K, epi, force_generic))
-        return gemm_direct(dt, A, lda, Wt, C, ldc, R, M, N, K, epi, norm_eps, nullptr, UploadJob(), s);
-    if (norm_eps >= 0.f || epi == EPI_SWIGLU_HALVES) return hipErrorInvalidValue;     // only the kernel above does these
+        return gemm_direct(dt, A, lda, Wt, C, ldc, R, M, N, K, epi, -1.0f, nullptr, UploadJob(), s);
+    if (epi == EPI_SWIGLU_HALVES) return hipErrorInvalidValue;     // only the kernel above does it
     if (dt == BF16 && !force_generic && gemm_mfma_supported(M, N, K, lda, ldc, epi))
         return gemm_mfma_bf16(A, lda, Wt, C, ldc, R, M, N, K, epi, s, ws, ws_bytes, max_rounds, row_scale);
     if (epi == EPI_SWIGLU) return hipErrorInvalidValue;

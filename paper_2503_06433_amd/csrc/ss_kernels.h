@@ -132,15 +132,17 @@ using namespace ssk;
 // activation or store: the RMSNorm factor of token m when A holds the raw activations and the gains are
 // folded into the weight rows.  Not combined with EPI_RESIDUAL or EPI_STORE_F32 by the large-output and
 // fp32-output kernels (refused there).
-// norm_eps >= 0 instead of a row_scale: the product works out the factor rsqrt(mean(A[m, 0..K)^2) + norm_eps) of its
-// rows by itself.  Only where gemm_norms_itself says so (few rows, or fp32), refused elsewhere; EPI_SWIGLU_HALVES as well.
-bool gemm_norms_itself(int dt, const void* A, int lda, const void* Wt, int M, int N, int K, int epi, bool force_generic);
+// EPI_SWIGLU_HALVES only where gemm_norms_itself says so, refused elsewhere.
 hipError_t gemm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int ldc,
                    const void* R, int M, int N, int K, int epi, bool force_generic,
                    hipStream_t s, float* ws = nullptr, size_t ws_bytes = 0, int max_rounds = 0,
-                   const float* row_scale = nullptr, float norm_eps = -1.0f);
+                   const float* row_scale = nullptr);
 
-// gemm_nt of a product that works its rows' RMSNorm factor out itself (gemm_norms_itself), with an upload.
+// Whether a product is one whose kernel works out the factor rsqrt(mean(A[m, 0..K)^2) + eps) of its rows by itself (few
+// rows, or fp32).
+bool gemm_norms_itself(int dt, const void* A, int lda, const void* Wt, int M, int N, int K, int epi, bool force_generic);
+
+// gemm_nt of such a product with that factor, and with an upload.
 hipError_t norm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int ldc, int M, int N, int K, int epi, float norm_eps,
                    const UploadJob& job, hipStream_t s);
 

@@ -2382,7 +2382,7 @@ int ss_embed(ss_ctx* c, const int32_t* ids, int n, void* x_out, void* stream) {
     return SS_OK;
 }
 
-// The final norm inside the head's product, where the product's kernel does it (few rows, or fp32): *done.
+// The final norm inside the head's product, where the product's kernel does it (up to 64 rows, bf16 and fp32): *done.
 static int head_with_norm(ss_ctx* c, const void* x, int n, float* logits, hipStream_t st, bool* done) {
     const int H = c->m.hidden, V = c->m.vocab;
     *done = c->m.rms_eps >= 0.f && SSK_CALL(c, head_norms_itself, x, H, c->d_wlm_t, c->d_gf, n, V, H, c->force_generic);
