@@ -1,6 +1,6 @@
 """Products whose K ranges meet in memory: tiles over ranges of K, ragged in rows and columns, and the kernel that sums the
 ranges eight columns a thread, where the last of its blocks is partly empty; through the MLP phase of a layer and against the
-CPU oracle.  (test_product_routes.py checks that these products are cut as said here.)"""
+CPU oracle.  (test_product_routes.py checks that every product named here is cut as said.)"""
 import pytest
 import torch
 
@@ -15,8 +15,10 @@ if torch.cuda.is_available():
 
 
 @pytest.mark.parametrize("dtype,T,hidden,ffn", [
-    (wl.BF16, 261, 12288, 1056),       # gate / up in eight ranges: 261 x 132 pieces, 134.6 blocks
-    (wl.F16, 97, 1096, 12800),         # down in eight ranges, with and without a residual: 97 x 137 pieces, 51.9 blocks
+    (wl.BF16, 261, 12288, 1056),       # tiles of the gate / up product in four ranges: 261 x 132 pieces, 134.6 blocks
+    (wl.F16, 97, 1096, 12800),         # register-staged kernel, down in eight ranges, with and without a residual: 97 x 137 pieces, 51.9 blocks
+    (wl.BF16, 601, 4160, 11008),       # persistent kernel, down in four ranges: 601 x 520 pieces, 1220.8 blocks
+    (wl.F16, 700, 4112, 8192),         # ... in four, the last tiles' rows and columns cut short
     (wl.BF16, 81, 8192, 640),          # tiles of the gate / up product in eight ranges
     (wl.F16, 141, 1096, 12288),        # ... of the down projection in eight, the last ones wider than what is left of the output
     (wl.BF16, 333, 2088, 8192),        # ... in four

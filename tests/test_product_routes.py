@@ -103,6 +103,15 @@ def test_tiles_over_ranges_of_long_contractions(rows, n, k, epi, split):
     assert plan(rows, n, k, epi, ws=0)[2] == 1                    # nowhere to put the sums
 
 
+@pytest.mark.parametrize("rows,n,k,epi,kernel,split", [
+    (261, 2112, 12288, EPI_SWIGLU, TILE, 4), (97, 1096, 12800, EPI_RESIDUAL, STAGED, 8), (97, 1096, 12800, EPI_STORE, STAGED, 8),
+    (601, 4160, 11008, EPI_RESIDUAL, STREAM, 4), (601, 4160, 11008, EPI_STORE, STREAM, 4), (700, 4112, 8192, EPI_RESIDUAL, STREAM, 4),
+    (700, 4112, 8192, EPI_STORE, STREAM, 4),
+])
+def test_each_kernel_that_is_cut_has_a_product_whose_sums_are_tested(rows, n, k, epi, kernel, split):
+    assert plan(rows, n, k, epi)[::2] == (kernel, split)
+
+
 def stream_columns(rows, n, k, cus=256):
     f = C.CDLL(_library()).ssk_gemm_stream_columns
     f.argtypes = [C.c_int] * 4 + [C.POINTER(C.c_int)]
