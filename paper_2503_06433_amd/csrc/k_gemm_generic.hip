@@ -104,13 +104,26 @@ hipError_t norm_nt(int dt, const void* A, int lda, const void* Wt, void* C, int 
     return gemm_direct(dt, A, lda, Wt, C, ldc, nullptr, M, N, K, epi, norm_eps, nullptr, job, s);
 }
 
-// Few rows: every column block scales the rows again.  IEEE half keeps the norm apart: a row times its gains has to fit the type
-// before the row's factor brings it to size.
+// Few rows: every column block scales the rows again, which has to cost less than the launch that it saves (2.5 to 4 us).  With the
+// norm apart / inside, us:
+//  - 16-bit, up to 8 rows (blocks of one column tile): contractions of 2048 and more up to 8192 columns (8 rows 4096 x 8192
+//    16.0 / 15.3, 2048 x 16000 15.0 / 16.9, 4096 x 64000 91 / 109; 1024 x 64000 23.5 / 21.5);
+//  - 9 to 16 rows (up to four): all but wide outputs of contractions beyond 4096 (4096 x 32000 44.8 / 43.2, 8192 x 16000 47.4 / 44.4,
+//    8192 x 32000 103.3 / 106.1);
+//  - 17 to 32 rows all that come here (4096 x 8192 18.7 / 16.6); more rows up to 48 rows of 2048 or so (48 rows 2048 x 4096 9.8
+//    / 8.8, 8192 x 512 17.5 / 19.1; 64 rows 1024 x 2048 7.8 / 7.2, 4096 x 2048 13.8 / 15.2);
+//  - fp32: up to 16 rows all (1024 x 64000 47.6 / 44.3), up to 32 rows 16384 columns (4096 x 16000 74.6 / 74.1, 1024 x 32000
+//    36.2 / 37.3), beyond that 8192 (64 rows 1024 x 8192 25.5 / 24.8, x 16000 35.9 / 36.4).
+// IEEE half keeps the norm apart: a row times its gains has to fit the type before the row's factor brings it to size.
 bool head_norms_itself(int dt, const void* A, int lda, const void* Wt, const void* gain, int M, int N, int K, bool force_generic) {
 #ifdef SS_HALF_F16
     if (dt != F32) return false;
 #endif
-    return M <= 64 && ((uintptr_t)gain & 15) == 0 && gemm_norms_itself(dt, A, lda, Wt, M, N, K, EPI_STORE_F32, force_generic);
+    if (M > 64 || ((uintptr_t)gain & 15) != 0 || !gemm_norms_itself(dt, A, lda, Wt, M, N, K, EPI_STORE_F32, force_generic)) return false;
+    if (dt == F32) return M <= 16 || N <= (M <= 32 ? 16384 : 8192);
+    if (M <= 8) return K < 2048 || N <= 8192;
+    if (M <= 16) return K <= 4096 || N <= 16384;
+    return M <= 32 || M * K <= 48 * 2048;
 }
 
 hipError_t head_nt(int dt, const void* A, int lda, const void* Wt, float* C, int ldc, int M, int N, int K, float norm_eps,
@@ -152,4 +165,8 @@ extern "C" int ssk_gemm_plan(int dt, int M, int N, int K, int epi, long long ws_
     return plan.kernel;
 }
 extern "C" int ssk_gemm_stream_columns(int M, int N, int K, int n_cus, int* pick) { return ssk::gemm_stream_columns(M, N, K, n_cus, pick); }
+extern "C" bool ssk_head_norms_itself(int dt, int M, int N, int K) {
+    const void* p = (const void*)(uintptr_t)4096;
+    return ssk::head_norms_itself(dt, p, K, p, p, M, N, K, false);
+}
 #endif

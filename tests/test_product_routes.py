@@ -138,6 +138,20 @@ def test_a_cut_product_keeps_whole_tiles_and_whole_rounds(rows, cus):
             assert c == n or (0 < c < n and c % 256 == 0 and tiles_m * c // 256 <= tiles_m * -(-n // 256) // cus * cus)
 
 
+@pytest.mark.parametrize("dt,rows,hidden,vocab,inside", [
+    (BF16, 8, 4096, 2048, True), (BF16, 8, 4096, 8192, True), (BF16, 8, 4096, 32000, False), (BF16, 1, 5120, 32000, False), (BF16, 8, 1024, 64000, True),
+    (BF16, 9, 4096, 128256, True), (BF16, 16, 8192, 16000, True), (BF16, 16, 8192, 32000, False), (BF16, 32, 4096, 8192, True),
+    (BF16, 32, 4096, 32000, False), (BF16, 48, 2048, 4096, True), (BF16, 48, 4096, 2048, False), (BF16, 64, 1024, 2048, True),
+    (BF16, 64, 4096, 2048, False), (BF16, 65, 256, 512, False),
+    (F32, 4, 256, 512, True), (F32, 16, 4096, 32000, True), (F32, 32, 1024, 16000, True), (F32, 17, 1024, 32000, False), (F32, 64, 256, 512, True),
+    (F32, 64, 1024, 16000, False), (F32, 65, 256, 512, False),
+])
+def test_the_head_takes_its_norm_inside_where_that_saves_time(dt, rows, hidden, vocab, inside):
+    f = C.CDLL(_library()).ssk_head_norms_itself
+    f.restype = C.c_bool
+    assert f(dt, rows, vocab, hidden) == inside
+
+
 @pytest.mark.parametrize("dt,heads,kv_heads,d,seqs,pages,rotates", [
     # the plain kernel: few blocks of 64-wide heads only
     (F32, 4, 1, 64, 128, 400, True), (F32, 16, 16, 64, 32, 32, True), (F32, 16, 16, 64, 33, 3300, False), (F32, 16, 1, 64, 1024, 2048, False),
