@@ -484,12 +484,16 @@ bool gemm_direct_takes(int dt, const void* A, const void* Wt, int M, int N, int 
 //  - 129 to 256 tiles, a block for each: sixteen waves (4096 x 4096 at 8 / 16 rows 9.0 / 9.5 -> 8.5 / 8.9 us, 4096 x 11008 22.6 / 23.4
 //    -> 21.4 / 22.5; 80 tiles, 1280 x 8192 10.5 -> 10.8, stay with eight);
 //  - up to 8 rows one tile and four chunks on their way per wave, whatever the width (22016 x 4096 33.0 us, 34.8 by the rule
-//    above, 12288 x 4096 19.4 and 21.4), but two tiles where one would give a quarter to a half of the units a second long block
-//    (5120 x 13824 36.1 -> 30.6; not 5504 x 4096, 12.4 and 13.8, nor 7168 x 8192, 25.6 and 28.4);
+//    above, 12288 x 4096 19.4 and 21.4), but two tiles for 257 to 384 of them with K of 8192 and more, where some units would
+//    have a second long block (5120 x 13824 36.1 -> 30.6; whole MLPs of 8 rows with one / two: 4112 x 11008 71.3 / 66.7, 4160 x 13824
+//    73.5 / 68.9, 4608 x 11008 69.9 / 66.3, 4864 x 20480 118.7 / 115.6, 5888 x 13824 97.0 / 92.1, 6144 x 8192 62.7 / 62.0; not 5504 x
+//    4096, 12.4 and 13.8, nor 7168 x 8192, 25.6 and 28.4);
 //  - 9 to 16 rows, SwiGLU over 257 to 512 tiles: sixteen waves (7168 x 8192 28.4 -> 25.4, 5504 x 4096 13.8 -> 12.7; without SwiGLU 5120 x
 //    13824 33.3 -> 33.8, 8192 x 3584 12.9 -> 13.1);
-//  - 9 to 16 rows, wider: four tiles where they fill the last round of blocks better than three (14336 x 8192 59.5 -> 47.2, 27648 x
-//    5120 58.1 -> 53.4; 22016 x 4096 stays at three, 35.2, 12288 x 4096 as well, 21.3 and 21.5).
+//  - 9 to 16 rows, wider: four tiles where their rounds of blocks are fuller than with three (14336 x 8192 59.5 -> 47.2, 27648 x
+//    5120 58.1 -> 53.4; 22016 x 4096 stays at three, 35.2, 12288 x 4096 as well, 21.3 and 21.5).  Over 62 such outputs of K 2048
+//    to 8192 3 to 23 % less at 12800 to 64000 columns (4096 x 32000, 2 to 3 % more, and 8192 x 64000 but for); a thirtieth
+//    fuller is not enough (128256 x 4096 188.0 and 194.6).
 // Shorter: 50257 x 768 one tile 27 us, by the rule above 18; 32001 x 1024 21 and 14.
 template <typename T, int MT>
 static hipError_t pick_direct(const void* A, int lda, const void* Wt, void* C, int ldc, const void* R, int M, int N, int K,
@@ -502,9 +506,9 @@ static hipError_t pick_direct(const void* A, int lda, const void* Wt, void* C, i
             if (M <= 8 && tiles > 256 && tiles <= 384 && K >= 8192) SS_GO(2, 8, 2);
             if (M <= 8) SS_GO(1, 8, 4);
             if (tiles > 256 && tiles <= 512 && epi == EPI_SWIGLU) SS_GO(2, 16, 2);
-            if (tiles > 512) {      // three or four tiles a block: the one whose last round of blocks is fuller
+            if (tiles > 512) {      // three or four tiles a block: four if their rounds of blocks are a twentieth fuller
                 const long long b3 = (tiles + 2) / 3, b4 = (tiles + 3) / 4;
-                if (b4 * ((b3 + 255) / 256) > b3 * ((b4 + 255) / 256)) SS_GO(4, 8, 2);
+                if (20 * b4 * ((b3 + 255) / 256) > 21 * b3 * ((b4 + 255) / 256)) SS_GO(4, 8, 2);
             }
         }
     }
