@@ -542,7 +542,9 @@ hipError_t attn_prefill(int dt, const void* qkv, void* out, int n_q, int n_kv, c
 // chain (eight chat users of the 7B shape, eight tokens through two layers 1995 -> 1932 us; six steps of 1024 sequences on one
 // kv head 3161 -> 3114, of 512 on ten heads 7306 -> 7279, of 256 on 32 heads 8081 -> 8034).  Written by this kernel the value
 // alone, in stores of two bytes or as whole 4 KB pieces of the page, cost 50 us a step of 256 sequences on 32 heads: writes
-// between the page reads of the other waves.
+// between the page reads of the other waves.  It wins the launch and its gap, not kernel time (256 sequences on 32 heads, us a
+// step: rotation 17.4 gone, merge 5.0 -> 20.5, this kernel 1153.9 -> 1154.0; 1024 on one head 7.1 gone, 5.0 -> 6.9, 237.8 ->
+// 241.3), so it is left out where the waves are short (attn_decode_rotates).
 // Partial (max, sum, O) of every item go to scratch and are merged per sequence.
 // scratch layout: float [n_items][n_q][D + 4]  (O[D], running max, running sum)
 // ======================================================================

@@ -746,10 +746,14 @@ static hipError_t device_cus(int* out) {
 //  - fewer than 16: no XCD is in step with another, each has a run of whole columns where a group holds all rows; one or
 //    two groups of equal height (9 rows 57344 x 8192 1891 / 1775 / 1728, groups of 5 1537; 13 rows 2655 / 2466 / 2312, of 7
 //    2267; 27648 x 5120 790 / 730 / 703, of 7 715; 22016 x 4096 458 / 451 / 452, of 7 452);
-//    8 rows stay at 4 (27648 x 5120 448 / 448 / 461, 57344 x 8192 1358 / 1322 / 1339);
+//    8 rows stay at 4 (27648 x 5120 448 / 448 / 461, 57344 x 8192 1358 / 1322 / 1339), and so do 16, two whole groups an XCD
+//    where 2 would be four (whole MLPs of 16 rows: 22016 x 4096 868 / 866 / 874, 27648 x 5120 1372 / 1373 / 1369, 57344 x 8192 4241 /
+//    4132 / 4165; of 8: 466 / 463 / 470, 716 / 714 / 707, 2137 / 2091 / 2130);
 //  - fewer than 6 and contractions shorter than 8192: groups of 2, 5 rows 4 (4 rows 27648 x 5120 228 / 242 / 242, 22016 x 4096
 //    197 / 194 / 195; 57344 x 8192 775 / 715 / 725; 5 rows 27648 x 5120 348 / 345 / 362, groups of 5 361; 57344 x 8192 1043 /
-//    974 / 894).
+//    974 / 894; whole MLPs of 5 rows with groups of 2 / 4 / 5: 338 / 331 / 340, 520 / 504 / 516, 1591 / 1534 / 1512).
+// Whole MLPs of these three shapes at 19 heights from 4 to 31 rows, groups of 2 to 8 tried at each: within 2.9 % of the best one,
+// but for 57344 x 8192 at 29 and 30 rows (groups of 3 would be 5 and 7 % faster).
 static int group_rows(int tiles_m, int tiles_n, int K) {
     if (tiles_n < 64 || tiles_m >= 30 || tiles_m == 16 || tiles_m == 8) return 4;
     if (tiles_m > 16) return 2;
