@@ -51,3 +51,30 @@ def test_what_an_earlier_owner_left_is_not_seen(dtype, nq, nkv, d):
         assert torch.isfinite(outs[0]).all()
         for o in outs[1:]:
             assert torch.equal(o, outs[0]), "%s %s behind %s" % (kind, new, before)
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+def test_many_short_sequences_on_recycled_pages(dtype):
+    """4096 waves of the matrix-core kernel and a page or two each: the new tokens are rotated and written in front of it."""
+    cfg = wl.ModelCfg(hidden=128, n_q_heads=32, n_kv_heads=32, head_dim=128, ffn=64, n_layers=1, dtype=dtype)
+    _, raws = wl.make_layer_weights(cfg, 923)
+    gen = torch.Generator(device="cuda").manual_seed(924)
+    fill = lambda *s: torch.empty(s, device="cuda", dtype=torch_dtype(dtype)).normal_(0, 1, generator=gen)
+    desc, ids = pp_desc(cfg), list(range(128))
+    lens = [(16, 1, 30, 32)[i % 4] for i in ids]          # a new page, two inside one, another new page
+    x, cached, outs = fill(128, cfg.hidden), fill(sum(lens) * 2 * 32 * 128), []
+    for bad in (None, float("inf"), float("nan")):
+        ctx = make_context(cfg, pages=128 * 3, max_seq_len=64)
+        ctx.load_layer(desc, 0, raws)
+        if bad is not None:
+            old = [1000 + i for i in ids]
+            ctx.kv_import_dev(desc, old, [48] * 128, torch.full((128 * 48 * 2 * 32 * 128,), bad, device="cuda", dtype=torch_dtype(dtype)))
+            ctx.kv_free(desc, old)
+        ctx.kv_import_dev(desc, ids, lens, cached)
+        out = empty_like_acts(128, cfg.hidden, dtype)
+        ctx.layer_decode(desc, 0, ss.SS_ATTN | ss.SS_NO_RESIDUAL, ids, lens, x, out)
+        torch.cuda.synchronize()
+        outs.append(out.float().cpu())
+        ctx.destroy()
+    assert torch.isfinite(outs[0]).all()
+    assert torch.equal(outs[1], outs[0]) and torch.equal(outs[2], outs[0])
