@@ -846,15 +846,16 @@ static bool decode_mfma(int dt, int n_q, int n_kv, int d, bool force_generic) {
 // / 28.4 us, 64 37.3 / 35.1, 256 of 8 tokens 80 / 65; 16-bit, 64 of 40 25.2 / 26.8, 128 37.3 / 34.5, 512 72 / 54; the tiny fp32
 // model's run of four prompts and eight tokens 494 / 522.  Heads of 128 need 256 registers and more with it: 32 heads over one, 256
 // sequences of 40 tokens 165 / 64, and at 1 to 8 sequences no gain either.
-// The matrix-core kernel rotates but for batches of one query head per kv head with 4096 waves and more and about three pages a
-// sequence, or with more than 16384 waves and one page: there its waves are so short that the loads of cos / sin, of the new
-// key and value show.  Layer call with / without: 256 sequences of 8 / 40 / 100 tokens on 32 heads 112 / 107 us, 130.6 / 128.5,
-// 166 / 172; 512 of 40 on 10 heads 109 / 106; 1024 of 24 on 40 heads 402 / 418; 64 of 40 on 32 heads 65.4 / 67.7; 512 of 40 with
+// The matrix-core kernel rotates but for batches of one query head per kv head and 256 sequences and more (from where the kernel of
+// its own takes several heads a block) with 4096 waves and more and about three pages a sequence, or with more than 16384 waves and
+// one page: there its waves are so short that the loads of cos / sin, of the new key and value show.  Layer call with /
+// without: 256 sequences of 8 / 40 / 100 tokens on 32 heads 112 / 107 us, 130.6 / 128.5, 172.5 / 178.6; 512 of 40 on 10 heads 109 /
+// 106; 1024 of 24 on 40 heads 402 / 418; 64 of 40 on 32 heads 65.4 / 67.7, 128 of one page on 40 111.2 / 115.6; 512 of 40 with
 // four query heads each on 8 113 either way.
 bool attn_decode_rotates(int dt, int n_q, int n_kv, int d, int n_seqs, long long pages, bool force_generic) {
     if (decode_mfma(dt, n_q, n_kv, d, force_generic)) {
         const long long waves = (long long)n_seqs * n_kv;
-        return n_q != n_kv || waves < 4096 || 2 * pages > (waves <= 16384 ? 7 : 2) * (long long)n_seqs;
+        return n_q != n_kv || n_seqs < 256 || waves < 4096 || 2 * pages > (waves <= 16384 ? 7 : 2) * (long long)n_seqs;
     }
     return d == 64 && (long long)n_q * n_seqs <= (dt == F32 ? 512 : 1024);
 }

@@ -31,8 +31,8 @@ LENS = [0, 1, 14, 15, 16, 17, 31, 32, 33, 47, 48, 63, 64, 255, 256, 257, 300, 51
     (wl.F16, 16, 16, 128, LENS),       # two thousand key values a token: some land on a tie
     (wl.F32, 80, 2, 64, LENS[:10]),      # no sequence of more than four pages
     (wl.F32, 8, 2, 128, LENS[:10]),
-    (wl.F16, 41, 41, 128, [0] + [1 + i % 37 for i in range(99)]),
-    (wl.BF16, 32, 32, 128, [0] + [1 + i % 40 for i in range(127)]),      # so many waves of few pages that a kernel of its own does it for both
+    (wl.F16, 17, 17, 128, [0] + [1 + i % 37 for i in range(255)]),
+    (wl.BF16, 16, 16, 128, [0] + [1 + i % 40 for i in range(255)]),      # so many waves of few pages that a kernel of its own does it for both
 ])
 def test_decode_leaves_the_cache_of_a_one_token_prefill(dtype, nq, nkv, d, lens):
     cfg = wl.ModelCfg(hidden=128, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=64, n_layers=1, dtype=dtype)

@@ -56,22 +56,22 @@ def test_what_an_earlier_owner_left_is_not_seen(dtype, nq, nkv, d):
 @pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
 def test_many_short_sequences_on_recycled_pages(dtype):
     """4096 waves of the matrix-core kernel and a page or two each: the new tokens are rotated and written in front of it."""
-    cfg = wl.ModelCfg(hidden=128, n_q_heads=32, n_kv_heads=32, head_dim=128, ffn=64, n_layers=1, dtype=dtype)
+    cfg = wl.ModelCfg(hidden=128, n_q_heads=16, n_kv_heads=16, head_dim=128, ffn=64, n_layers=1, dtype=dtype)
     _, raws = wl.make_layer_weights(cfg, 923)
     gen = torch.Generator(device="cuda").manual_seed(924)
     fill = lambda *s: torch.empty(s, device="cuda", dtype=torch_dtype(dtype)).normal_(0, 1, generator=gen)
-    desc, ids = pp_desc(cfg), list(range(128))
+    desc, ids = pp_desc(cfg), list(range(256))
     lens = [(16, 1, 30, 32)[i % 4] for i in ids]          # a new page, two inside one, another new page
-    x, cached, outs = fill(128, cfg.hidden), fill(sum(lens) * 2 * 32 * 128), []
+    x, cached, outs = fill(256, cfg.hidden), fill(sum(lens) * 2 * 16 * 128), []
     for bad in (None, float("inf"), float("nan")):
-        ctx = make_context(cfg, pages=128 * 3, max_seq_len=64)
+        ctx = make_context(cfg, pages=256 * 3, max_seq_len=64)
         ctx.load_layer(desc, 0, raws)
         if bad is not None:
             old = [1000 + i for i in ids]
-            ctx.kv_import_dev(desc, old, [48] * 128, torch.full((128 * 48 * 2 * 32 * 128,), bad, device="cuda", dtype=torch_dtype(dtype)))
+            ctx.kv_import_dev(desc, old, [48] * 256, torch.full((256 * 48 * 2 * 16 * 128,), bad, device="cuda", dtype=torch_dtype(dtype)))
             ctx.kv_free(desc, old)
         ctx.kv_import_dev(desc, ids, lens, cached)
-        out = empty_like_acts(128, cfg.hidden, dtype)
+        out = empty_like_acts(256, cfg.hidden, dtype)
         ctx.layer_decode(desc, 0, ss.SS_ATTN | ss.SS_NO_RESIDUAL, ids, lens, x, out)
         torch.cuda.synchronize()
         outs.append(out.float().cpu())

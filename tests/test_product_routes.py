@@ -158,7 +158,7 @@ def test_the_head_takes_its_norm_inside_where_that_saves_time(dt, rows, hidden, 
     (BF16, 16, 4, 64, 64, 64, True), (BF16, 16, 4, 64, 65, 6500, False), (F32, 8, 8, 128, 1, 1, False), (BF16, 32, 1, 128, 1, 9, False),
     (BF16, 32, 1, 128, 256, 5000, False),
     # the matrix-core kernel: all but many short sequences of ungrouped heads
-    (BF16, 32, 32, 128, 1, 1, True), (BF16, 32, 32, 128, 127, 127, True), (BF16, 32, 32, 128, 128, 448, False), (BF16, 32, 32, 128, 128, 449, True),
+    (BF16, 32, 32, 128, 1, 1, True), (BF16, 40, 40, 128, 255, 255, True), (BF16, 15, 15, 128, 256, 256, True), (BF16, 16, 16, 128, 256, 896, False), (BF16, 16, 16, 128, 256, 897, True),
     (BF16, 32, 32, 128, 512, 1792, False), (BF16, 32, 32, 128, 513, 514, True), (BF16, 32, 32, 128, 1024, 1024, False),
     (BF16, 64, 8, 128, 1024, 1024, True),
 ])
